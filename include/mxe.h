@@ -200,9 +200,9 @@ mxe_status mxe_spmv(mxe_ctx *ctx, mxe_mat m, int32_t k, const void *X, int64_t l
 #define MXE_SR_OR_AND     2   /* y_i = 1 if a stored v != 0 meets x != 0 in row i, else 0 */
 
 /* Y = M X over `semiring`, otherwise as mxe_spmv (k >= 1, index spaces,
- * storage and accumulation types); the kernel is the column-slab one when the
- * matrix's autotuned (+, *) variant for k is (tuning first if needed), else
- * a row-group kernel. (min, +) and (or, and) results do not depend on the
+ * storage and accumulation types); the kernel is the column-slab or
+ * column-panel one when the matrix's autotuned (+, *) variant for k is
+ * (tuning first if needed), else a row-group kernel. (min, +) and (or, and) results do not depend on the
  * order of the terms, so they are exact: the same bits as a sequential loop
  * over each row in the accumulation type. */
 mxe_status mxe_spmv_semiring(mxe_ctx *ctx, mxe_mat m, int32_t semiring, int32_t k, const void *X,
@@ -248,6 +248,15 @@ mxe_status mxe_scatter_y(mxe_ctx *ctx, mxe_mat b, int32_t k, const void *Yp, int
  * block's columns cluster (the unpermuted, mostly diagonal matrices of
  * Section 7), not after the max-entropy permutation spreads them. */
 #define MXE_VAR_WINDOW  0x600
+/* MXE_VAR_PANEL (lanes ignored, 0; k = 1): a second layout of the entries, cut
+ * into column panels whose x fits the LDS and into chunks of consecutive
+ * rows. One pass multiplies every entry with its x from LDS and streams the
+ * products out (a workspace of one value per entry, taken for the call from
+ * the stream-ordered pool; the call runs as a row-group product when there is
+ * no room for it), a second sums them by row, so no x is gathered from
+ * memory. MXE_ERR_UNSUPPORTED from mxe_set_variant when k > 1 or the layout
+ * does not fit. A batch runs its items on slab layouts instead. */
+#define MXE_VAR_PANEL   0x700
 #define MXE_VARIANT(family, lanes) ((family) | (lanes))
 
 /* Measures the device's random 8-byte gather rate, the ceiling of a sparse

@@ -57,6 +57,7 @@ struct Scratch {
         hipError_t e = hipMallocAsync(&p, std::max<size_t>(bytes, 256), stream);
         if (e != hipSuccess) {
             p = nullptr;
+            (void)hipGetLastError();             // a launch that does without is not to report it
             return hip_fail(e, "hipMallocAsync(workspace)");
         }
         return MXE_OK;
@@ -213,12 +214,15 @@ static SpmvArgs make_args(Matrix &A, int32_t k, const void *X, int64_t ldx, void
     a.bin_off_host = A.bin_off;
     a.merge_coords = A.merge_coords;
     a.coo_row = A.coo_row;
+    a.panel = A.panel.ready ? &A.panel.g : nullptr;
+    a.panel_layout = A.panel.ready ? &A.panel.l : nullptr;
     return a;
 }
 
-// bytes of the launch's own carry workspace: MERGE and COO, else 0
+// bytes of the launch's own workspace: MERGE, COO and PANEL, else 0
 static size_t carry_bytes(const Matrix &A, int variant, int32_t k) {
     const int family = variant & 0xf00;
+    if (family == MXE_VAR_PANEL) return panel_entries(A.panel.g) * (size_t)elem_bytes_of(A.storage);
     if (family == MXE_VAR_MERGE) return merge_carry_bytes(A.nrows, A.nnz);
     if (family == MXE_VAR_COO) return coo_ws_bytes(A.nnz, kclass_of(k), elem_bytes_of(A.storage));
     return 0;
@@ -338,6 +342,86 @@ static mxe_status ensure_window(mxe_ctx *ctx, Matrix &A, Matrix::Slab &sl, hipSt
     return MXE_OK;
 }
 
+// ---- column-panel layout (built once per matrix) -------------------------------------
+
+// Longest row of A; a permuted matrix has its parent's.
+static mxe_status ensure_max_row(Matrix &A, hipStream_t s) {
+    if (A.max_row >= 0) return MXE_OK;
+    Matrix &R = A.parent ? *A.parent : A;
+    if (R.max_row < 0) {
+        Scratch m;
+        mxe_status st = m.alloc(sizeof(int32_t), s);
+        if (st) return st;
+        int32_t v = 0;
+        MXE_HIP(launch_row_max(R.nrows, R.rp, (int32_t *)m.p, s));
+        MXE_HIP(hipMemcpyAsync(&v, m.p, sizeof v, hipMemcpyDeviceToHost, s));
+        MXE_HIP(hipStreamSynchronize(s));
+        R.max_row = v;
+    }
+    A.max_row = R.max_row;
+    return MXE_OK;
+}
+
+static bool matrix_panel_geometry(const mxe_ctx *ctx, const Matrix &A, PanelGeom *g) {
+    return panel_geometry(A.nrows, A.ncols, A.nnz, A.max_row, vtype_of(A.storage), ctx->cu_count, g);
+}
+
+static void drop_panel(mxe_ctx *ctx, Matrix &A, hipStream_t s) {
+    PanelLayout &l = A.panel.l;
+    for (void *p : {(void *)l.offt, (void *)l.crow, (void *)l.c16, (void *)l.pos16, l.val}) {
+        if (!p) continue;
+        A.allocs.erase(std::remove(A.allocs.begin(), A.allocs.end(), p), A.allocs.end());
+        (void)hipFreeAsync(p, s);
+    }
+    A.bytes -= A.panel.bytes;
+    ctx->used -= A.panel.bytes;
+    A.panel = Matrix::Panel();
+}
+
+static mxe_status build_panel(Matrix &A, hipStream_t s) {
+    const PanelGeom &g = A.panel.g;
+    PanelLayout &l = A.panel.l;
+    const int vb = val_bytes_of(A.storage);
+    const size_t n = panel_entries(g);
+    mxe_status st;
+    void *p;
+    if ((st = dev_alloc(A, &p, 4 * panel_offsets_count(g), s))) return st;
+    l.offt = (int32_t *)p;
+    if ((st = dev_alloc(A, &p, 4 * ((size_t)g.chunks + 1), s))) return st;
+    l.crow = (int32_t *)p;
+    if ((st = dev_alloc(A, &p, 2 * n, s))) return st;
+    l.c16 = (uint16_t *)p;
+    if ((st = dev_alloc(A, &p, 2 * n, s))) return st;
+    l.pos16 = (uint16_t *)p;
+    if ((st = dev_alloc(A, &p, (size_t)vb * n, s))) return st;
+    l.val = p;
+    Scratch ws;
+    if ((st = ws.alloc(panel_build_ws_bytes(g), s))) return st;
+    MXE_HIP(launch_panel_build(g, A.rp, A.col, A.val, vb, l, ws.p, s));
+    MXE_HIP(hipStreamSynchronize(s));
+    return MXE_OK;
+}
+
+static mxe_status ensure_panel(mxe_ctx *ctx, Matrix &A, hipStream_t s) {
+    if (A.panel.ready) return MXE_OK;
+    mxe_status st;
+    if ((st = ensure_max_row(A, s))) return st;
+    if (!matrix_panel_geometry(ctx, A, &A.panel.g))
+        return fail(MXE_ERR_UNSUPPORTED, "column-panel layout does not fit this matrix");
+    const PanelGeom &g = A.panel.g;
+    const uint64_t bytes = 4ull * (panel_offsets_count(g) + (size_t)g.chunks + 1) +
+                           (4ull + (uint64_t)val_bytes_of(A.storage)) * panel_entries(g);
+    if ((st = reserve(ctx, bytes))) return st;
+    A.bytes += bytes;
+    A.panel.bytes = bytes;
+    if ((st = build_panel(A, s))) {
+        drop_panel(ctx, A, s);
+        return st;
+    }
+    A.panel.ready = true;
+    return MXE_OK;
+}
+
 static bool slab_family(int variant) {
     return (variant & 0xf00) == MXE_VAR_SLAB || (variant & 0xf00) == MXE_VAR_WINDOW;
 }
@@ -350,6 +434,7 @@ static mxe_status prepare_args(mxe_ctx *ctx, Matrix &A, int variant, int32_t k, 
     if (family == MXE_VAR_BINNED && (st = ensure_bins(ctx, A, s))) return st;
     if (family == MXE_VAR_MERGE && (st = ensure_merge(ctx, A, s))) return st;
     if (family == MXE_VAR_COO && (st = ensure_coo(ctx, A, s))) return st;
+    if (family == MXE_VAR_PANEL && (st = ensure_panel(ctx, A, s))) return st;
     *a = make_args(A, k, X, ldx, Y, ldy);
     if (slab_family(variant)) {
         const Matrix::Slab *sl;
@@ -373,7 +458,8 @@ static mxe_status prepare_args(mxe_ctx *ctx, Matrix &A, int variant, int32_t k, 
 // ---- autotuner ---------------------------------------------------------------------
 // Times every variant (GROUP with 1..64 lanes, BINNED, FIXED, MERGE when
 // k <= 4, SLAB with 0.75, 1, 2 and 4 MiB slabs at two workgroups per CU and
-// 1, 1.25 and 1.5 MiB at one, when the layout fits) on the matrix itself
+// 1, 1.25 and 1.5 MiB at one, WINDOW, PANEL when k = 1, each when its layout
+// fits) on the matrix itself
 // with scratch vectors, times the fastest few again and keeps the winner;
 // also keeps the fastest GROUP lanes for the persistent batch kernel.
 static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneResult *out) {
@@ -407,8 +493,15 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
             window_rows(ctx, g, (int)eb) > 0)
             cands.push_back(v);
     }
+    // last, so that no other candidate's layout misses its place in the budget
+    if (kc == 1) {
+        if ((st = ensure_max_row(A, s))) return st;
+        PanelGeom g;
+        if (matrix_panel_geometry(ctx, A, &g)) cands.push_back(MXE_VARIANT(MXE_VAR_PANEL, 0));
+    }
     std::set<std::tuple<int, int, int>> had;          // layouts other work may be using
     for (const auto &kv : A.slabs) had.insert(kv.first);
+    const bool had_panel = A.panel.ready;
     hipEvent_t e0, e1;
     MXE_HIP(hipEventCreate(&e0));
     MXE_HIP(hipEventCreate(&e1));
@@ -477,6 +570,9 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
         if (result == MXE_OK) {
             const size_t b = std::min_element(total.begin(), total.end()) - total.begin();
             r.variant = timed[b].second;
+            r.batch_variant = r.variant;
+            for (size_t i = 0; i < timed.size() && (r.batch_variant & 0xf00) == MXE_VAR_PANEL; ++i)
+                r.batch_variant = timed[i].second;           // the fastest of stage 1's others
             if (getenv("MXE_LOG"))
                 fprintf(stderr, "[mxe] tune rows=%d k=%d chose 0x%x: %.2f us\n", A.nrows, kc,
                         r.variant, 1e3f * total[b] / 2);
@@ -497,6 +593,8 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
             ++it;
         }
     }
+    if (A.panel.ready && !had_panel && (result != MXE_OK || (r.variant & 0xf00) != MXE_VAR_PANEL))
+        drop_panel(ctx, A, s);
     if (result != MXE_OK) return result;
     ctx->tuned[tune_key(A, k)] = r;
     if (out) *out = r;
@@ -526,12 +624,16 @@ static mxe_status spmv_core(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, i
         if ((st = prepare_args(ctx, A, r.variant, kc, (const char *)X + (size_t)c0 * eb, ldx,
                                (char *)Y + (size_t)c0 * eb, ldy, s, &a)))
             return st;
-        Scratch cw;                             // this launch's carries (MERGE, COO)
-        if (const size_t cb = carry_bytes(A, r.variant, kc)) {
-            if ((st = cw.alloc(cb, s))) return st;
+        Scratch cw;                             // this launch's workspace (MERGE, COO, PANEL)
+        int variant = r.variant;
+        if (const size_t cb = carry_bytes(A, variant, kc)) {
+            st = cw.alloc(cb, s);
+            if (st && (variant & 0xf00) != MXE_VAR_PANEL) return st;
+            // no room for the products: the row kernel needs none
+            if (st) variant = MXE_VARIANT(MXE_VAR_GROUP, r.group_lanes);
             a.carry_ws = cw.p;
         }
-        MXE_HIP(launch_spmv(a, r.variant, s));
+        MXE_HIP(launch_spmv(a, variant, s));
     }
     return MXE_OK;
 }
@@ -743,6 +845,7 @@ mxe_status mxe_permute(mxe_ctx *ctx, mxe_mat a, uint64_t seed, uint32_t mode, vo
     B->nnz = A->nnz;
     B->storage = A->storage;
     B->parent = A;
+    B->max_row = A->max_row;                        // the same rows
     B->seed = seed;
     B->mode = mode;
     void *p;
@@ -990,8 +1093,8 @@ mxe_status mxe_spmv(mxe_ctx *ctx, mxe_mat m, int32_t k, const void *X, int64_t l
 }
 
 // Y = M X over (min, +) or (or, and), 16 columns per launch: on the matrix's
-// column-slab layout when its tuned (+, *) variant is one, else the row-group
-// semiring kernel. For a permuted matrix in the original index space X is
+// column-slab or column-panel layout when its tuned (+, *) variant is one, else
+// the row-group semiring kernel. For a permuted matrix in the original index space X is
 // gathered by cperm and Y scattered by rperm around the product, as for (+, *).
 static mxe_status semiring_core(mxe_ctx *ctx, Matrix &A, int semiring, int32_t k, const void *X,
                                 int64_t ldx, void *Y, int64_t ldy, hipStream_t s) {
@@ -1003,7 +1106,16 @@ static mxe_status semiring_core(mxe_ctx *ctx, Matrix &A, int semiring, int32_t k
         TuneResult r;
         mxe_status st = ensure_variant(ctx, A, kc, s, &r);
         if (st) return st;
-        if (slab_family(r.variant)) {               // the layout; the window is (+, *) only
+        if ((r.variant & 0xf00) == MXE_VAR_PANEL) {
+            SpmvArgs a;
+            if ((st = prepare_args(ctx, A, r.variant, kc, Xc, ldx, Yc, ldy, s, &a))) return st;
+            Scratch cw;
+            if (cw.alloc(carry_bytes(A, r.variant, kc), s) == MXE_OK)
+                MXE_HIP(launch_spmv_panel(*a.panel, *a.panel_layout, a.vtype, semiring, a.rp, Xc, ldx, Yc,
+                                          ldy, cw.p, s));
+            else                                    // no room for the products
+                MXE_HIP(launch_spmv_semiring(a, semiring, s));
+        } else if (slab_family(r.variant)) {        // the layout; the window is (+, *) only
             SpmvArgs a;
             if ((st = prepare_args(ctx, A, r.variant, kc, Xc, ldx, Yc, ldy, s, &a))) return st;
             MXE_HIP(launch_spmv_slab(*a.slab, a.vtype, semiring, a.slab_off, a.slab_idx, a.slab_val,
@@ -1145,8 +1257,16 @@ mxe_status mxe_set_variant(mxe_ctx *ctx, mxe_mat m, int32_t k, int32_t variant) 
         return fail(MXE_ERR_INVALID_ARG, "lanes must be 1..64, a power of two");
     if (family != MXE_VAR_GROUP && family != MXE_VAR_BINNED && family != MXE_VAR_MERGE &&
         family != MXE_VAR_SLAB && family != MXE_VAR_FIXED && family != MXE_VAR_COO &&
-        family != MXE_VAR_WINDOW)
+        family != MXE_VAR_WINDOW && !(family == MXE_VAR_PANEL && lanes == 0))
         return fail(MXE_ERR_INVALID_ARG, "unknown variant family");
+    if (family == MXE_VAR_PANEL) {
+        if (k > 1) return fail(MXE_ERR_UNSUPPORTED, "panel variant handles k = 1");
+        mxe_status st = ensure_max_row(*A, nullptr);
+        if (st) return st;
+        PanelGeom pg;
+        if (!matrix_panel_geometry(ctx, *A, &pg))
+            return fail(MXE_ERR_UNSUPPORTED, "column-panel layout does not fit this matrix");
+    }
     if (slab_family(variant)) {
         SlabGeom sg;
         const int units = slab_units_of(variant);
@@ -1159,9 +1279,11 @@ mxe_status mxe_set_variant(mxe_ctx *ctx, mxe_mat m, int32_t k, int32_t variant) 
     }
     if (family == MXE_VAR_MERGE && kclass_of(k) > 4)
         return fail(MXE_ERR_UNSUPPORTED, "merge-path variant handles k <= 4");
-    TuneResult r{variant, family == MXE_VAR_GROUP ? lanes : 8, true};
+    TuneResult r{variant, family == MXE_VAR_GROUP ? lanes : 8, true, variant};
     auto it = ctx->tuned.find(key);
     if (it != ctx->tuned.end() && family != MXE_VAR_GROUP) r.group_lanes = it->second.group_lanes;
+    // PANEL is no batch unit: batches keep the choice they had, or take slab units
+    if (family == MXE_VAR_PANEL && it != ctx->tuned.end()) r.batch_variant = it->second.batch_variant;
     ctx->tuned[key] = r;
     return MXE_OK;
 }
@@ -1274,14 +1396,15 @@ static mxe_status batch_layout(mxe_ctx *ctx, Matrix &A, int32_t k, int32_t index
                                                  " is not tuned for its k yet");
         *r = tr->second;
     }
-    const bool slab_tuned = slab_family(r->variant);
-    if (!slab_tuned && r->forced) return MXE_OK;                // row tiles
+    const int variant = r->batch_variant;
+    const bool slab_tuned = slab_family(variant);
+    if (!slab_tuned && r->forced && (variant & 0xf00) != MXE_VAR_PANEL) return MXE_OK;                // row tiles
     const int kc = kclass_of(k);
     const int xcd_cus = std::max(1, ctx->cu_count / kBatchQueues);
-    const int units = slab_tuned ? slab_units_of(r->variant) : kBatchSlabUnits;
+    const int units = slab_tuned ? slab_units_of(variant) : kBatchSlabUnits;
     std::vector<int> cus{xcd_cus};
     if (slab_tuned) {
-        cus.push_back(slab_cus_of(ctx, r->variant));
+        cus.push_back(slab_cus_of(ctx, variant));
         if (full) std::swap(cus[0], cus[1]);
     }
     const Matrix::Slab *sl = nullptr;
@@ -1292,7 +1415,7 @@ static mxe_status batch_layout(mxe_ctx *ctx, Matrix &A, int32_t k, int32_t index
     const int min_units = (int)std::min<int64_t>(64, (x_bytes + 64 * 65536 - 1) / (64 * 65536));
     for (int c : cus) {
         // the tuned layout keeps its slabs
-        const int u = (slab_tuned && c == slab_cus_of(ctx, r->variant))
+        const int u = (slab_tuned && c == slab_cus_of(ctx, variant))
                           ? units
                           : std::max(std::min(units, kBatchSlabUnits), min_units);
         if (prepare) {
@@ -1319,7 +1442,12 @@ static mxe_status batch_layout(mxe_ctx *ctx, Matrix &A, int32_t k, int32_t index
 mxe_status prepare_batch_layout(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s) {
     TuneResult r;
     const Matrix::Slab *sl;
-    return batch_layout(ctx, A, k, 0, s, true, false, &r, &sl);
+    mxe_status st = batch_layout(ctx, A, k, 0, s, true, false, &r, &sl);
+    // the layout of rounds with few items: the tuned one, which a product of
+    // MXE_VAR_PANEL does not build by itself
+    if (st == MXE_OK && (r.variant & 0xf00) == MXE_VAR_PANEL)
+        st = batch_layout(ctx, A, k, 0, s, true, true, &r, &sl);
+    return st;
 }
 
 mxe_status batch_item_desc(mxe_ctx *ctx, Matrix &A, const mxe_item &it, int32_t index,

@@ -145,6 +145,37 @@ hipError_t launch_spmv_slab(const SlabGeom &g, int vtype, int semiring, const in
                             int64_t ldx, void *Y, int64_t ldy, const int32_t *wstart, int32_t win,
                             hipStream_t s);
 
+// Column-panel layout (kernels_panel.hip), for one right-hand side.
+struct PanelGeom {
+    int32_t nrows, ncols;
+    int64_t nnz;
+    int32_t wbits, panels;                // panels of 2^wbits columns
+    int32_t chunks, quota, cap;           // chunk b: the rows whose entries start in
+                                          // [b quota, (b + 1) quota), at most cap entries
+    int32_t split;                        // workgroups per panel in the first pass
+};
+struct PanelLayout {
+    int32_t *offt = nullptr;              // [chunks + 1][panels] run starts (last row: panel ends)
+    int32_t *crow = nullptr;              // [chunks + 1] first row of each chunk
+    uint16_t *c16 = nullptr;              // per entry, byte offset of its x in the panel
+    uint16_t *pos16 = nullptr;            // per entry, byte offset of its product's place in LDS
+    void *val = nullptr;
+};
+// false when the matrix cannot use the layout: too many panels, a row too
+// long for a chunk, runs too short, or offsets past 32 bits.
+bool panel_geometry(int32_t nrows, int32_t ncols, int64_t nnz, int32_t max_row, int vtype, int cu_count,
+                    PanelGeom *g);
+size_t panel_offsets_count(const PanelGeom &g);
+size_t panel_entries(const PanelGeom &g); // entries with the runs' padding, at most
+size_t panel_build_ws_bytes(const PanelGeom &g);
+hipError_t launch_panel_build(const PanelGeom &g, const int32_t *rp, const int32_t *col, const void *val,
+                              int val_bytes, const PanelLayout &l, void *ws, hipStream_t s);
+// semiring: MXE_SR_* (mxe.h); k = 1. prod: panel_entries values of the
+// accumulation type, this launch's own.
+hipError_t launch_spmv_panel(const PanelGeom &g, const PanelLayout &l, int vtype, int semiring,
+                             const int32_t *rp, const void *X, int64_t ldx, void *Y, int64_t ldy,
+                             void *prod, hipStream_t s);
+
 struct SpmvArgs {
     int32_t nrows, ncols;
     int64_t nnz;
@@ -162,8 +193,9 @@ struct SpmvArgs {
     // merge variant: the matrix's slice starts (merge_coords_bytes, built once
     // by launch_merge_coords, read only)
     const void *merge_coords;
-    // MERGE / COO: this launch's own carry workspace (merge_carry_bytes /
-    // coo_ws_bytes); never shared between launches that may overlap
+    // MERGE / COO / PANEL: this launch's own workspace (merge_carry_bytes /
+    // coo_ws_bytes / panel_entries products); never shared between launches
+    // that may overlap
     void *carry_ws;
     // slab variant layout (null when not built)
     const SlabGeom *slab;
@@ -175,6 +207,9 @@ struct SpmvArgs {
     int32_t slab_win;
     // COO variant: row index per entry (built once, read only)
     const int32_t *coo_row;
+    // panel variant layout (null when not built); its products go to carry_ws
+    const PanelGeom *panel;
+    const PanelLayout *panel_layout;
 };
 
 size_t merge_coords_bytes(int32_t nrows, int64_t nnz);

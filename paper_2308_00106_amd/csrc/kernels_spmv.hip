@@ -686,6 +686,11 @@ hipError_t launch_spmv(const SpmvArgs &a, int variant, hipStream_t s) {
                                 a.slab_val, a.k, a.X, a.ldx, a.Y, a.ldy, win ? a.slab_wstart : nullptr,
                                 win ? a.slab_win : 0, s);
     }
+    if ((variant & 0xf00) == MXE_VAR_PANEL) {
+        if (!a.panel || !a.panel_layout || a.k != 1) return hipErrorInvalidValue;
+        return launch_spmv_panel(*a.panel, *a.panel_layout, a.vtype, MXE_SR_PLUS_TIMES, a.rp, a.X, a.ldx,
+                                 a.Y, a.ldy, a.carry_ws, s);
+    }
     switch (a.vtype) {
     case VAL_F64: return spmv_t<double, double>(a, variant, s);
     case VAL_F32: return spmv_t<float, float>(a, variant, s);

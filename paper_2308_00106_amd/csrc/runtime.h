@@ -75,6 +75,14 @@ struct Matrix {
     };
     // (k class, slab size in 64 KiB, CUs the geometry is sized for) -> layout
     std::map<std::tuple<int, int, int>, Slab> slabs;
+    // MXE_VAR_PANEL layout (one right-hand side), built on first use
+    struct Panel {
+        PanelGeom g;
+        PanelLayout l;
+        uint64_t bytes = 0;
+        bool ready = false;
+    };
+    Panel panel;
     std::atomic<int> busy{0};           // serving requests queued or running
     std::vector<void *> allocs;         // device allocations to free
     // per stream, an event recorded after the last work queued there on this
@@ -102,6 +110,9 @@ struct TuneResult {
     int variant;
     int group_lanes;
     bool forced = false;                // set by mxe_set_variant, not by the tuner
+    // what a batch item runs as: `variant`, or where that is MXE_VAR_PANEL
+    // (a whole-device product) the fastest of the others
+    int batch_variant = 0;
 };
 
 struct Plan {
