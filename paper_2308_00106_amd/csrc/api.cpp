@@ -652,7 +652,7 @@ mxe_status spmv_internal(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, int6
     if ((st = yp.alloc((size_t)eb * std::max(A.nrows, 1) * k, s))) return st;
     MXE_HIP(launch_gather_rows(A.ncols, k, A.cperm, X, ldx, xp.p, k, eb, s));
     if ((st = spmv_core(ctx, A, k, xp.p, k, yp.p, k, s))) return st;
-    MXE_HIP(launch_scatter_rows(A.nrows, k, A.rperm, yp.p, k, Y, ldy, eb, s));
+    MXE_HIP(launch_scatter_rows(A.nrows, k, A.rperm, A.rinv, yp.p, k, Y, ldy, eb, s));
     return note_use(A, s);
 }
 
@@ -1151,7 +1151,7 @@ mxe_status mxe_spmv_semiring(mxe_ctx *ctx, mxe_mat m, int32_t semiring, int32_t 
     if ((st = yp.alloc((size_t)eb * std::max(A->nrows, 1) * k, s))) return st;
     MXE_HIP(launch_gather_rows(A->ncols, k, A->cperm, X, ldx, xp.p, k, eb, s));
     if ((st = semiring_core(ctx, *A, semiring, k, xp.p, k, yp.p, k, s))) return st;
-    MXE_HIP(launch_scatter_rows(A->nrows, k, A->rperm, yp.p, k, Y, ldy, eb, s));
+    MXE_HIP(launch_scatter_rows(A->nrows, k, A->rperm, A->rinv, yp.p, k, Y, ldy, eb, s));
     return note_use(*A, s);
 }
 
@@ -1189,7 +1189,7 @@ mxe_status mxe_scatter_y(mxe_ctx *ctx, mxe_mat b, int32_t k, const void *Yp, int
         MXE_HIP(launch_copy_cols(B->nrows, k, Yp, ldyp, Y, ldy, eb, s));
         return MXE_OK;
     }
-    MXE_HIP(launch_scatter_rows(B->nrows, k, B->rperm, Yp, ldyp, Y, ldy, eb, s));
+    MXE_HIP(launch_scatter_rows(B->nrows, k, B->rperm, B->rinv, Yp, ldyp, Y, ldy, eb, s));
     return note_use(*B, s);
 }
 

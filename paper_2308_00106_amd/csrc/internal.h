@@ -50,11 +50,13 @@ hipError_t launch_gather_relabel_sort(int32_t nrows, const int32_t *rp, const in
                                       void *val_b, hipStream_t s);
 
 // ---- vectors --------------------------------------------------------------
-// elem_bytes 8 (FP64) or 4 (FP32).
+// Xp row j = X row perm[j], n rows of k values of elem_bytes 8 (FP64) or 4 (FP32).
 hipError_t launch_gather_rows(int32_t n, int32_t k, const int32_t *perm, const void *X,
                               int64_t ldx, void *Xp, int64_t ldxp, int elem_bytes, hipStream_t s);
-hipError_t launch_scatter_rows(int32_t n, int32_t k, const int32_t *perm, const void *Yp,
-                               int64_t ldyp, void *Y, int64_t ldy, int elem_bytes, hipStream_t s);
+// Y row perm[i] = Yp row i; inv is perm's inverse.
+hipError_t launch_scatter_rows(int32_t n, int32_t k, const int32_t *perm, const int32_t *inv,
+                               const void *Yp, int64_t ldyp, void *Y, int64_t ldy, int elem_bytes,
+                               hipStream_t s);
 
 // ---- values ----------------------------------------------------------------
 hipError_t launch_convert_f64(const double *in, void *out, int64_t n, int dtype, hipStream_t s);
