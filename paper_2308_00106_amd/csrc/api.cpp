@@ -872,14 +872,14 @@ mxe_status mxe_permute(mxe_ctx *ctx, mxe_mat a, uint64_t seed, uint32_t mode, vo
                                 permuted_row_ptr_ws_bytes(M)});
     if (grad)
         ws_bytes = std::max({ws_bytes, gradient_perm_ws_bytes(M) + counts_bytes(M),
-                             gradient_perm_ws_bytes(N) + counts_bytes(N)});
+                             counts_bytes(N) + std::max(gradient_perm_ws_bytes(N), line_counts_ws_bytes(A->nnz, N))});
     if ((st = ws.alloc(ws_bytes, s))) return st;
     // gradient formats (Section 8, G-R and G-C): per-line counts go first in
     // the workspace, the shuffle's own workspace after them
     auto gradient = [&](bool rows, int32_t n, uint64_t seed_n, int32_t *perm, int32_t *inv) {
         int32_t *counts = (int32_t *)ws.p;
         void *gws = (char *)ws.p + counts_bytes(n);
-        hipError_t e = launch_line_counts(rows, M, A->nnz, A->rp, A->col, n, counts, s);
+        hipError_t e = launch_line_counts(rows, M, A->nnz, A->rp, A->col, n, counts, gws, s);
         if (e == hipSuccess) e = launch_gradient_perm(n, counts, seed_n, perm, inv, gws, s);
         return e;
     };
@@ -900,7 +900,7 @@ mxe_status mxe_permute(mxe_ctx *ctx, mxe_mat a, uint64_t seed, uint32_t mode, vo
         MXE_HIP(launch_iota_i32(B->cinv, N, s));
     }
     MXE_HIP(launch_permuted_row_ptr(M, A->rp, B->rperm, B->rp, ws.p, s));
-    MXE_HIP(launch_gather_relabel_sort(M, A->rp, A->col, A->val, vb, B->rinv,
+    MXE_HIP(launch_gather_relabel_sort(M, N, A->rp, A->col, A->val, vb, B->rinv,
                                        (mode & MXE_COLS) ? B->cinv : nullptr, B->rp, B->col,
                                        B->val, s));
     if ((st = note_use(*A, s)) || (st = note_use(*B, s))) return st;

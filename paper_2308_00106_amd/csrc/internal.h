@@ -25,9 +25,12 @@ hipError_t launch_random_perm(int64_t n, uint64_t stream_seed, int32_t *perm, in
                               void *ws, hipStream_t s);
 
 // ---- gradient-based shuffle --------------------------------------------------
-// counts[i] = nonzeros of row i (rows) or of column i (!rows, n = ncols).
+// counts[i] = nonzeros of row i (rows) or of column i (!rows, n = ncols; ws:
+// line_counts_ws_bytes(nnz, n)).
+size_t line_counts_ws_bytes(int64_t nnz, int64_t n);
 hipError_t launch_line_counts(bool rows, int32_t nrows, int64_t nnz, const int32_t *rp,
-                              const int32_t *col, int32_t n, int32_t *counts, hipStream_t s);
+                              const int32_t *col, int32_t n, int32_t *counts, void *ws,
+                              hipStream_t s);
 // Pivot at the first maximum of counts[i+1] - counts[i], random permutation
 // of each part, riffle. Synchronizes s once (the pivot sizes the parts).
 // Workspace: gradient_perm_ws_bytes(n).
@@ -44,7 +47,7 @@ hipError_t launch_permuted_row_ptr(int32_t nrows, const int32_t *rp, const int32
 // Row i of A -> row rinv[i] of B (at rp_b[rinv[i]]) with column j -> cinv[j]
 // (cinv may be NULL: no column permutation), re-sorted by new column.
 // val_bytes: 8, 4, 2.
-hipError_t launch_gather_relabel_sort(int32_t nrows, const int32_t *rp, const int32_t *col,
+hipError_t launch_gather_relabel_sort(int32_t nrows, int32_t ncols, const int32_t *rp, const int32_t *col,
                                       const void *val, int val_bytes, const int32_t *rinv,
                                       const int32_t *cinv, const int32_t *rp_b, int32_t *col_b,
                                       void *val_b, hipStream_t s);

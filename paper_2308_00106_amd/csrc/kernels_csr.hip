@@ -295,85 +295,171 @@ __global__ __launch_bounds__(kBlock) void k_perm_row_len(int32_t nrows, const in
     }
 }
 
-constexpr int kSortRows = 16;                           // rows of A per wavefront
-constexpr int kSortStage = 1024;                        // staged entries per wavefront
+constexpr int kSortRows = 16;                           // rows of A per wavefront, at most
+constexpr int64_t kSortFew = 128 * 1024;                // rows below which a wavefront takes half of that
+constexpr int kSortStage = 512;                         // staged entries per wavefront
+constexpr int kSortPairs = 32;                          // rows up to this long are ranked pair by pair
+constexpr int kSortLong = 2 * kSortStage;               // longest row staged alone
 constexpr int kSortWaves = kBlock / kWave;
 
-// Each wavefront moves kSortRows consecutive rows of A (row i goes to row
-// rinv[i] of B, at rp_b[rinv[i]]): it stages the rows' relabelled columns
-// (j -> cinv[j]) in LDS, then every lane takes entries, finds each one's row
-// by binary search over the staged row starts, and writes it at its rank among
-// its row's new columns (distinct, so the rank is its sorted position). Reads
-// stream through A in order, so a matrix whose columns cluster by row keeps
-// its cinv lookups in cache. Groups of rows with more than kSortStage entries
-// are moved one row at a time; a row longer than the stage ranks against
-// cinv in memory.
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_gather_relabel_sort(
-    int32_t nrows, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-    const V *__restrict__ val, const int32_t *__restrict__ rinv, const int32_t *__restrict__ cinv,
-    const int32_t *__restrict__ rp_b, int32_t *__restrict__ col_b, V *__restrict__ val_b) {
-    __shared__ int32_t stage[kSortWaves][kSortStage];
-    __shared__ int32_t rstart[kSortWaves][kSortRows + 1];   // row starts, relative to e0
-    __shared__ int32_t rdest[kSortWaves][kSortRows];        // where each row goes in B
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int64_t r0 = ((int64_t)blockIdx.x * kSortWaves + wave) * kSortRows;
-    if (r0 >= nrows) return;                            // uniform per wavefront
-    const int nr = (int)std::min<int64_t>(kSortRows, nrows - r0);
-    const int32_t e0 = rp[r0];
-    if (lane <= nr) rstart[wave][lane] = rp[r0 + lane] - e0;
-    if (lane < nr) rdest[wave][lane] = rp_b[rinv[r0 + lane]];
+__device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    const int32_t n = rstart[wave][nr];
+}
+
+// Each wavefront moves ROWS consecutive rows of A (row i goes to row
+// rinv[i] of B, at rp_b[rinv[i]]), as many of them at a time as kSortStage
+// entries hold: it stages their relabelled columns (j -> cinv[j]) in LDS, then
+// every lane takes entries, finds each one's row by binary search over the
+// staged row starts, and writes it at its rank among its row's new columns
+// (distinct, so the rank is its sorted position). Reads stream through A in
+// order, so a matrix whose columns cluster by row keeps its cinv lookups in
+// cache. Short rows are ranked pair by pair. Where a row is longer than
+// kSortPairs, the rows are sorted by counting: a row of L entries has L
+// counters, an entry's is the one at c / ncols of them, so that after a random
+// column permutation most hold one entry and a rank takes a few steps instead
+// of L. A band of 10,000 rows of 256 entries in 1M rows of 8 made the kernel
+// take 885 us when its wavefronts ranked them pair by pair, 194 us now; 2M rows of
+// 10 FP64 entries take 289 us either way. A row longer than the stage is ranked pair by pair, from LDS up to kSortLong
+// entries, else against cinv in memory.
+template <typename V, int ROWS>
+__global__ __launch_bounds__(kBlock, 8) void k_gather_relabel_sort(
+    int32_t nrows, float inv_ncols, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+    const V *__restrict__ val, const int32_t *__restrict__ rinv, const int32_t *__restrict__ cinv,
+    const int32_t *__restrict__ rp_b, int32_t *__restrict__ col_b, V *__restrict__ val_b) {
+    __shared__ int32_t buffer[kSortWaves][kSortLong];
+    __shared__ uint32_t counts[kSortWaves][kSortStage / 2];
+    __shared__ int32_t rstart[kSortWaves][ROWS + 1];   // row starts, relative to e0
+    __shared__ int32_t rdest[kSortWaves][ROWS];        // where each row goes in B
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int64_t r0 = ((int64_t)blockIdx.x * kSortWaves + wave) * ROWS;
+    if (r0 >= nrows) return;                            // uniform per wavefront
+    const int nr = (int)std::min<int64_t>(ROWS, nrows - r0);
+    const int32_t e0 = rp[r0];
+    int32_t *stage = buffer[wave], *sorted = buffer[wave] + kSortStage;
+    uint32_t *cnt = counts[wave];
+    const int32_t *rs = rstart[wave];
+    const int32_t start = lane <= nr ? rp[r0 + lane] - e0 : 0;
+    if (lane <= nr) rstart[wave][lane] = start;
+    if (lane < nr) rdest[wave][lane] = rp_b[rinv[r0 + lane]];
+    wave_sync();
     auto relabel = [&](int32_t j) { return cinv ? cinv[j] : j; };
-    if (n <= kSortStage) {
-        for (int32_t i = lane; i < n; i += kWave) stage[wave][i] = relabel(col[e0 + i]);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (int32_t i = lane; i < n; i += kWave) {
-            int lo = 0, hi = nr - 1;                    // last row whose start is <= i
+    for (int j0 = 0, j1; j0 < nr; j0 = j1) {            // rows [j0, j1): at most kSortStage entries
+        const int32_t b0 = rs[j0];
+        const uint64_t fit = __ballot(lane > j0 && lane <= nr && start - b0 <= kSortStage);
+        if (fit == 0) {                                 // a row longer than the stage
+            j1 = j0 + 1;
+            const int32_t b = e0 + b0, len = rs[j1] - b0, d0 = rdest[wave][j0];
+            const bool staged = len <= kSortLong;
+            if (staged)
+                for (int32_t t = lane; t < len; t += kWave) stage[t] = relabel(col[b + t]);
+            wave_sync();
+            for (int32_t t = lane; t < len; t += kWave) {
+                const int32_t c = staged ? stage[t] : relabel(col[b + t]);
+                int32_t r = t;                          // rows only: order unchanged
+                if (cinv) {
+                    r = 0;
+                    if (staged) {
+                        for (int32_t u = 0; u < len; ++u) r += stage[u] < c;
+                    } else {
+                        for (int32_t u = 0; u < len; ++u) r += cinv[col[b + u]] < c;
+                    }
+                }
+                col_b[d0 + r] = c;
+                val_b[d0 + r] = val[b + t];
+            }
+            wave_sync();
+            continue;
+        }
+        j1 = 63 - __builtin_clzll(fit);
+        const int32_t n = rs[j1] - b0;
+        const bool longer = __ballot(lane > j0 && lane <= j1 && start - rs[max(lane - 1, 0)] > kSortPairs) != 0;
+        auto row_of = [&](int32_t i) {                  // last row of the group whose start is <= i
+            int lo = j0, hi = j1 - 1;
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
-                if (rstart[wave][mid] <= i) lo = mid;
+                if (rs[mid] - b0 <= i) lo = mid;
                 else hi = mid - 1;
             }
-            const int32_t b = rstart[wave][lo], e = rstart[wave][lo + 1];
-            const int32_t c = stage[wave][i];
-            int32_t r = i - b;                          // rows only: order unchanged
-            if (cinv) {
-                r = 0;
-                for (int32_t u = b; u < e; ++u) r += stage[wave][u] < c;
-            }
-            col_b[rdest[wave][lo] + r] = c;
-            val_b[rdest[wave][lo] + r] = val[e0 + i];
-        }
-        return;
-    }
-    for (int j = 0; j < nr; ++j) {                      // one row at a time
-        const int32_t b = e0 + rstart[wave][j], len = rstart[wave][j + 1] - rstart[wave][j];
-        const int32_t d0 = rdest[wave][j];
-        const bool staged = len <= kSortStage;
-        if (staged)
-            for (int32_t t = lane; t < len; t += kWave) stage[wave][t] = relabel(col[b + t]);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (int32_t t = lane; t < len; t += kWave) {
-            const int32_t c = staged ? stage[wave][t] : relabel(col[b + t]);
-            int32_t r = t;
-            if (cinv) {
-                r = 0;
-                if (staged) {
-                    for (int32_t u = 0; u < len; ++u) r += stage[wave][u] < c;
-                } else {
-                    for (int32_t u = 0; u < len; ++u) r += cinv[col[b + u]] < c;
+            return lo;
+        };
+        if (!cinv || !longer) {
+            for (int32_t i = lane; i < n; i += kWave) stage[i] = relabel(col[e0 + b0 + i]);
+            wave_sync();
+            for (int32_t i = lane; i < n; i += kWave) {
+                const int j = row_of(i);
+                const int32_t b = rs[j] - b0, e = rs[j + 1] - b0;
+                const int32_t c = stage[i];
+                int32_t r = i - b;                      // rows only: order unchanged
+                if (cinv) {
+                    r = 0;
+                    for (int32_t u = b; u < e; ++u) r += stage[u] < c;
                 }
+                col_b[rdest[wave][j] + r] = c;
+                val_b[rdest[wave][j] + r] = val[e0 + b0 + i];
             }
-            col_b[d0 + r] = c;
-            val_b[d0 + r] = val[b + t];
+            wave_sync();
+            continue;
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        // two counters to a word; after the last pass a counter holds its bucket's end
+        for (int32_t i = lane; i < kSortStage / 2; i += kWave) cnt[i] = 0;
+        for (int32_t i = lane; i < n; i += 4 * kWave) {
+            int32_t j[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) j[u] = i + u * kWave < n ? col[e0 + b0 + i + u * kWave] : 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) j[u] = cinv[j[u]];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i + u * kWave < n) stage[i + u * kWave] = j[u];
+        }
+        wave_sync();
+        // rounding keeps the order of the products, hence of the counters
+        auto bucket_of = [&](int32_t c, int j) {
+            const int32_t len = rs[j + 1] - rs[j];
+            return rs[j] - b0 + min((int32_t)((float)c * inv_ncols * (float)len), len - 1);
+        };
+        for (int32_t i = lane; i < n; i += kWave) {
+            const int32_t k = bucket_of(stage[i], row_of(i));
+            atomicAdd(&cnt[k >> 1], 1u << (k & 1) * 16);
+        }
+        wave_sync();
+        uint32_t v[kSortStage / 2 / kWave], sum = 0;    // counts to starts
+#pragma unroll
+        for (int k = 0; k < kSortStage / 2 / kWave; ++k) {
+            v[k] = cnt[lane * (kSortStage / 2 / kWave) + k];
+            sum += (v[k] & 0xffffu) + (v[k] >> 16);
+        }
+        uint32_t inc = sum;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const uint32_t t = __shfl_up(inc, o);
+            if (lane >= o) inc += t;
+        }
+        inc -= sum;
+#pragma unroll
+        for (int k = 0; k < kSortStage / 2 / kWave; ++k) {
+            cnt[lane * (kSortStage / 2 / kWave) + k] = inc | (inc + (v[k] & 0xffffu)) << 16;
+            inc += (v[k] & 0xffffu) + (v[k] >> 16);
+        }
+        wave_sync();
+        for (int32_t i = lane; i < n; i += kWave) {
+            const int32_t c = stage[i], k = bucket_of(c, row_of(i));
+            sorted[atomicAdd(&cnt[k >> 1], 1u << (k & 1) * 16) >> (k & 1) * 16 & 0xffffu] = c;
+        }
+        wave_sync();
+        const uint16_t *end = reinterpret_cast<const uint16_t *>(cnt);
+        for (int32_t i = lane; i < n; i += kWave) {
+            const int j = row_of(i);
+            const int32_t c = stage[i], k = bucket_of(c, j);
+            const int32_t first = k ? end[k - 1] : 0, past = end[k];
+            int32_t r = first;
+            for (int32_t u = first; u < past; ++u) r += sorted[u] < c;
+            const int32_t d = rdest[wave][j] - (rs[j] - b0) + r;
+            col_b[d] = c;
+            val_b[d] = val[e0 + b0 + i];
+        }
+        wave_sync();
     }
 }
 
@@ -528,6 +614,91 @@ __global__ __launch_bounds__(kBlock) void k_col_counts(int64_t nnz, const int32_
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
          e += (int64_t)gridDim.x * blockDim.x)
         atomicAdd(&counts[col[e]], 1);
+}
+
+// Column counts of a large matrix without an atomic per entry (they run at 28
+// G/s, less where columns are heavy): the entries' columns are bucketed by
+// their high bits, then each bucket is counted in LDS. 10.5M entries over 1M
+// columns, a quarter of them in 14K columns: 372 us with atomics, 85 us here.
+constexpr int kColBlock = 512;
+constexpr int kColMinBits = 12, kColMaxBits = 15;        // columns per bucket: 4096 to 32768
+constexpr int kColBuckets = 1024;
+constexpr int64_t kColChunk = 16384;                     // entries of a bucketing workgroup, at least
+constexpr int64_t kColPiece = 32768;                     // items a workgroup counts
+constexpr int kColPieces = 64;                           // workgroups that share a bucket, at most
+
+// Runs of equal buckets among neighbouring lanes (columns ascend in a row) take
+// one LDS atomic. Returns this lane's place: its run's first, from cursor, plus
+// its index in the run.
+__device__ inline int32_t run_place(int32_t *cursor, int32_t d, bool valid) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t prev = __shfl_up(d, 1);
+    const bool head = valid && (lane == 0 || prev != d);
+    const uint64_t heads = __ballot(head), live = __ballot(valid);
+    int32_t first = 0;
+    if (head) {
+        const uint64_t above = lane == kWave - 1 ? 0ull : heads & (~0ull << (lane + 1));
+        const int end = above ? __builtin_ctzll(above) : 64 - __builtin_clzll(live);
+        first = atomicAdd(&cursor[d], end - lane);
+    }
+    const uint64_t upto = heads & (~0ull >> (kWave - 1 - lane));
+    const int h = upto ? 63 - __builtin_clzll(upto) : 0;
+    return __shfl(first, h) + lane - h;
+}
+
+// counts[d * nwg + w] = entries of workgroup w's range in bucket d
+__global__ __launch_bounds__(kColBlock) void k_col_bucket_count(int64_t nnz, int64_t chunk, int bits, int nd,
+                                                                const int32_t *__restrict__ col,
+                                                                int32_t *__restrict__ counts) {
+    __shared__ int32_t hist[kColBuckets];
+    for (int d = threadIdx.x; d < nd; d += kColBlock) hist[d] = 0;
+    __syncthreads();
+    const int64_t a = blockIdx.x * chunk, b = std::min(a + chunk, nnz);
+    for (int64_t e = a; e < b; e += kColBlock) {         // uniform per workgroup
+        const bool valid = e + threadIdx.x < b;
+        run_place(hist, valid ? col[e + threadIdx.x] >> bits : -1, valid);
+    }
+    __syncthreads();
+    for (int d = threadIdx.x; d < nd; d += kColBlock) counts[(int64_t)d * gridDim.x + blockIdx.x] = hist[d];
+}
+
+// items[place] = the column within its bucket, in any order inside a bucket
+__global__ __launch_bounds__(kColBlock) void k_col_bucket_scatter(int64_t nnz, int64_t chunk, int bits, int nd,
+                                                                  const int32_t *__restrict__ col,
+                                                                  const int32_t *__restrict__ offsets,
+                                                                  uint16_t *__restrict__ items) {
+    __shared__ int32_t cursor[kColBuckets];
+    for (int d = threadIdx.x; d < nd; d += kColBlock) cursor[d] = offsets[(int64_t)d * gridDim.x + blockIdx.x];
+    __syncthreads();
+    const int64_t a = blockIdx.x * chunk, b = std::min(a + chunk, nnz);
+    for (int64_t e = a; e < b; e += kColBlock) {
+        const bool valid = e + threadIdx.x < b;
+        const int32_t c = valid ? col[e + threadIdx.x] : 0;
+        const int32_t at = run_place(cursor, valid ? c >> bits : -1, valid);
+        if (valid) items[at] = (uint16_t)(c & ((1 << bits) - 1));
+    }
+}
+
+// Bucket blockIdx.x's items, shared by as many workgroups as it holds pieces;
+// out is zero where they are several.
+__global__ __launch_bounds__(kColBlock) void k_col_bucket_hist(int32_t n, int bits, int32_t nwg,
+                                                               const int32_t *__restrict__ offsets,
+                                                               const uint16_t *__restrict__ items,
+                                                               int32_t *__restrict__ out) {
+    extern __shared__ int32_t hist[];                    // 1 << bits
+    const int64_t i0 = offsets[(int64_t)blockIdx.x * nwg], m = offsets[(int64_t)(blockIdx.x + 1) * nwg] - i0;
+    const int64_t pieces = std::min<int64_t>(std::max<int64_t>((m + kColPiece - 1) / kColPiece, 1), gridDim.y);
+    if (blockIdx.y >= pieces) return;
+    const int32_t c0 = (int32_t)blockIdx.x << bits, w = min(1 << bits, n - c0);
+    for (int c = threadIdx.x; c < w; c += kColBlock) hist[c] = 0;
+    __syncthreads();
+    const int64_t a = i0 + m * blockIdx.y / pieces, b = i0 + m * (blockIdx.y + 1) / pieces;
+    for (int64_t i = a + threadIdx.x; i < b; i += kColBlock) atomicAdd(&hist[items[i]], 1);
+    __syncthreads();
+    for (int c = threadIdx.x; c < w; c += kColBlock) {
+        if (pieces == 1) out[c0 + c] = hist[c];
+        else if (hist[c]) atomicAdd(&out[c0 + c], hist[c]);
+    }
 }
 
 struct ArgMax { int64_t g; int64_t i; };
@@ -685,28 +856,31 @@ hipError_t launch_permuted_row_ptr(int32_t nrows, const int32_t *rp, const int32
     return launch_exclusive_scan(rp_b, rp_b, (int64_t)nrows + 1, ws, s);
 }
 
-hipError_t launch_gather_relabel_sort(int32_t nrows, const int32_t *rp, const int32_t *col,
+hipError_t launch_gather_relabel_sort(int32_t nrows, int32_t ncols, const int32_t *rp, const int32_t *col,
                                       const void *val, int val_bytes, const int32_t *rinv,
                                       const int32_t *cinv, const int32_t *rp_b, int32_t *col_b,
                                       void *val_b, hipStream_t s) {
     if (nrows <= 0) return hipSuccess;
-    const int64_t g = cdiv(nrows, (int64_t)kSortRows * kSortWaves);
+    const float inv_n = 1.0f / (float)std::max(ncols, 1);
+    // few rows leave CUs idle at kSortRows per wavefront: 4096 rows of 16 took
+    // 10 us, half as many rows each 6.8; 2M rows of 10 fill the lanes better
+    // with all of them (289 against 319 us)
+    const bool few = nrows < kSortFew;
+    const unsigned g = (unsigned)cdiv(nrows, (int64_t)(few ? kSortRows / 2 : kSortRows) * kSortWaves);
+#define MXE_SORT(V, ROWS)                                                                                \
+    hipLaunchKernelGGL((k_gather_relabel_sort<V, ROWS>), dim3(g), dim3(kBlock), 0, s, nrows, inv_n, rp, col, \
+                       (const V *)val, rinv, cinv, rp_b, col_b, (V *)val_b)
+#define MXE_SORT_FEW(V)                   \
+    if (few) MXE_SORT(V, kSortRows / 2);  \
+    else MXE_SORT(V, kSortRows);
     switch (val_bytes) {
-    case 8:
-        hipLaunchKernelGGL(k_gather_relabel_sort<uint64_t>, dim3((unsigned)g), dim3(kBlock), 0, s, nrows, rp,
-                           col, (const uint64_t *)val, rinv, cinv, rp_b, col_b, (uint64_t *)val_b);
-        break;
-    case 4:
-        hipLaunchKernelGGL(k_gather_relabel_sort<uint32_t>, dim3((unsigned)g), dim3(kBlock), 0, s, nrows, rp,
-                           col, (const uint32_t *)val, rinv, cinv, rp_b, col_b, (uint32_t *)val_b);
-        break;
-    case 2:
-        hipLaunchKernelGGL(k_gather_relabel_sort<uint16_t>, dim3((unsigned)g), dim3(kBlock), 0, s, nrows, rp,
-                           col, (const uint16_t *)val, rinv, cinv, rp_b, col_b, (uint16_t *)val_b);
-        break;
-    default:
-        return hipErrorInvalidValue;
+    case 8: MXE_SORT_FEW(uint64_t) break;
+    case 4: MXE_SORT_FEW(uint32_t) break;
+    case 2: MXE_SORT_FEW(uint16_t) break;
+    default: return hipErrorInvalidValue;
     }
+#undef MXE_SORT_FEW
+#undef MXE_SORT
     return hipGetLastError();
 }
 
@@ -812,8 +986,36 @@ hipError_t launch_convert_f64(const double *in, void *out, int64_t n, int dtype,
     return hipGetLastError();
 }
 
+namespace {
+
+// the bucketed column counts of nnz entries over n columns; false where atomics
+// serve: below a million entries they take less than the five launches, and
+// past 2^25 columns the buckets' counters outgrow the LDS
+struct ColBuckets {
+    int bits, nd;
+    int64_t nwg, chunk, ncounts;
+};
+bool col_buckets(int64_t nnz, int64_t n, ColBuckets *c) {
+    if (nnz < (1 << 20) || n > ((int64_t)kColBuckets << kColMaxBits)) return false;
+    c->bits = kColMinBits;
+    while (cdiv(n, int64_t(1) << c->bits) > kColBuckets) ++c->bits;
+    c->nd = (int)cdiv(n, int64_t(1) << c->bits);
+    c->chunk = std::max(kColChunk, cdiv(cdiv(nnz, 4096), kColBlock) * kColBlock);
+    c->nwg = cdiv(nnz, c->chunk);
+    c->ncounts = c->nwg * c->nd + 1;
+    return true;
+}
+
+}  // namespace
+
+size_t line_counts_ws_bytes(int64_t nnz, int64_t n) {
+    ColBuckets c;
+    if (!col_buckets(nnz, n, &c)) return 0;
+    return align256(sizeof(int32_t) * c.ncounts) + align256(sizeof(uint16_t) * nnz) + scan_ws_bytes(c.ncounts);
+}
+
 hipError_t launch_line_counts(bool rows, int32_t nrows, int64_t nnz, const int32_t *rp,
-                              const int32_t *col, int32_t n, int32_t *counts, hipStream_t s) {
+                              const int32_t *col, int32_t n, int32_t *counts, void *ws, hipStream_t s) {
     if (rows) {
         if (nrows <= 0) return hipSuccess;
         hipLaunchKernelGGL(k_row_counts, dim3(grid_for(nrows, kBlock, 16384)), dim3(kBlock), 0, s,
@@ -822,8 +1024,23 @@ hipError_t launch_line_counts(bool rows, int32_t nrows, int64_t nnz, const int32
     }
     hipError_t e = launch_fill_i32(counts, n, 0, s);
     if (e != hipSuccess || nnz <= 0) return e;
-    hipLaunchKernelGGL(k_col_counts, dim3(grid_for(nnz, kBlock, 16384)), dim3(kBlock), 0, s, nnz,
-                       col, counts);
+    ColBuckets c;
+    if (!col_buckets(nnz, n, &c)) {
+        hipLaunchKernelGGL(k_col_counts, dim3(grid_for(nnz, kBlock, 16384)), dim3(kBlock), 0, s, nnz,
+                           col, counts);
+        return hipGetLastError();
+    }
+    char *w = (char *)ws;
+    int32_t *off = (int32_t *)w;     w += align256(sizeof(int32_t) * c.ncounts);
+    uint16_t *items = (uint16_t *)w; w += align256(sizeof(uint16_t) * nnz);
+    if ((e = launch_fill_i32(off + c.ncounts - 1, 1, 0, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_col_bucket_count, dim3((unsigned)c.nwg), dim3(kColBlock), 0, s, nnz, c.chunk, c.bits,
+                       c.nd, col, off);
+    if ((e = launch_exclusive_scan(off, off, c.ncounts, w, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_col_bucket_scatter, dim3((unsigned)c.nwg), dim3(kColBlock), 0, s, nnz, c.chunk, c.bits,
+                       c.nd, col, (const int32_t *)off, items);
+    hipLaunchKernelGGL(k_col_bucket_hist, dim3(c.nd, kColPieces), dim3(kColBlock), sizeof(int32_t) << c.bits, s, n,
+                       c.bits, (int32_t)c.nwg, (const int32_t *)off, (const uint16_t *)items, counts);
     return hipGetLastError();
 }
 
