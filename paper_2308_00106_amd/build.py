@@ -18,7 +18,7 @@ LIB = os.path.join(PKG, "libmxe.so")
 
 SOURCES = ["kernels_csr.hip", "kernels_entropy.hip", "kernels_spmv.hip", "kernels_slab.hip", "kernels_panel.hip",
            "kernels_batch.hip", "kernels_probe.hip", "api.cpp", "serve.cpp", "batch_noalloc.cpp"]
-HEADERS = ["device_common.h", "internal.h", "runtime.h", "slab_device.h", "spmv_device.h"]
+HEADERS = ["device_common.h", "device_pool.h", "internal.h", "runtime.h", "slab_device.h", "spmv_device.h"]
 
 ARCH = "gfx950"
 CFLAGS = [

@@ -43,20 +43,21 @@ static int vtype_of(mxe_dtype d) { return d == MXE_F64 ? VAL_F64 : d == MXE_F32 
 
 namespace {
 
-// Stream-ordered allocation from the device's pool (freed blocks stay cached).
+// A workspace of one call on one stream, from the context's pool.
 struct Scratch {
     void *p = nullptr;
     hipStream_t s = nullptr;
+    DevicePool *pool = nullptr;
     Scratch() = default;
     Scratch(const Scratch &) = delete;
     ~Scratch() {
-        if (p) (void)hipFreeAsync(p, s);
+        if (p) pool->put(p, s);
     }
-    mxe_status alloc(size_t bytes, hipStream_t stream) {
+    mxe_status alloc(DevicePool &from, size_t bytes, hipStream_t stream) {
         s = stream;
-        hipError_t e = hipMallocAsync(&p, std::max<size_t>(bytes, 256), stream);
+        pool = &from;
+        hipError_t e = from.get(&p, std::max<size_t>(bytes, 256), stream);
         if (e != hipSuccess) {
-            p = nullptr;
             (void)hipGetLastError();             // a launch that does without is not to report it
             return hip_fail(e, "hipMallocAsync(workspace)");
         }
@@ -64,13 +65,30 @@ struct Scratch {
     }
 };
 
+Matrix::Use *use_of(Matrix &m, hipStream_t s) {
+    for (Matrix::Use &u : m.uses)
+        if (u.s == s) return &u;
+    Matrix::Use u{s, nullptr, false};
+    if (m.pool->event(&u.ev) != hipSuccess) return nullptr;
+    m.uses.push_back(u);
+    return &m.uses.back();
+}
+
 mxe_status dev_alloc(Matrix &m, void **p, size_t bytes, hipStream_t s) {
-    hipError_t e = hipMallocAsync(p, std::max<size_t>(bytes, 256), s);
-    if (e != hipSuccess) {
-        *p = nullptr;
-        return hip_fail(e, "hipMallocAsync(matrix)");
-    }
+    Matrix::Use *u = use_of(m, s);
+    if (!u) return fail(MXE_ERR_DEVICE, "no event for a matrix");
+    hipError_t e = m.pool->get(p, std::max<size_t>(bytes, 256), s);
+    if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(matrix)");
+    u->late = true;
     m.allocs.push_back(*p);
+    return MXE_OK;
+}
+
+// Waits for s, on which m's memory was taken and filled.
+mxe_status settle(Matrix &m, hipStream_t s) {
+    MXE_HIP(hipStreamSynchronize(s));
+    for (Matrix::Use &u : m.uses)
+        if (u.s == s) u.late = false;
     return MXE_OK;
 }
 
@@ -97,16 +115,19 @@ mxe_status reserve(mxe_ctx *ctx, uint64_t bytes) {
 // other streams and unrelated work are not waited for.
 std::shared_ptr<Matrix> make_matrix(mxe_ctx *ctx) {
     int dev = ctx->device;
-    return std::shared_ptr<Matrix>(new Matrix(), [ctx, dev](Matrix *m) {
+    std::shared_ptr<Matrix> A(new Matrix(), [ctx, dev](Matrix *m) {
         DeviceGuard g(dev);
         for (const Matrix::Use &u : m->uses) {
+            if (u.late && hipEventRecord(u.ev, u.s) != hipSuccess) (void)hipDeviceSynchronize();
             (void)hipEventSynchronize(u.ev);
-            (void)hipEventDestroy(u.ev);
+            ctx->pool.put_event(u.ev);
         }
-        for (void *p : m->allocs) (void)hipFreeAsync(p, nullptr);
+        for (void *p : m->allocs) ctx->pool.put_idle(p);
         ctx->used -= m->bytes;
         delete m;
     });
+    A->pool = &ctx->pool;
+    return A;
 }
 
 int64_t root_of(const Matrix &m) { return m.parent ? m.parent->id : m.id; }
@@ -114,15 +135,10 @@ int64_t root_of(const Matrix &m) { return m.parent ? m.parent->id : m.id; }
 }  // namespace
 
 mxe_status note_use(Matrix &A, hipStream_t s) {
-    for (Matrix::Use &u : A.uses)
-        if (u.s == s) {
-            MXE_HIP(hipEventRecord(u.ev, s));
-            return MXE_OK;
-        }
-    Matrix::Use u{s, nullptr};
-    MXE_HIP(hipEventCreateWithFlags(&u.ev, hipEventDisableTiming));
-    A.uses.push_back(u);
-    MXE_HIP(hipEventRecord(u.ev, s));
+    Matrix::Use *u = use_of(A, s);
+    if (!u) return fail(MXE_ERR_DEVICE, "no event for a matrix");
+    MXE_HIP(hipEventRecord(u->ev, s));
+    u->late = false;
     return MXE_OK;
 }
 
@@ -148,12 +164,12 @@ static mxe_status ensure_bins(mxe_ctx *, Matrix &A, hipStream_t s) {
     if (st) return st;
     A.bin_off_dev = (int32_t *)p;
     Scratch ws;
-    if ((st = ws.alloc(row_bins_ws_bytes(A.nrows), s))) return st;
+    if ((st = ws.alloc(*A.pool, row_bins_ws_bytes(A.nrows), s))) return st;
     MXE_HIP(launch_row_bins(A.nrows, A.rp, A.bin_list, A.bin_off_dev, ws.p, s));
     MXE_HIP(launch_row_max(A.nrows, A.rp, A.bin_off_dev + kNumBins + 1, s));
     int32_t host[kNumBins + 2];
     MXE_HIP(hipMemcpyAsync(host, A.bin_off_dev, sizeof host, hipMemcpyDeviceToHost, s));
-    MXE_HIP(hipStreamSynchronize(s));
+    if ((st = settle(A, s))) return st;
     std::memcpy(A.bin_off, host, sizeof A.bin_off);
     A.max_row = host[kNumBins + 1];
     A.bins_ready = true;
@@ -174,7 +190,7 @@ static mxe_status ensure_merge(mxe_ctx *ctx, Matrix &A, hipStream_t s) {
     void *p;
     if ((st = dev_alloc(A, &p, bytes, s))) return st;
     MXE_HIP(launch_merge_coords(A.nrows, A.nnz, A.rp, p, s));
-    MXE_HIP(hipStreamSynchronize(s));
+    if ((st = settle(A, s))) return st;
     A.merge_coords = p;
     return MXE_OK;
 }
@@ -189,7 +205,7 @@ static mxe_status ensure_coo(mxe_ctx *ctx, Matrix &A, hipStream_t s) {
     void *r;
     if ((st = dev_alloc(A, &r, 4 * (size_t)A.nnz, s))) return st;
     MXE_HIP(launch_coo_rows(A.nrows, A.rp, (int32_t *)r, s));
-    MXE_HIP(hipStreamSynchronize(s));
+    if ((st = settle(A, s))) return st;
     A.coo_row = (int32_t *)r;
     return MXE_OK;
 }
@@ -292,9 +308,9 @@ static mxe_status ensure_slab(mxe_ctx *ctx, Matrix &A, int kclass, int units, in
     if ((st = dev_alloc(A, &p, (size_t)vb * A.nnz, s))) return st;
     sl.val = p;
     Scratch ws;
-    if ((st = ws.alloc(slab_build_ws_bytes(sl.g), s))) return st;
+    if ((st = ws.alloc(ctx->pool, slab_build_ws_bytes(sl.g), s))) return st;
     MXE_HIP(launch_slab_build(sl.g, A.rp, A.col, A.val, vb, sl.off, sl.idx, sl.val, ws.p, s));
-    MXE_HIP(hipStreamSynchronize(s));
+    if ((st = settle(A, s))) return st;
     *out = &(A.slabs[key] = sl);
     return MXE_OK;
 }
@@ -306,7 +322,7 @@ static void drop_slab(mxe_ctx *ctx, Matrix &A, const Matrix::Slab &sl, hipStream
     for (void *p : {(void *)sl.off, (void *)sl.idx, sl.val, (void *)sl.wstart}) {
         if (!p) continue;
         A.allocs.erase(std::remove(A.allocs.begin(), A.allocs.end(), p), A.allocs.end());
-        (void)hipFreeAsync(p, s);
+        A.pool->put(p, s);
     }
     A.bytes -= bytes;
     ctx->used -= bytes;
@@ -336,7 +352,7 @@ static mxe_status ensure_window(mxe_ctx *ctx, Matrix &A, Matrix::Slab &sl, hipSt
     void *p;
     if ((st = dev_alloc(A, &p, bytes, s))) return st;
     MXE_HIP(launch_slab_window(sl.g, A.rp, A.col, win, (int32_t *)p, s));
-    MXE_HIP(hipStreamSynchronize(s));
+    if ((st = settle(A, s))) return st;
     sl.wstart = (int32_t *)p;
     sl.win = win;
     return MXE_OK;
@@ -350,7 +366,7 @@ static mxe_status ensure_max_row(Matrix &A, hipStream_t s) {
     Matrix &R = A.parent ? *A.parent : A;
     if (R.max_row < 0) {
         Scratch m;
-        mxe_status st = m.alloc(sizeof(int32_t), s);
+        mxe_status st = m.alloc(*A.pool, sizeof(int32_t), s);
         if (st) return st;
         int32_t v = 0;
         MXE_HIP(launch_row_max(R.nrows, R.rp, (int32_t *)m.p, s));
@@ -371,7 +387,7 @@ static void drop_panel(mxe_ctx *ctx, Matrix &A, hipStream_t s) {
     for (void *p : {(void *)l.offt, (void *)l.crow, (void *)l.c16, (void *)l.pos16, l.val}) {
         if (!p) continue;
         A.allocs.erase(std::remove(A.allocs.begin(), A.allocs.end(), p), A.allocs.end());
-        (void)hipFreeAsync(p, s);
+        A.pool->put(p, s);
     }
     A.bytes -= A.panel.bytes;
     ctx->used -= A.panel.bytes;
@@ -396,9 +412,9 @@ static mxe_status build_panel(Matrix &A, hipStream_t s) {
     if ((st = dev_alloc(A, &p, (size_t)vb * n, s))) return st;
     l.val = p;
     Scratch ws;
-    if ((st = ws.alloc(panel_build_ws_bytes(g), s))) return st;
+    if ((st = ws.alloc(*A.pool, panel_build_ws_bytes(g), s))) return st;
     MXE_HIP(launch_panel_build(g, A.rp, A.col, A.val, vb, l, ws.p, s));
-    MXE_HIP(hipStreamSynchronize(s));
+    if ((st = settle(A, s))) return st;
     return MXE_OK;
 }
 
@@ -467,8 +483,8 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
     const int kc = kclass_of(k);
     const size_t eb = elem_bytes_of(A.storage);
     Scratch xs, ys;
-    if ((st = xs.alloc(eb * (size_t)std::max(A.ncols, 1) * kc, s))) return st;
-    if ((st = ys.alloc(eb * (size_t)std::max(A.nrows, 1) * kc, s))) return st;
+    if ((st = xs.alloc(ctx->pool, eb * (size_t)std::max(A.ncols, 1) * kc, s))) return st;
+    if ((st = ys.alloc(ctx->pool, eb * (size_t)std::max(A.nrows, 1) * kc, s))) return st;
     MXE_HIP(hipMemsetAsync(xs.p, 0, eb * (size_t)std::max(A.ncols, 1) * kc, s));
     std::vector<int> cands;
     for (int l = 1; l <= 64; l <<= 1) cands.push_back(MXE_VARIANT(MXE_VAR_GROUP, l));
@@ -512,7 +528,7 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
         if (st2) return st2;
         Scratch cw;
         if (const size_t cb = carry_bytes(A, v, kc)) {
-            if ((st2 = cw.alloc(cb, s))) return st2;
+            if ((st2 = cw.alloc(ctx->pool, cb, s))) return st2;
             a.carry_ws = cw.p;
         }
         hipError_t e = launch_spmv(a, v, s);
@@ -627,7 +643,7 @@ static mxe_status spmv_core(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, i
         Scratch cw;                             // this launch's workspace (MERGE, COO, PANEL)
         int variant = r.variant;
         if (const size_t cb = carry_bytes(A, variant, kc)) {
-            st = cw.alloc(cb, s);
+            st = cw.alloc(ctx->pool, cb, s);
             if (st && (variant & 0xf00) != MXE_VAR_PANEL) return st;
             // no room for the products: the row kernel needs none
             if (st) variant = MXE_VARIANT(MXE_VAR_GROUP, r.group_lanes);
@@ -648,8 +664,8 @@ mxe_status spmv_internal(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, int6
     const int eb = elem_bytes_of(A.storage);
     Scratch xp, yp;
     mxe_status st;
-    if ((st = xp.alloc((size_t)eb * std::max(A.ncols, 1) * k, s))) return st;
-    if ((st = yp.alloc((size_t)eb * std::max(A.nrows, 1) * k, s))) return st;
+    if ((st = xp.alloc(ctx->pool, (size_t)eb * std::max(A.ncols, 1) * k, s))) return st;
+    if ((st = yp.alloc(ctx->pool, (size_t)eb * std::max(A.nrows, 1) * k, s))) return st;
     MXE_HIP(launch_gather_rows(A.ncols, k, A.cperm, X, ldx, xp.p, k, eb, s));
     if ((st = spmv_core(ctx, A, k, xp.p, k, yp.p, k, s))) return st;
     MXE_HIP(launch_scatter_rows(A.nrows, k, A.rperm, A.rinv, yp.p, k, Y, ldy, eb, s));
@@ -757,6 +773,7 @@ mxe_status mxe_destroy(mxe_ctx *ctx) {
         ctx->plans.clear();
         ctx->mats.clear();
     }
+    DeviceGuard g(ctx->device);
     delete ctx;
     return MXE_OK;
 }
@@ -810,12 +827,12 @@ mxe_status mxe_register_matrix(mxe_ctx *ctx, int32_t nrows, int32_t ncols, int64
             MXE_HIP(hipMemcpyAsync(A->val, vals, 8 * (size_t)nnz, kind, s));
         } else {
             Scratch tmp;
-            if ((st = tmp.alloc(8 * (size_t)nnz, s))) return st;
+            if ((st = tmp.alloc(ctx->pool, 8 * (size_t)nnz, s))) return st;
             MXE_HIP(hipMemcpyAsync(tmp.p, vals, 8 * (size_t)nnz, kind, s));
             MXE_HIP(launch_convert_f64((const double *)tmp.p, A->val, nnz, vtype_of(storage), s));
         }
     }
-    MXE_HIP(hipStreamSynchronize(s));
+    if ((st = settle(*A, s))) return st;
     A->id = ctx->next_id++;
     ctx->mats[A->id] = A;
     *out = A->id;
@@ -873,7 +890,7 @@ mxe_status mxe_permute(mxe_ctx *ctx, mxe_mat a, uint64_t seed, uint32_t mode, vo
     if (grad)
         ws_bytes = std::max({ws_bytes, gradient_perm_ws_bytes(M) + counts_bytes(M),
                              counts_bytes(N) + std::max(gradient_perm_ws_bytes(N), line_counts_ws_bytes(A->nnz, N))});
-    if ((st = ws.alloc(ws_bytes, s))) return st;
+    if ((st = ws.alloc(ctx->pool, ws_bytes, s))) return st;
     // gradient formats (Section 8, G-R and G-C): per-line counts go first in
     // the workspace, the shuffle's own workspace after them
     auto gradient = [&](bool rows, int32_t n, uint64_t seed_n, int32_t *perm, int32_t *inv) {
@@ -1006,9 +1023,9 @@ mxe_status mxe_entropy(mxe_ctx *ctx, mxe_mat m, int32_t grid_rows, int32_t grid_
     }
     Scratch hdev, ws, res;
     mxe_status st;
-    if ((st = hdev.alloc(4 * (size_t)bins, s))) return st;
-    if ((st = ws.alloc(entropy_ws_bytes(bins), s))) return st;
-    if ((st = res.alloc(4 * sizeof(double), s))) return st;
+    if ((st = hdev.alloc(ctx->pool, 4 * (size_t)bins, s))) return st;
+    if ((st = ws.alloc(ctx->pool, entropy_ws_bytes(bins), s))) return st;
+    if ((st = res.alloc(ctx->pool, 4 * sizeof(double), s))) return st;
     MXE_HIP(launch_block_hist(A->nrows, A->ncols, A->nnz, A->rp, A->col, grid_rows, grid_cols,
                               (uint32_t *)hdev.p, s));
     MXE_HIP(launch_entropy((const uint32_t *)hdev.p, bins, (double *)res.p, ws.p, s));
@@ -1051,9 +1068,9 @@ mxe_status mxe_entropy_levels(mxe_ctx *ctx, mxe_mat m, int32_t grid_rows, int32_
     hipStream_t s = (hipStream_t)stream;
     Scratch hdev, ws, res;
     mxe_status st;
-    if ((st = hdev.alloc(4 * (size_t)bins, s))) return st;
-    if ((st = ws.alloc(entropy_regions_ws_bytes(grid_rows, grid_cols, levels, nlevels), s))) return st;
-    if ((st = res.alloc(4 * sizeof(double) * (size_t)nreg, s))) return st;
+    if ((st = hdev.alloc(ctx->pool, 4 * (size_t)bins, s))) return st;
+    if ((st = ws.alloc(ctx->pool, entropy_regions_ws_bytes(grid_rows, grid_cols, levels, nlevels), s))) return st;
+    if ((st = res.alloc(ctx->pool, 4 * sizeof(double) * (size_t)nreg, s))) return st;
     MXE_HIP(launch_block_hist(A->nrows, A->ncols, A->nnz, A->rp, A->col, grid_rows, grid_cols,
                               (uint32_t *)hdev.p, s));
     MXE_HIP(launch_entropy_regions((const uint32_t *)hdev.p, grid_rows, grid_cols, levels, nlevels,
@@ -1110,7 +1127,7 @@ static mxe_status semiring_core(mxe_ctx *ctx, Matrix &A, int semiring, int32_t k
             SpmvArgs a;
             if ((st = prepare_args(ctx, A, r.variant, kc, Xc, ldx, Yc, ldy, s, &a))) return st;
             Scratch cw;
-            if (cw.alloc(carry_bytes(A, r.variant, kc), s) == MXE_OK)
+            if (cw.alloc(ctx->pool, carry_bytes(A, r.variant, kc), s) == MXE_OK)
                 MXE_HIP(launch_spmv_panel(*a.panel, *a.panel_layout, a.vtype, semiring, a.rp, Xc, ldx, Yc,
                                           ldy, cw.p, s));
             else                                    // no room for the products
@@ -1147,8 +1164,8 @@ mxe_status mxe_spmv_semiring(mxe_ctx *ctx, mxe_mat m, int32_t semiring, int32_t 
     }
     const int eb = elem_bytes_of(A->storage);
     Scratch xp, yp;
-    if ((st = xp.alloc((size_t)eb * std::max(A->ncols, 1) * k, s))) return st;
-    if ((st = yp.alloc((size_t)eb * std::max(A->nrows, 1) * k, s))) return st;
+    if ((st = xp.alloc(ctx->pool, (size_t)eb * std::max(A->ncols, 1) * k, s))) return st;
+    if ((st = yp.alloc(ctx->pool, (size_t)eb * std::max(A->nrows, 1) * k, s))) return st;
     MXE_HIP(launch_gather_rows(A->ncols, k, A->cperm, X, ldx, xp.p, k, eb, s));
     if ((st = semiring_core(ctx, *A, semiring, k, xp.p, k, yp.p, k, s))) return st;
     MXE_HIP(launch_scatter_rows(A->nrows, k, A->rperm, A->rinv, yp.p, k, Y, ldy, eb, s));
@@ -1219,7 +1236,7 @@ mxe_status mxe_probe_gather(mxe_ctx *ctx, int64_t table_bytes, int64_t gathers, 
     const int32_t grid = ctx->cu_count * 8;
     Scratch ws;
     mxe_status st;
-    if ((st = ws.alloc(probe_gather_ws_bytes(table_bytes, grid), s))) return st;
+    if ((st = ws.alloc(ctx->pool, probe_gather_ws_bytes(table_bytes, grid), s))) return st;
     MXE_HIP(hipMemsetAsync(ws.p, 0, (size_t)table_bytes, s));
     hipEvent_t e0, e1;
     MXE_HIP(hipEventCreate(&e0));
@@ -1552,8 +1569,8 @@ mxe_status mxe_spmv_batch(mxe_ctx *ctx, int32_t count, const mxe_item *items, vo
     const int32_t grid = batch_grid_size(vt, lds);
     if (grid < 1) return fail(MXE_ERR_DEVICE, "batch kernel occupancy query failed");
     Scratch dd, ctr;
-    if ((st = dd.alloc(sizeof(BatchDesc) * descs.size(), s))) return st;
-    if ((st = ctr.alloc(sizeof(int32_t) * (kBatchQueues + qent.size()), s))) return st;
+    if ((st = dd.alloc(ctx->pool, sizeof(BatchDesc) * descs.size(), s))) return st;
+    if ((st = ctr.alloc(ctx->pool, sizeof(int32_t) * (kBatchQueues + qent.size()), s))) return st;
     int32_t *counters = (int32_t *)ctr.p;
     MXE_HIP(hipStreamSynchronize(s));     // pool blocks ready before the blocking copies
     MXE_HIP(hipMemcpy(dd.p, descs.data(), sizeof(BatchDesc) * descs.size(), hipMemcpyHostToDevice));

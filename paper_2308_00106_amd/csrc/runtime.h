@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/mxe.h"
+#include "device_pool.h"
 #include "internal.h"
 
 namespace mxe {
@@ -84,12 +85,16 @@ struct Matrix {
     };
     Panel panel;
     std::atomic<int> busy{0};           // serving requests queued or running
-    std::vector<void *> allocs;         // device allocations to free
+    DevicePool *pool = nullptr;         // its context's
+    std::vector<void *> allocs;         // device allocations to give back
     // per stream, an event recorded after the last work queued there on this
-    // matrix: freeing waits for these, never for the whole device
+    // matrix: freeing waits for these, never for the whole device. late: work
+    // on memory taken since may follow the event (a build that failed half
+    // way); freeing then records it anew
     struct Use {
         hipStream_t s;
         hipEvent_t ev;
+        bool late;
     };
     std::vector<Use> uses;
 };
@@ -162,6 +167,7 @@ struct Server;
 
 struct mxe_ctx {
     int device = 0;
+    mxe::DevicePool pool;               // outlives the matrices below
     uint64_t budget = 0;                // 0: no cap
     std::atomic<uint64_t> used{0};      // resident bytes
     std::recursive_mutex mu;            // serializes non-serving calls
