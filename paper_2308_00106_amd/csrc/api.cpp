@@ -1497,7 +1497,7 @@ mxe_status batch_item_desc(mxe_ctx *ctx, Matrix &A, const mxe_item &it, int32_t 
         d.slab_off = sl->off;
         d.slab_idx = sl->idx;
         d.slab_val = sl->val;
-        d.vec_x = slab_vec_x(d.kclass, it.k, it.X, it.ldx, eb) ? 1 : 0;
+        d.x32 = slab_x32(it.ldx, eb, A.ncols);
         *lds = std::max(*lds, (size_t)sl->g.rows_per_block * d.kclass * eb);
     }
     d.unit0 = 0;
@@ -1649,7 +1649,7 @@ mxe_status mxe_batch_launch(mxe_ctx *ctx, mxe_plan h, const mxe_item *items, voi
                 d.ldx = a.ldx;
                 d.ldy = a.ldy;
                 if (d.slab_off)
-                    d.vec_x = slab_vec_x(d.kclass, d.k, d.X, d.ldx, d.vtype == VAL_F64 ? 8 : 4) ? 1 : 0;
+                    d.x32 = slab_x32(d.ldx, d.vtype == VAL_F64 ? 8 : 4, d.slab.ncols);
                 changed = true;
             }
         }

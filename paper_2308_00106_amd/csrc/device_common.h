@@ -184,11 +184,40 @@ template <typename T> struct Semiring<2, T> {
 // Inclusive segmented scan over a wavefront whose keys never decrease
 // (equal keys are adjacent; real keys stay below 0xfffffffe, padding lanes
 // carry 0xffffffff after every real one), on DPP lane moves instead of LDS
-// permutes:
-// four row_shr steps inside each row of 16 lanes, then row_bcast:15 into rows
-// 1 and 3 and row_bcast:31 into rows 2 and 3. A lane adds the moved value only
-// when it carries its own key; moves from outside a row read key 0 and value
-// 0 (adding nothing), and rows a broadcast skips keep a key no row can have.
+// permutes: four row_shr steps inside each row of 16 lanes, then row_bcast:15
+// into rows 1 and 3 and row_bcast:31 into rows 2 and 3. A lane adds the moved
+// value only when it carries its own key; moves from outside a row read value 0
+// (adding nothing), and rows a broadcast skips keep a key no row can have.
+// A step in which no lane has anything to take is left out: the wavefront's
+// chunk of a wide product holds a few entries of a row at most, and with 8
+// right-hand sides the six steps were three quarters of the product's
+// instructions (see slab_block for what that cost).
+//
+// same: the lanes that carry the key of the lane before them.
+__device__ inline uint64_t same_as_before(uint32_t key) {
+    const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)0xfffffffeu, (int)key, 0x138, 0xf, 0xf,
+                                                                false);          // wave_shr:1
+    return __builtin_amdgcn_ballot_w64(prev == key && key != 0xffffffffu);
+}
+__device__ inline bool in_lanes(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// the lanes that take from 1, 2, 4 and 8 lanes before them in their row of
+// 16, and whether a run of equal keys crosses the rows' edges
+struct ScanSteps {
+    uint64_t take[4];
+    bool rows01_23, rows1_2;
+};
+__device__ inline ScanSteps scan_steps(uint64_t same) {
+    ScanSteps s;
+    const uint64_t s2 = same & (same << 1), s4 = s2 & (s2 << 2), s8 = s4 & (s4 << 4);
+    s.take[0] = same & 0xfffefffefffefffeull;
+    s.take[1] = s2 & 0xfffcfffcfffcfffcull;
+    s.take[2] = s4 & 0xfff0fff0fff0fff0ull;
+    s.take[3] = s8 & 0xff00ff00ff00ff00ull;
+    s.rows01_23 = same & 0x0001000000010000ull;
+    s.rows1_2 = same & 0x0000000100000000ull;
+    return s;
+}
 // CTRL: a row shift, row_shr:n (0x110 + n) or row_shl:n (0x100 + n)
 template <int CTRL>
 __device__ inline uint32_t dpp_shr_u32(uint32_t v) {
@@ -219,26 +248,35 @@ __device__ inline float dpp_bcast(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, RMASK, 0xf, false));
 }
 
-template <int CTRL, typename T, int KM>
-__device__ inline void scan_shr(uint32_t key, T (&v)[KM]) {
+// ALL: every lane's key is compared and no step left out.
+template <int N, bool ALL, typename T, int KM>
+__device__ inline void scan_shr(uint32_t key, uint64_t take, T (&v)[KM]) {
+    constexpr int CTRL = 0x110 + N;                           // row_shr:N
+    if constexpr (!ALL) {
+        if (take == 0) return;
+    }
     if constexpr (sizeof(T) == 4) {
-        // FP32: each lane zeroes what the lane n places on in its row must
-        // not take (the row_shl:n move of the key gives that lane's key), so
+        // FP32: each lane zeroes what the lane N places on in its row must
+        // not take (the row_shl:N move of the key gives that lane's key), so
         // the move folds into a DPP add: two instructions per value, not
         // three. The same terms are added in the same order.
-        constexpr int kShl = CTRL - 0x10;                     // row_shl:n for row_shr:n
-        const bool keep = dpp_shr_u32<kShl>(key) == key;
+        bool keep;
+        if constexpr (ALL) keep = dpp_shr_u32<0x100 + N>(key) == key;
+        else keep = in_lanes(take >> N);
+        T w[KM];                                              // all first: a DPP move waits for its source
 #pragma unroll
-        for (int q = 0; q < KM; ++q) {
-            const T w = keep ? v[q] : T(0);
-            v[q] += dpp_shr<CTRL>(w);
-        }
+        for (int q = 0; q < KM; ++q) w[q] = keep ? v[q] : T(0);
+        if constexpr (KM > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < KM; ++q) v[q] += dpp_shr<CTRL>(w[q]);
     } else {
-        const bool take = dpp_shr_u32<CTRL>(key) == key;
+        bool mine;
+        if constexpr (ALL) mine = dpp_shr_u32<CTRL>(key) == key;
+        else mine = in_lanes(take);
 #pragma unroll
         for (int q = 0; q < KM; ++q) {
             const T m = dpp_shr<CTRL>(v[q]);
-            v[q] += take ? m : T(0);
+            v[q] += mine ? m : T(0);
         }
     }
 }
@@ -276,24 +314,36 @@ __device__ inline void scan_step_op(uint32_t key, T (&v)[KM]) {
         v[q] = take ? Op::add(v[q], m) : v[q];
     }
 }
-template <typename Op, typename T, int KM>
-__device__ inline void segmented_scan_op(uint32_t key, T (&v)[KM]) {
-    scan_step_op<0x111, 0xf, Op>(key, v);
-    scan_step_op<0x112, 0xf, Op>(key, v);
-    scan_step_op<0x114, 0xf, Op>(key, v);
-    scan_step_op<0x118, 0xf, Op>(key, v);
-    scan_step_op<0x142, 0xa, Op>(key, v);
-    scan_step_op<0x143, 0xc, Op>(key, v);
+template <bool ALL, typename Op, typename T, int KM>
+__device__ inline void segmented_scan_op(uint32_t key, uint64_t same, T (&v)[KM]) {
+    ScanSteps s{};
+    if constexpr (!ALL) {
+        if (same == 0) return;
+        s = scan_steps(same);
+    }
+    if (ALL || s.take[0]) scan_step_op<0x111, 0xf, Op>(key, v);
+    if (ALL || s.take[1]) scan_step_op<0x112, 0xf, Op>(key, v);
+    if (ALL || s.take[2]) scan_step_op<0x114, 0xf, Op>(key, v);
+    if (ALL || s.take[3]) scan_step_op<0x118, 0xf, Op>(key, v);
+    if (ALL || s.rows01_23) scan_step_op<0x142, 0xa, Op>(key, v);
+    if (ALL || s.rows1_2) scan_step_op<0x143, 0xc, Op>(key, v);
 }
 
-template <typename T, int KM>
-__device__ inline void segmented_scan(uint32_t key, T (&v)[KM]) {
-    scan_shr<0x111>(key, v);            // row_shr:1
-    scan_shr<0x112>(key, v);            // row_shr:2
-    scan_shr<0x114>(key, v);            // row_shr:4
-    scan_shr<0x118>(key, v);            // row_shr:8
-    scan_bcast<0x142, 0xa>(key, v);     // row_bcast:15 -> rows 1, 3
-    scan_bcast<0x143, 0xc>(key, v);     // row_bcast:31 -> rows 2, 3
+// ALL: the steps in one stream of instructions, for one right-hand side, where
+// choosing them costs more than the moves (same is not used then).
+template <bool ALL, typename T, int KM>
+__device__ inline void segmented_scan(uint32_t key, uint64_t same, T (&v)[KM]) {
+    ScanSteps s{};
+    if constexpr (!ALL) {
+        if (same == 0) return;
+        s = scan_steps(same);
+    }
+    scan_shr<1, ALL>(key, s.take[0], v);
+    scan_shr<2, ALL>(key, s.take[1], v);
+    scan_shr<4, ALL>(key, s.take[2], v);
+    scan_shr<8, ALL>(key, s.take[3], v);
+    if (ALL || s.rows01_23) scan_bcast<0x142, 0xa>(key, v);   // row_bcast:15 -> rows 1, 3
+    if (ALL || s.rows1_2) scan_bcast<0x143, 0xc>(key, v);     // row_bcast:31 -> rows 2, 3
 }
 
 }  // namespace mxe

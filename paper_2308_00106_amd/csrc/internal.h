@@ -124,14 +124,11 @@ size_t slab_build_ws_bytes(const SlabGeom &g);
 hipError_t launch_slab_build(const SlabGeom &g, const int32_t *rp, const int32_t *col,
                              const void *val, int val_bytes, int32_t *off, uint32_t *idx_out,
                              void *val_out, void *ws, hipStream_t s);
-// Whole X rows may be read as 16-byte vectors when each row is exactly kclass
-// values (elem_bytes each) on a 16-byte boundary: never a read past a row's k
-// values.
-inline bool slab_vec_x(int kclass, int32_t k, const void *X, int64_t ldx, int elem_bytes) {
-    // the slab kernel reads an X row min(16, kclass x elem_bytes) bytes at a time
-    const int64_t vb = (int64_t)kclass * elem_bytes < 16 ? (int64_t)kclass * elem_bytes : 16;
-    return kclass > 1 && k == kclass && (ldx * elem_bytes) % vb == 0 &&
-           (reinterpret_cast<uintptr_t>(X) % vb) == 0;
+// Column x stride in bytes is a product of 24 bits each below 2^32: one
+// instruction per X row where the 64-bit product takes the time of eight.
+inline bool slab_x32(int64_t ldx, int elem_bytes, int32_t ncols) {
+    return ncols <= (1 << 24) && ldx * elem_bytes < (1 << 24) &&
+           (int64_t)ncols * ldx * elem_bytes < (int64_t(1) << 32);
 }
 // The x window of MXE_VAR_WINDOW: in a block's dynamic LDS, after its partial
 // y (rows_per_block x kclass values of elem_bytes), 16-byte aligned.
@@ -249,7 +246,7 @@ struct BatchDesc {             // one piece of one batch item (device-resident t
     // so one product can serve several requests' Y (device arrays of k)
     void *const *ycol;
     const int64_t *ycol_ld;
-    int32_t vec_x;             // slab units: whole X rows as vector loads (slab_vec_x)
+    int32_t x32;               // slab units: slab_x32
     // slab units (slab_off non-null): one work unit per block of this layout
     // for k class kclass, in place of row tiles
     SlabGeom slab;

@@ -48,7 +48,7 @@ batch_unit(const BatchDesc &d, int32_t u, int q, unsigned char *smem, int32_t (*
         const int64_t *ycl = d.ycol_ld ? as_global(d.ycol_ld) : nullptr;
 #define MXE_BATCH_SLAB(KMV)                                                                        \
     slab_block<V, T, KMV, 0, false, kBatchInflight>(d.slab, u, q, so, si, sv, d.k, X, d.ldx, Y,     \
-                                                   d.ldy, d.vec_x, yp, soff, tid, nullptr, 0, 0,  \
+                                                   d.ldy, d.x32, yp, soff, tid, nullptr, 0, 0,  \
                                                    yc, ycl)
         switch (d.slab.kclass) {
         case 1: MXE_BATCH_SLAB(1); break;

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kSlabBlock) void k_spmv_slab(SlabGeom g, const int3
                                                           const V *__restrict__ val, int32_t k,
                                                           const T *__restrict__ X, int64_t ldx,
                                                           T *__restrict__ Y, int64_t ldy,
-                                                          int vec_x, const int32_t *__restrict__ wstart,
+                                                          int x32, const int32_t *__restrict__ wstart,
                                                           int32_t win, int prio) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int32_t soff[kSubBlocks][kSlabMax + 1];
@@ -167,11 +167,11 @@ __global__ __launch_bounds__(kSlabBlock) void k_spmv_slab(SlabGeom g, const int3
     if constexpr (WIN) {
         T *xw = yp + slab_window_offset(g, (int)sizeof(T)) / sizeof(T);
         slab_block<V, T, KM, SR, true>(g, blockIdx.x, blockIdx.x % 8, off, idx, val, k, X, ldx, Y,
-                                       ldy, vec_x, yp, soff, threadIdx.x, xw, wstart[blockIdx.x], win,
+                                       ldy, x32, yp, soff, threadIdx.x, xw, wstart[blockIdx.x], win,
                                        nullptr, nullptr, prio != 0);
     } else {
         slab_block<V, T, KM, SR>(g, blockIdx.x, blockIdx.x % 8, off, idx, val, k, X, ldx, Y, ldy,
-                                 vec_x, yp, soff, threadIdx.x, nullptr, 0, 0, nullptr, nullptr,
+                                 x32, yp, soff, threadIdx.x, nullptr, 0, 0, nullptr, nullptr,
                                  prio != 0);
     }
 }
@@ -193,18 +193,18 @@ hipError_t slab_launch(const SlabGeom &g, const int32_t *off, const uint32_t *id
                        int32_t k, const void *X, int64_t ldx, void *Y, int64_t ldy,
                        const int32_t *wstart, int32_t win, hipStream_t s) {
     size_t lds = (size_t)g.rows_per_block * KM * sizeof(T);
-    const int vec_x = slab_vec_x(KM, k, X, ldx, (int)sizeof(T));
+    const int x32 = slab_x32(ldx, (int)sizeof(T), g.ncols);
     if constexpr (SR == 0) {
         if (win > 0) {
             lds = slab_window_offset(g, (int)sizeof(T)) + (size_t)win * KM * sizeof(T);
             hipLaunchKernelGGL((k_spmv_slab<V, T, KM, SR, true>), dim3(g.blocks), dim3(kSlabBlock),
                                lds, s, g, off, idx, (const V *)val, k, (const T *)X, ldx, (T *)Y,
-                               ldy, vec_x, wstart, win, gather_prio(g, win));
+                               ldy, x32, wstart, win, gather_prio(g, win));
             return hipGetLastError();
         }
     }
     hipLaunchKernelGGL((k_spmv_slab<V, T, KM, SR, false>), dim3(g.blocks), dim3(kSlabBlock), lds, s,
-                       g, off, idx, (const V *)val, k, (const T *)X, ldx, (T *)Y, ldy, vec_x,
+                       g, off, idx, (const V *)val, k, (const T *)X, ldx, (T *)Y, ldy, x32,
                        (const int32_t *)nullptr, 0, gather_prio(g, 0));
     return hipGetLastError();
 }

@@ -411,7 +411,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_coo(int32_t nrows, int64_t nnz,
 #pragma unroll
             for (int q = 0; q < KM; ++q) prod[q] += carry[q];
         }
-        segmented_scan<T, KM>(key, prod);                      // inclusive, by row
+        segmented_scan<true>(key, 0, prod);                      // inclusive, by row
         const uint32_t nxt = __shfl_down(key, 1);
         const bool seg_end = valid && (lane == kWave - 1 || nxt != key);
         const bool to_next = seg_end && e + 1 < e1 && nr == (int32_t)key;

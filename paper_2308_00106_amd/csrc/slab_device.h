@@ -13,12 +13,15 @@ constexpr int kSlabBlock = 1024;                    // 16 wavefronts
 constexpr int kSubBlocks = kSlabBlock / kWave;      // wavefront sub-blocks per block
 constexpr int kSlabMax = 64;                        // column slabs per layout
 // 64-entry chunks each wavefront keeps in flight. IF = 0 (the single-product
-// kernels): four for one or two right-hand sides, two for four, one above.
+// kernels): 64 bytes of x per lane, at most four chunks. With several
+// right-hand sides a wavefront has about one chunk per slab, so a chunk past
+// the group's end is skipped, but two of a group wait for their x together.
 // IF > 0 (the persistent batch kernel): as many as keep about IF bytes of x
 // per lane in flight, 1 to 8.
 template <int KM, typename T, int IF> struct SlabUnroll {
     static constexpr int B = IF / (KM * (int)sizeof(T));
-    static constexpr int value = IF == 0 ? (KM <= 2 ? 4 : KM <= 4 ? 2 : 1) : B < 1 ? 1 : B > 8 ? 8 : B;
+    static constexpr int F = 64 / (KM * (int)sizeof(T)), L = F < 1 ? 1 : F > 4 ? 4 : F;
+    static constexpr int value = IF == 0 ? L : B < 1 ? 1 : B > 8 ? 8 : B;
 };
 template <typename V, typename T> struct SlabVal;
 template <> struct SlabVal<double, double> {
@@ -31,6 +34,47 @@ template <> struct SlabVal<uint16_t, float> {
     __device__ static float get(uint16_t v) { return bf16_to_f32(v); }
 };
 
+// The k values of an X row, 16 bytes at a time as long as they last, whatever
+// the row's alignment: 16 bytes of a row cost the L1 one access, as a single
+// value does. 500K rows of 12 FP32 entries with 5 right-hand sides take 79 us,
+// read value by value 112.
+template <typename T, int KM>
+__device__ __attribute__((always_inline)) inline void load_x(const char *row, int32_t k, T (&x)[KM]) {
+    constexpr int W = (16 / (int)sizeof(T)) < KM ? 16 / (int)sizeof(T) : KM;
+    typedef T vec_t __attribute__((ext_vector_type(W), aligned(sizeof(T))));
+    typedef T two_t __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+    const T *xr = reinterpret_cast<const T *>(row);
+    if (k == KM) {                                            // no branch between the loads
+#pragma unroll
+        for (int q = 0; q < KM; q += W) {
+            const vec_t w = *reinterpret_cast<const vec_t *>(xr + q);
+#pragma unroll
+            for (int r = 0; r < W; ++r) x[q + r] = w[r];
+        }
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < KM; q += W) {
+        if (q + W <= k) {
+            const vec_t w = *reinterpret_cast<const vec_t *>(xr + q);
+#pragma unroll
+            for (int r = 0; r < W; ++r) x[q + r] = w[r];
+            continue;
+        }
+#pragma unroll
+        for (int r = 0; r < W; r += 2) {
+            if (q + r + 2 <= k) {
+                const two_t w = *reinterpret_cast<const two_t *>(xr + q + r);
+                x[q + r] = w[0];
+                x[q + r + 1] = w[1];
+            } else {
+                x[q + r] = q + r < k ? xr[q + r] : T(0);
+                x[q + r + 1] = T(0);
+            }
+        }
+    }
+}
+
 // Block `block` of the layout, by a workgroup of kSlabBlock threads; tid is
 // the thread's index in it. The workgroup walks the slabs in a rotation that
 // starts at the slab tied to XCD `xcd` (its own XCD; in a batch, the XCD of
@@ -40,21 +84,26 @@ template <> struct SlabVal<uint16_t, float> {
 // gathers together, then reduces each chunk by row. The first batch of the
 // next slab's group is loaded before each barrier. yp: LDS for the block's
 // partial y (rows_per_block x KM values of T); soff: LDS for the wavefronts'
-// group offsets; vec_x: X rows are read as vectors of min(16, KM x sizeof(T))
-// bytes (slab_vec_x). The
+// group offsets; x32: slab_x32, 32-bit offsets of X rows. The
 // caller separates two calls on one workgroup by a barrier.
 // WIN: X rows [w0, w0 + win) are first copied to LDS (xw, win x KM values of
 // T), and entries whose column falls there read x from LDS instead of
 // gathering it (the same values, so the same sums).
 // ycol (may be null): column q of the result goes to ycol[q] (its row 0)
 // with leading dimension ycol_ld[q] instead of Y + q with ldy.
+// What bounds it: with one right-hand side the L2's request rate (one per
+// entry), with several the latency of a slab's gathers and the wavefronts'
+// instructions. With the sums' idle steps left out (segmented_scan), two chunks
+// in flight and 24-bit row offsets, 1.16M rows of 12 FP32 entries and k = 8 went
+// from 153 to 116 us (0.75 MiB slabs), 700K rows of 10 FP64 entries and k = 4
+// from 122 to 63.
 // prio (one right-hand side): the wavefront raises its issue priority while
 // it sends out a batch's x gathers and drops it for the reductions.
 template <typename V, typename T, int KM, int SR, bool WIN = false, int IF = 0>
 __device__ __attribute__((always_inline)) inline void
 slab_block(const SlabGeom &g, int32_t block, int xcd, const int32_t *__restrict__ off,
            const uint32_t *__restrict__ idx, const V *__restrict__ val, int32_t k,
-           const T *__restrict__ X, int64_t ldx, T *__restrict__ Y, int64_t ldy, int vec_x,
+           const T *__restrict__ X, int64_t ldx, T *__restrict__ Y, int64_t ldy, int x32,
            T *yp, int32_t (*soff)[kSlabMax + 1], int tid, T *xw = nullptr, int32_t w0 = 0,
            int32_t win = 0, void *const *ycol = nullptr, const int64_t *ycol_ld = nullptr,
            bool prio = false) {
@@ -93,7 +142,8 @@ slab_block(const SlabGeom &g, int32_t block, int xcd, const int32_t *__restrict_
     load_batch(soff[wave][s0], soff[wave][s0 + 1]);
     for (int t = 0; t < g.slabs; ++t) {                       // same count in every wavefront
         const int s = s0 + t < g.slabs ? s0 + t : s0 + t - g.slabs;
-        const int32_t b = soff[wave][s], e = soff[wave][s + 1];
+        const int32_t b = __builtin_amdgcn_readfirstlane(soff[wave][s]);
+        const int32_t e = __builtin_amdgcn_readfirstlane(soff[wave][s + 1]);
         for (int32_t c = b; c < e; c += kD * kWave) {
             if (c != b) load_batch(c, e);                     // the first batch is already loaded
             T xv[kD][KM];
@@ -102,6 +152,7 @@ slab_block(const SlabGeom &g, int32_t block, int xcd, const int32_t *__restrict_
             }
 #pragma unroll
             for (int j = 0; j < kD; ++j) {
+                if (KM > 2 && j > 0 && c + j * kWave >= e) break;      // uniform per wavefront
                 const bool v = u[j] != 0xffffffffu;
                 if constexpr (WIN) {
                     const uint32_t d = (u[j] & cmask) - (uint32_t)w0;
@@ -111,22 +162,15 @@ slab_block(const SlabGeom &g, int32_t block, int xcd, const int32_t *__restrict_
                         continue;
                     }
                 }
-                const T *xr = X + (int64_t)(v ? (u[j] & cmask) : 0) * ldx;
-                if constexpr (KM > 1) {
-                    if (vec_x) {                              // k == KM, rows aligned to the vector
-                        constexpr int W = (16 / (int)sizeof(T)) < KM ? 16 / (int)sizeof(T) : KM;
-                        typedef T vec_t __attribute__((ext_vector_type(W)));
-#pragma unroll
-                        for (int q = 0; q < KM; q += W) {
-                            const vec_t w = *reinterpret_cast<const vec_t *>(xr + q);
-#pragma unroll
-                            for (int r = 0; r < W; ++r) xv[j][q + r] = v ? w[r] : T(0);
-                        }
-                        continue;
-                    }
+                const uint32_t col = v ? u[j] & cmask : 0;        // padding reads row 0 into no row's sum
+                if constexpr (KM == 1) {
+                    xv[j][0] = v ? X[(int64_t)col * ldx] : T(0);
+                } else if (x32) {
+                    load_x<T, KM>(reinterpret_cast<const char *>(X) + __umul24(col, (uint32_t)ldx * (uint32_t)sizeof(T)),
+                                  k, xv[j]);
+                } else {
+                    load_x<T, KM>(reinterpret_cast<const char *>(X + (int64_t)col * ldx), k, xv[j]);
                 }
-#pragma unroll
-                for (int q = 0; q < KM; ++q) xv[j][q] = (v && (KM == 1 || q < k)) ? xr[q] : T(0);
             }
             if constexpr (KM == 1) {
                 if (prio) __builtin_amdgcn_s_setprio(0);
@@ -140,10 +184,18 @@ slab_block(const SlabGeom &g, int32_t block, int xcd, const int32_t *__restrict_
                 T prod[KM];
 #pragma unroll
                 for (int q = 0; q < KM; ++q) prod[q] = S::mul(aj, xv[j][q]);
-                if constexpr (SR == 0) segmented_scan<T, KM>(key, prod);
-                else segmented_scan_op<S, T, KM>(key, prod);
-                const uint32_t nxt = __shfl_down(key, 1);
-                const bool tail = key != 0xffffffffu && (lane == kWave - 1 || nxt != key);
+                bool tail;                                    // the last lane of each row
+                if constexpr (KM == 1) {
+                    if constexpr (SR == 0) segmented_scan<true>(key, 0, prod);
+                    else segmented_scan_op<true, S>(key, 0, prod);
+                    const uint32_t nxt = __shfl_down(key, 1);
+                    tail = key != 0xffffffffu && (lane == kWave - 1 || nxt != key);
+                } else {
+                    const uint64_t same = same_as_before(key);
+                    if constexpr (SR == 0) segmented_scan<false>(key, same, prod);
+                    else segmented_scan_op<false, S>(key, same, prod);
+                    tail = in_lanes(__builtin_amdgcn_ballot_w64(key != 0xffffffffu) & ~(same >> 1));
+                }
                 if (tail) {
 #pragma unroll
                     for (int q = 0; q < KM; ++q)
