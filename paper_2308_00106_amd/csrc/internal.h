@@ -155,12 +155,13 @@ struct PanelGeom {
     int32_t chunks, quota, cap;           // chunk b: the rows whose entries start in
                                           // [b quota, (b + 1) quota), at most cap entries
     int32_t split;                        // workgroups per panel in the first pass
+    int32_t cus;                          // workgroups of the second pass, at most
 };
 struct PanelLayout {
     int32_t *offt = nullptr;              // [chunks + 1][panels] run starts (last row: panel ends)
     int32_t *crow = nullptr;              // [chunks + 1] first row of each chunk
     uint16_t *c16 = nullptr;              // per entry, byte offset of its x in the panel
-    uint16_t *pos16 = nullptr;            // per entry, byte offset of its product's place in LDS
+    uint16_t *pos16 = nullptr;            // per entry, its product's place in LDS
     void *val = nullptr;
 };
 // false when the matrix cannot use the layout: too many panels, a row too

@@ -5,32 +5,37 @@
 // and is bound by the L2's request rate, about one request per entry: 48.7M
 // FP32 entries over 4M columns take 288 us, whatever the value type. Here no x
 // is gathered from memory at all. Columns are cut into panels whose x fills
-// 64 KiB of LDS, rows into chunks whose products fill 64 KiB of LDS:
+// 64 KiB of LDS, rows into chunks whose products fill 128 KiB of LDS:
 //
 //   1. k_panel_products: a workgroup copies one panel's x into LDS, streams a
 //      share of the panel's entries (value and a 16-bit offset of its x) and
 //      streams their products out, in the same order;
-//   2. k_panel_rows: a workgroup collects its chunk's products, one run of
-//      consecutive entries per panel, puts each at its row order's place in
-//      LDS (a 16-bit offset per entry) and sums the rows there.
+//   2. k_panel_rows: a workgroup per CU walks chunks: it collects a chunk's
+//      products, one run of consecutive entries per panel, puts each at its row
+//      order's place in LDS (a 16-bit index per entry) and sums the rows there.
 //
 // Both passes move whole cache lines only, 2 sizeof(T) + sizeof(V) + 4 bytes
-// per entry, and run at the rate of memory: the FP32 matrix above takes 91 us
-// (520 MB, 5.7 TB/s) and 88 us (325 MB, 3.7 TB/s), its BF16 form of 1.5M rows
-// 61 us where the slab kernel takes 106. FP64 entries move 28 bytes, 2M rows
-// of 10 take 68 + 43 us, about what the slab kernel's gathers take, so the
-// tuner times both. Two workgroups of 1024 threads fit a CU in both passes;
-// 128 KiB panels (one workgroup per CU) made the first pass 6% slower, chunks
-// of 32 and 16 KiB with as many workgroups the second 5-40% (shorter runs).
+// per entry, and run at the rate of memory: the FP32 matrix above takes 90 us
+// (520 MB, 5.7 TB/s) and 86 us (325 MB, 3.8 TB/s), its BF16 form of 1.5M rows
+// 30 + 32 us where the slab kernel takes 106. FP64 entries move 28 bytes, 2M
+// rows of 10 take 67 + 45 us, about what the slab kernel's gathers take, so the
+// tuner times both. In the first pass two workgroups of 1024 threads fit a CU;
+// 128 KiB panels (one per CU) made it 6% slower. In the second one workgroup per
+// CU with twice the chunk, so runs twice as long, and the next chunk's products
+// on their way while it sums takes 92 / 36 / 60 us (FP32 / BF16 / FP64, new
+// matrices in turn) where two with 64 KiB took 97 / 38 / 66; its products alone
+// take 64 and summing 20, which two workgroups half a chunk apart hid no better.
 // With several right-hand sides the products grow with k while a gather of k
 // values stays one request, so those stay with the slab kernel.
 //
 // Rows are summed in a fixed order (positions in groups, groups in row
 // order), so results are deterministic.
+
 #include "device_common.h"
 #include "internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mxe {
 
@@ -40,8 +45,8 @@ constexpr int kPanelBlock = 1024;
 constexpr int kPanelWaves = kPanelBlock / kWave;
 constexpr int kPanelMax = 1024;                    // panels per layout
 constexpr int kPanelBytes = 65536;                 // of x in LDS per workgroup
-constexpr int kChunkBytes = 65536;                 // of products in LDS per workgroup
-constexpr int kRowSlice = 2048;                    // row starts of a chunk kept in LDS
+constexpr int kChunkBytes = 131072;                // of products in LDS per workgroup
+constexpr int kRowSlice = 4096;                    // row starts of a chunk kept in LDS
 constexpr int kPanelMinRun = 8;                    // mean entries of a run, at least
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -105,12 +110,12 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_count(PanelGeom g, const 
     for (int p = threadIdx.x; p < g.panels; p += kPanelBlock) cnt[(int64_t)p * g.chunks + b] = (c[p] + 3) & ~3;
 }
 
-// LDS byte offset of position i of a chunk: a thread's positions lie a
-// workgroup's width apart
+// place in LDS of position i of a chunk: a thread's positions lie a workgroup's
+// width apart
 template <int EB>
 __device__ inline uint32_t place(uint32_t i) {
     constexpr uint32_t E = kChunkBytes / EB / kPanelBlock;
-    return ((i % E) * kPanelBlock + i / E) * EB;
+    return (i % E) * kPanelBlock + i / E;
 }
 
 // Pass 2 of the build: a workgroup orders its chunk's entries by panel in LDS
@@ -275,32 +280,39 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_products(
 // stay in flight across it (__syncthreads would wait for them).
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Second pass: one chunk per workgroup. G lanes share a run, each lane taking
-// four entries at a time; R runs of up to U groups of G fours are in flight
-// per lane. A chunk's place i lies at (i % E, i / E) of an E x 1024 array, so
+// Second pass: a workgroup per CU walks its chunks, the next chunk's products
+// on their way to registers while it sums the current one. G lanes share a run,
+// each lane taking four entries at a time; R runs of up to U groups of G fours
+// are in flight per lane, what lies past them is read when the chunk's turn
+// comes. A chunk's place i lies at (i % E, i / E) of an E x 1024 array, so
 // that thread t sums places [E t, E t + E) by row without bank conflicts (a
 // bit per place marks the row starts); a row's sum is then the last partial
 // sum of each group of E it spans. Summing with one to eight lanes per row
-// over its places instead took 100 us where this takes 88 (rows of 1 to 256
-// entries: the longest row of a wavefront held up the others).
+// over its places instead took 13% longer (rows of 1 to 256 entries: the longest
+// row of a wavefront held up the others).
 template <typename T, int SR, int G, int R, int U>
-__global__ __launch_bounds__(kPanelBlock, 8) void k_panel_rows(
+__global__ __launch_bounds__(kPanelBlock) void k_panel_rows(
     PanelGeom g, const int32_t *__restrict__ offt, const int32_t *__restrict__ crow,
     const int32_t *__restrict__ rp, const uint16_t *__restrict__ pos16, const T *__restrict__ prod,
     T *__restrict__ Y, int64_t ldy) {
     constexpr int E = kChunkBytes / (int)sizeof(T) / kPanelBlock;     // positions per thread
+    constexpr int RP = 3;                                             // row starts per thread held ahead
     __shared__ T sp[E * kPanelBlock];
     __shared__ int32_t rs[kRowSlice + 1];
     __shared__ uint32_t mask[E * kPanelBlock / 32 + 1];
-    using S = Semiring<SR, T>;
+    // FP32 products are summed in FP64: a row's terms stand in a line here, where
+    // the other products' lanes add them as a tree
+    using A = std::conditional_t<SR == 0, double, T>;
+    using Sum = Semiring<SR, A>;
     constexpr int NG = kPanelBlock / G;
     typedef T tv __attribute__((ext_vector_type(4)));
     typedef uint16_t pv __attribute__((ext_vector_type(4)));
     // neighbouring chunks share cache lines at the ends of their runs: each
-    // XCD takes a contiguous range of chunks
-    const int32_t per = (g.chunks + 7) / 8;
-    const int32_t b = (int32_t)(blockIdx.x % 8) * per + (int32_t)(blockIdx.x / 8);
-    if (b >= g.chunks) return;
+    // XCD takes a contiguous range of chunks, its workgroups side by side in it
+    const int32_t per = (g.chunks + 7) / 8, side = (int32_t)gridDim.x / 8;
+    const int32_t c0 = (int32_t)(blockIdx.x % 8) * per, c1 = min(c0 + per, g.chunks);
+    int32_t b = c0 + (int32_t)(blockIdx.x / 8);
+    if (b >= c1) return;
     // quads by 32-bit byte offsets from uniform bases (panel_geometry bounds them)
     auto prodv = [&](int32_t a) {
         return *reinterpret_cast<const tv *>(reinterpret_cast<const char *>(prod) + (uint32_t)a * (uint32_t)sizeof(tv));
@@ -310,80 +322,104 @@ __global__ __launch_bounds__(kPanelBlock, 8) void k_panel_rows(
     };
     auto put = [&](tv a, pv q) {
 #pragma unroll
-        for (int n = 0; n < 4; ++n) *reinterpret_cast<T *>(reinterpret_cast<char *>(sp) + q[n]) = a[n];
+        for (int n = 0; n < 4; ++n) sp[q[n]] = a[n];
     };
     const int t = threadIdx.x, lane = t % G;
-    const int32_t *o0 = offt + (int64_t)b * g.panels, *o1 = o0 + g.panels;
-    for (int p = t / G; p < g.panels; p += R * NG) {
-        int32_t a[R], n[R];
-        bool more = false;
+    int32_t a[R], n[R];                             // first quad and end of the chunk's runs t / G + r NG
+    int32_t a1[R], n1[R], r1 = 0, rows1 = 0;        // the same of the chunk after it
+    int32_t start[RP], r0 = 0, rows = 0, e0 = 0;
+    tv v[R][U];
+    pv w[R][U];
+    auto offsets = [&](int32_t c) {
+        const int32_t *o0 = offt + (int64_t)c * g.panels, *o1 = o0 + g.panels;
+        r1 = crow[c];
+        rows1 = crow[c + 1] - r1;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const bool in = p + r * NG < g.panels;
-            a[r] = in ? (o0[p + r * NG] >> 2) + lane : 0;
-            n[r] = in ? o1[p + r * NG] >> 2 : 0;
+            const int32_t p = min(t / G + r * NG, g.panels - 1);
+            a1[r] = (o0[p] >> 2) + lane;
+            n1[r] = t / G + r * NG < g.panels ? o1[p] >> 2 : 0;
         }
-        do {
-            tv v[R][U];
-            pv w[R][U];
+    };
+    auto fetch = [&]() {                            // the chunk whose offsets have come
+        r0 = r1;
+        rows = rows1;
+        e0 = rp[r0];
 #pragma unroll
-            for (int r = 0; r < R; ++r)
+        for (int k = 0; k < RP; ++k) start[k] = rp[r0 + min(t + k * kPanelBlock, rows)];
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (a[r] + u * G < n[r]) {
-                        v[r][u] = prodv(a[r] + u * G);
-                        w[r][u] = posv(a[r] + u * G);
-                    }
-            more = false;
+        for (int r = 0; r < R; ++r) {
+            a[r] = a1[r];
+            n[r] = n1[r];
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
+            for (int u = 0; u < U; ++u)
+                if (a[r] + u * G < n[r]) {
+                    v[r][u] = prodv(a[r] + u * G);
+                    w[r][u] = posv(a[r] + u * G);
+                }
+        }
+    };
+    offsets(b);
+    fetch();
+    for (;;) {
+        if (b + side < c1) offsets(b + side);
+        for (int i = t; i <= E * kPanelBlock / 32; i += kPanelBlock) mask[i] = 0;
+        lds_barrier();                              // the previous chunk's sums have been read as well
+        auto mark = [&](int i, int32_t s) {
+            if (i <= kRowSlice) rs[i] = s;
+            atomicOr(&mask[s >> 5], 1u << (s & 31));
+        };
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (a[r] + u * G < n[r]) put(v[r][u], w[r][u]);
-                a[r] += U * G;
-                more |= a[r] < n[r];
+        for (int k = 0; k < RP; ++k)
+            if (t + k * kPanelBlock <= rows) mark(t + k * kPanelBlock, start[k] - e0);
+        for (int i = t + RP * kPanelBlock; i <= rows; i += kPanelBlock) mark(i, rp[r0 + i] - e0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (a[r] + u * G < n[r]) put(v[r][u], w[r][u]);
+            for (int32_t q = a[r] + U * G; q < n[r]; q += G) put(prodv(q), posv(q));
+        }
+        for (int p = t / G + R * NG; p < g.panels; p += NG) {
+            const int32_t o = offt[(int64_t)b * g.panels + p] >> 2, e = offt[(int64_t)(b + 1) * g.panels + p] >> 2;
+            for (int32_t q = o + lane; q < e; q += G) put(prodv(q), posv(q));
+        }
+        const int32_t row0 = r0, nrow = rows, first = e0;
+        b += side;
+        if (b < c1) fetch();
+        lds_barrier();
+        // positions [E t, E t + E): running sums by row
+        {
+            const uint32_t m = mask[t * E >> 5] >> (t * E & 31);
+            A acc = sp[t];
+#pragma unroll
+            for (int j = 1; j < E; ++j) {
+                const A x = sp[j * kPanelBlock + t];
+                acc = (m >> j & 1) ? x : Sum::add(acc, x);
+                sp[j * kPanelBlock + t] = (T)acc;
             }
-        } while (more);
-    }
-    for (int i = t; i <= E * kPanelBlock / 32; i += kPanelBlock) mask[i] = 0;
-    const int32_t r0 = crow[b], rows = crow[b + 1] - r0, e0 = rp[r0];
-    lds_barrier();
-    for (int i = t; i <= rows; i += kPanelBlock) {
-        const int32_t s = rp[r0 + i] - e0;
-        if (i <= kRowSlice) rs[i] = s;
-        atomicOr(&mask[s >> 5], 1u << (s & 31));
-    }
-    lds_barrier();
-    // positions [E t, E t + E): running sums by row
-    {
-        const uint32_t m = mask[t * E >> 5] >> (t * E & 31);
-        T v[E];
-#pragma unroll
-        for (int j = 0; j < E; ++j) v[j] = sp[j * kPanelBlock + t];
-#pragma unroll
-        for (int j = 1; j < E; ++j) {
-            v[j] = (m >> j & 1) ? v[j] : S::add(v[j - 1], v[j]);
-            sp[j * kPanelBlock + t] = v[j];
         }
-    }
-    lds_barrier();
-    for (int32_t i = t; i < rows; i += kPanelBlock) {
-        const int32_t s = i < kRowSlice ? rs[i] : rp[r0 + i] - e0;
-        const int32_t last = (i < kRowSlice ? rs[i + 1] : rp[r0 + i + 1] - e0) - 1;
-        T acc = S::identity();
-        for (int32_t q = s / E; q <= last / E && s <= last; ++q) {
-            const int32_t j = min(last, q * E + E - 1) % E;
-            acc = S::add(acc, sp[j * kPanelBlock + q]);
+        lds_barrier();
+        for (int32_t i = t; i < nrow; i += kPanelBlock) {
+            const int32_t s = i < kRowSlice ? rs[i] : rp[row0 + i] - first;
+            const int32_t last = (i < kRowSlice ? rs[i + 1] : rp[row0 + i + 1] - first) - 1;
+            A acc = Sum::identity();
+            for (int32_t q = s / E; q <= last / E && s <= last; ++q) {
+                const int32_t j = min(last, q * E + E - 1) % E;
+                acc = Sum::add(acc, A(sp[j * kPanelBlock + q]));
+            }
+            __builtin_nontemporal_store((T)acc, &Y[(int64_t)(row0 + i) * ldy]);
         }
-        __builtin_nontemporal_store(acc, &Y[(int64_t)(r0 + i) * ldy]);
+        if (b >= c1) break;
     }
 }
 
 template <typename T, int SR, int G, int R, int U>
 void rows_launch(const PanelGeom &g, const PanelLayout &l, const int32_t *rp, const void *prod, void *Y,
                  int64_t ldy, hipStream_t s) {
-    hipLaunchKernelGGL((k_panel_rows<T, SR, G, R, U>), dim3((g.chunks + 7) / 8 * 8), dim3(kPanelBlock), 0, s, g,
-                       l.offt, l.crow, rp, l.pos16, (const T *)prod, (T *)Y, ldy);
+    const int32_t per = (g.chunks + 7) / 8, side = std::max(1, std::min(per, g.cus / 8));
+    hipLaunchKernelGGL((k_panel_rows<T, SR, G, R, U>), dim3(8 * side), dim3(kPanelBlock), 0, s, g, l.offt, l.crow,
+                       rp, l.pos16, (const T *)prod, (T *)Y, ldy);
 }
 
 template <typename V, typename T, int SR>
@@ -391,8 +427,8 @@ hipError_t panel_launch(const PanelGeom &g, const PanelLayout &l, const int32_t 
                         int64_t ldx, void *Y, int64_t ldy, void *prod, hipStream_t s) {
     hipLaunchKernelGGL((k_panel_products<V, T, SR>), dim3(g.panels * g.split), dim3(kPanelBlock), 0, s,
                        g, l.offt, l.c16, (const V *)l.val, (const T *)X, ldx, (T *)prod);
-    if constexpr (sizeof(T) == 8) rows_launch<T, SR, 8, 1, 2>(g, l, rp, prod, Y, ldy, s);
-    else rows_launch<T, SR, 8, 2, 3>(g, l, rp, prod, Y, ldy, s);
+    if constexpr (sizeof(T) == 8) rows_launch<T, SR, 8, 2, 3>(g, l, rp, prod, Y, ldy, s);
+    else rows_launch<T, SR, 8, 2, 5>(g, l, rp, prod, Y, ldy, s);
     return hipGetLastError();
 }
 
@@ -419,13 +455,13 @@ bool panel_geometry(int32_t nrows, int32_t ncols, int64_t nnz, int32_t max_row, 
     const int64_t panels = cdiv(ncols, int64_t(1) << wbits);
     const int32_t cap = kChunkBytes / eb - 1;       // one place is left for the padding entries
     if (panels > kPanelMax || max_row > cap / 2) return false;
-    const int64_t slots = 2 * (int64_t)cu_count;    // workgroups resident at once, in both passes
+    const int64_t slots = 2 * (int64_t)cu_count;    // workgroups resident at once in the first pass
     // a chunk starts its rows within `quota` entries and ends its last one at
     // most max_row later; as many chunks as fill whole waves of workgroups,
     // with at least an entry per thread
     const int64_t most = cap - max_row;
-    const int64_t waves = cdiv(nnz, most * slots);
-    const int64_t quota = std::min<int64_t>(most, std::max<int64_t>(kPanelBlock, cdiv(nnz, waves * slots)));
+    const int64_t waves = cdiv(nnz, most * cu_count);
+    const int64_t quota = std::min<int64_t>(most, std::max<int64_t>(kPanelBlock, cdiv(nnz, waves * cu_count)));
     // runs of a few entries would be mostly padding
     if (quota < kPanelMinRun * panels) return false;
     g->nrows = nrows;
@@ -434,6 +470,7 @@ bool panel_geometry(int32_t nrows, int32_t ncols, int64_t nnz, int32_t max_row, 
     g->wbits = wbits;
     g->panels = (int32_t)panels;
     g->cap = cap;
+    g->cus = cu_count;
     g->quota = (int32_t)quota;
     g->chunks = (int32_t)cdiv(nnz, quota);
     // workgroups per panel: fill the chip, with at least 4096 entries each

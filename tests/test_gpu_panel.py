@@ -1,8 +1,8 @@
 """GPU: the column-panel product (MXE_VAR_PANEL, one right-hand side) against
 the CPU oracle at the edges of its layout: matrices one column short of and
 past a whole panel, one panel and many, rectangular ones, chunks whose rows are
-nearly all empty or that hold more rows than the row starts kept in LDS, the
-longest row a chunk takes, strided X and Y. Products stay within the normalized
+nearly all empty or that hold more rows than the row starts kept in LDS, long
+rows, strided X and Y. Products stay within the normalized
 errors of the other variants (1e-13 FP64, 1e-5 FP32, 1e-2 BF16 against the FP64
 oracle); (min, +) and (or, and) match bit for bit in FP64."""
 import numpy as np
@@ -56,9 +56,11 @@ CASES = {
     "skewed": lambda: synth.skewed_clustered(40_000, 2.0, 1.0, 256, 2000.0, 5),
     "mostly_empty": lambda: _mostly_empty(30_000, 3000, 6),
     "all_but_one_empty": lambda: _rows(4000, 5000, [3000] + [0] * 3999, 7),
-    # half a chunk: 8191 places in FP64, 16383 in FP32
-    "longest_row": lambda: _rows(700, 20_000, [4095] + [60] * 698 + [4095], 8),
-    "several_waves": lambda: _rows(480_000, 300_000, np.full(480_000, 11), 9),
+    "long_rows": lambda: _rows(700, 20_000, [4095] + [60] * 698 + [4095], 8),
+    # more chunks than CUs, in FP32 too
+    "several_waves": lambda: _rows(800_000, 300_000, np.full(800_000, 11), 9),
+    # 318 panels in FP64, 159 in FP32
+    "wide": lambda: _rows(60_000, 2_600_000, np.full(60_000, 12), 10),
 }
 
 
