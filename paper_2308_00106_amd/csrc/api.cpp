@@ -753,8 +753,11 @@ mxe_status mxe_create(int32_t device, uint64_t hbm_budget_bytes, mxe_ctx **out) 
     MXE_HIP(hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr));
     mxe_status st = noalloc_init(device);
     if (st) return st;
+    double *results = nullptr;
+    MXE_HIP(hipHostMalloc((void **)&results, sizeof(double) * kResultDoubles, hipHostMallocDefault));
     auto *ctx = new mxe_ctx();
     ctx->device = device;
+    ctx->results = results;
     ctx->budget = hbm_budget_bytes;
     ctx->cu_count = prop.multiProcessorCount;
     ctx->lds_per_cu = prop.maxSharedMemoryPerMultiProcessor;
@@ -774,6 +777,7 @@ mxe_status mxe_destroy(mxe_ctx *ctx) {
         ctx->mats.clear();
     }
     DeviceGuard g(ctx->device);
+    (void)hipHostFree(ctx->results);
     delete ctx;
     return MXE_OK;
 }
@@ -1021,22 +1025,20 @@ mxe_status mxe_entropy(mxe_ctx *ctx, mxe_mat m, int32_t grid_rows, int32_t grid_
         if (hist) std::fill(hist, hist + bins, (int64_t)0);
         return MXE_OK;
     }
-    Scratch hdev, ws, res;
+    Scratch hdev, ws;
     mxe_status st;
     if ((st = hdev.alloc(ctx->pool, 4 * (size_t)bins, s))) return st;
     if ((st = ws.alloc(ctx->pool, entropy_ws_bytes(bins), s))) return st;
-    if ((st = res.alloc(ctx->pool, 4 * sizeof(double), s))) return st;
     MXE_HIP(launch_block_hist(A->nrows, A->ncols, A->nnz, A->rp, A->col, grid_rows, grid_cols,
-                              (uint32_t *)hdev.p, s));
-    MXE_HIP(launch_entropy((const uint32_t *)hdev.p, bins, (double *)res.p, ws.p, s));
-    double r[4];
-    MXE_HIP(hipMemcpyAsync(r, res.p, sizeof r, hipMemcpyDeviceToHost, s));
+                              (uint32_t *)hdev.p, ws.p, s));
+    MXE_HIP(launch_entropy((const uint32_t *)hdev.p, bins, ctx->results, ws.p, s));
     std::vector<uint32_t> h32;
     if (hist) {
         h32.resize((size_t)bins);
         MXE_HIP(hipMemcpyAsync(h32.data(), hdev.p, 4 * (size_t)bins, hipMemcpyDeviceToHost, s));
     }
     MXE_HIP(hipStreamSynchronize(s));
+    const double *r = ctx->results;
     *h_bits = r[0];
     if (h_nats) *h_nats = r[1];
     if (hist) for (int64_t i = 0; i < bins; ++i) hist[i] = h32[(size_t)i];
@@ -1070,14 +1072,17 @@ mxe_status mxe_entropy_levels(mxe_ctx *ctx, mxe_mat m, int32_t grid_rows, int32_
     mxe_status st;
     if ((st = hdev.alloc(ctx->pool, 4 * (size_t)bins, s))) return st;
     if ((st = ws.alloc(ctx->pool, entropy_regions_ws_bytes(grid_rows, grid_cols, levels, nlevels), s))) return st;
-    if ((st = res.alloc(ctx->pool, 4 * sizeof(double) * (size_t)nreg, s))) return st;
+    const bool direct = 4 * (size_t)nreg <= kResultDoubles;
+    if (!direct && (st = res.alloc(ctx->pool, 4 * sizeof(double) * (size_t)nreg, s))) return st;
     MXE_HIP(launch_block_hist(A->nrows, A->ncols, A->nnz, A->rp, A->col, grid_rows, grid_cols,
-                              (uint32_t *)hdev.p, s));
+                              (uint32_t *)hdev.p, nullptr, s));
     MXE_HIP(launch_entropy_regions((const uint32_t *)hdev.p, grid_rows, grid_cols, levels, nlevels,
-                                   (double *)res.p, ws.p, s));
-    std::vector<double> r(4 * (size_t)nreg);
-    MXE_HIP(hipMemcpyAsync(r.data(), res.p, sizeof(double) * r.size(), hipMemcpyDeviceToHost, s));
+                                   direct ? ctx->results : (double *)res.p, ws.p, s));
+    std::vector<double> copy(direct ? 0 : 4 * (size_t)nreg);
+    if (!direct)
+        MXE_HIP(hipMemcpyAsync(copy.data(), res.p, sizeof(double) * copy.size(), hipMemcpyDeviceToHost, s));
     MXE_HIP(hipStreamSynchronize(s));
+    const double *r = direct ? ctx->results : copy.data();
     bool ok = true;
     for (int32_t i = 0; i < nreg; ++i) {
         h_bits[i] = r[4 * (size_t)i];

@@ -103,32 +103,64 @@ __device__ inline dd dd_div(dd a, dd b) {
 }
 #pragma clang fp contract(on)
 
+// ln 2 as the nearest double-double (the nearest double, then the nearest
+// double to the rest).
+__device__ constexpr dd kLn2 = {0x1.62e42fefa39efp-1, 0x1.abc9e3b39803fp-56};
+
 // ln(m) for m in [sqrt(1/2), sqrt(2)]: 2 atanh(u), u = (m - 1) / (m + 1),
 // |u| <= 0.1716, summed as u * sum_k u^(2k) / (2k + 1) for k < 24; u^2 < 2^-5.08,
-// so the truncated tail is below 2^-120 of the sum. coef[k] = 1 / (2k + 1) in double-double.
-constexpr int kLnTerms = 24;
-
-__device__ inline dd dd_ln_reduced(dd m, const dd *coef) {
+// so the truncated tail is below 2^-120 of the sum. The coefficients, also
+// nearest double-doubles, stand in the unrolled code: a chain of 23 steps that
+// reads each from memory takes twice as long.
+__device__ inline dd dd_ln_reduced(dd m) {
+    constexpr int kTerms = 24;
+    constexpr dd coef[kTerms] = {
+        {0x1.0000000000000p+0, 0x0.0p+0},
+        {0x1.5555555555555p-2, 0x1.5555555555555p-56},
+        {0x1.999999999999ap-3, -0x1.999999999999ap-57},
+        {0x1.2492492492492p-3, 0x1.2492492492492p-57},
+        {0x1.c71c71c71c71cp-4, 0x1.c71c71c71c71cp-58},
+        {0x1.745d1745d1746p-4, -0x1.745d1745d1746p-59},
+        {0x1.3b13b13b13b14p-4, -0x1.3b13b13b13b14p-58},
+        {0x1.1111111111111p-4, 0x1.1111111111111p-60},
+        {0x1.e1e1e1e1e1e1ep-5, 0x1.e1e1e1e1e1e1ep-61},
+        {0x1.af286bca1af28p-5, 0x1.af286bca1af28p-59},
+        {0x1.8618618618618p-5, 0x1.8618618618618p-59},
+        {0x1.642c8590b2164p-5, 0x1.642c8590b2164p-60},
+        {0x1.47ae147ae147bp-5, -0x1.eb851eb851eb8p-61},
+        {0x1.2f684bda12f68p-5, 0x1.2f684bda12f68p-59},
+        {0x1.1a7b9611a7b96p-5, 0x1.1a7b9611a7b96p-61},
+        {0x1.0842108421084p-5, 0x1.0842108421084p-60},
+        {0x1.f07c1f07c1f08p-6, -0x1.f07c1f07c1f08p-61},
+        {0x1.d41d41d41d41dp-6, 0x1.0750750750750p-60},
+        {0x1.bacf914c1bad0p-6, -0x1.bacf914c1bad0p-60},
+        {0x1.a41a41a41a41ap-6, 0x1.0690690690690p-60},
+        {0x1.8f9c18f9c18fap-6, -0x1.f3831f3831f38p-61},
+        {0x1.7d05f417d05f4p-6, 0x1.7d05f417d05f4p-62},
+        {0x1.6c16c16c16c17p-6, -0x1.f49f49f49f49fp-61},
+        {0x1.5c9882b931057p-6, 0x1.310572620ae4cp-61},
+    };
     dd num = dd_sub(m, dd{1.0, 0.0});
     dd den = dd_add(m, dd{1.0, 0.0});
     dd u = dd_div(num, den);
     dd w = dd_mul(u, u);
-    dd acc = coef[kLnTerms - 1];
-    for (int k = kLnTerms - 2; k >= 0; --k) acc = dd_add(dd_mul(acc, w), coef[k]);
+    dd acc = coef[kTerms - 1];
+#pragma unroll
+    for (int k = kTerms - 2; k >= 0; --k) acc = dd_add(dd_mul(acc, w), coef[k]);
     dd r = dd_mul(u, acc);
     return dd{2.0 * r.hi, 2.0 * r.lo};
 }
 
 // ln(x) for an integer-valued double 1 <= x < 2^53: x = m 2^e with m in
-// [sqrt(1/2), sqrt(2)), then ln x = e ln2 + ln m (ln2 passed in).
-__device__ inline dd dd_ln_int(double x, dd ln2, const dd *coef) {
+// [sqrt(1/2), sqrt(2)), then ln x = e ln2 + ln m.
+__device__ inline dd dd_ln_int(double x) {
     int e;
     double m = __builtin_frexp(x, &e);        // x = m 2^e, m in [0.5, 1)
     m *= 2.0;
     e -= 1;                                   // m in [1, 2)
     if (m > 1.4142135623730951) { m *= 0.5; e += 1; }
-    dd lm = dd_ln_reduced(dd{m, 0.0}, coef);
-    return dd_add(dd_mul_d(ln2, (double)e), lm);
+    dd lm = dd_ln_reduced(dd{m, 0.0});
+    return dd_add(dd_mul_d(kLn2, (double)e), lm);
 }
 
 // ---------------------------------------------------------------------------

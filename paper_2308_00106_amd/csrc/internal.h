@@ -82,17 +82,19 @@ __host__ __device__ inline int bin_of_length(int32_t len) {
 }
 
 // ---- histogram and entropy -------------------------------------------------
-// hist: grid_r * grid_c uint32 (device). Workspace: block_hist_ws_bytes().
+// hist: grid_r * grid_c uint32 (device). entropy_ws (or null): launch_entropy's
+// workspace, cleared for it on the way.
 hipError_t launch_block_hist(int32_t nrows, int32_t ncols, int64_t nnz, const int32_t *rp,
                              const int32_t *col, int32_t grid_r, int32_t grid_c, uint32_t *hist,
-                             hipStream_t s);
-// result (device, 4 doubles): h_bits, h_nats, certified (1.0 / 0.0), S.
+                             void *entropy_ws, hipStream_t s);
+// result (4 doubles the device can write): h_bits, h_nats, certified (1.0 /
+// 0.0), S. ws: entropy_ws_bytes, cleared by launch_block_hist.
 size_t entropy_ws_bytes(int64_t bins);
 hipError_t launch_entropy(const uint32_t *hist, int64_t bins, double *result, void *ws,
                           hipStream_t s);
 // Hierarchical entropy: for each level L, min(L, G_r) x min(L, G_c) regions;
 // result holds 4 doubles per region (as launch_entropy), levels in order,
-// regions row-major. Synchronizes s (the region table is staged from the host).
+// regions row-major. At most 16 levels.
 int32_t entropy_regions_count(int32_t grid_r, int32_t grid_c, const int32_t *levels,
                               int32_t nlevels);
 size_t entropy_regions_ws_bytes(int32_t grid_r, int32_t grid_c, const int32_t *levels,

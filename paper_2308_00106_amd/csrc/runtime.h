@@ -165,6 +165,8 @@ struct Server;
 
 }  // namespace mxe
 
+constexpr size_t kResultDoubles = 8192;
+
 struct mxe_ctx {
     int device = 0;
     mxe::DevicePool pool;               // outlives the matrices below
@@ -176,6 +178,9 @@ struct mxe_ctx {
     std::map<int64_t, std::unique_ptr<mxe::Plan>> plans;
     int64_t next_id = 1;
     int cu_count = 256;
+    // pinned memory that kernels write small results to, read after the stream's
+    // synchronization under mu: no copy kernel, no staging
+    double *results = nullptr;
     size_t lds_per_cu = 0, lds_per_block = 0;   // bytes of LDS per CU / per workgroup
     mxe::Server *server = nullptr;      // owned; created and deleted by the serving loop
 };
