@@ -887,38 +887,43 @@ mxe_status mxe_permute(mxe_ctx *ctx, mxe_mat a, uint64_t seed, uint32_t mode, vo
     B->cinv = (int32_t *)p;
     // stream seeds: first and second SplitMix64 outputs started at `seed`
     const uint64_t s_row = sm64_key(seed, 0), s_col = sm64_key(seed, 1);
-    Scratch ws;
+    // the dimensions to shuffle, together; the others stay as they are
     const bool grad = mode & MXE_GRADIENT;
-    size_t ws_bytes = std::max({random_perm_ws_bytes(M), random_perm_ws_bytes(N),
-                                permuted_row_ptr_ws_bytes(M)});
-    if (grad)
-        ws_bytes = std::max({ws_bytes, gradient_perm_ws_bytes(M) + counts_bytes(M),
-                             counts_bytes(N) + std::max(gradient_perm_ws_bytes(N), line_counts_ws_bytes(A->nnz, N))});
-    if ((st = ws.alloc(ctx->pool, ws_bytes, s))) return st;
-    // gradient formats (Section 8, G-R and G-C): per-line counts go first in
-    // the workspace, the shuffle's own workspace after them
-    auto gradient = [&](bool rows, int32_t n, uint64_t seed_n, int32_t *perm, int32_t *inv) {
-        int32_t *counts = (int32_t *)ws.p;
-        void *gws = (char *)ws.p + counts_bytes(n);
-        hipError_t e = launch_line_counts(rows, M, A->nnz, A->rp, A->col, n, counts, gws, s);
-        if (e == hipSuccess) e = launch_gradient_perm(n, counts, seed_n, perm, inv, gws, s);
-        return e;
-    };
-    if ((mode & MXE_ROWS) && grad) {
-        MXE_HIP(gradient(true, M, s_row, B->rperm, B->rinv));
-    } else if (mode & MXE_ROWS) {
-        MXE_HIP(launch_random_perm(M, s_row, B->rperm, B->rinv, ws.p, s));
-    } else {
-        MXE_HIP(launch_iota_i32(B->rperm, M, s));
-        MXE_HIP(launch_iota_i32(B->rinv, M, s));
+    PermRequest perms[2];
+    GradRequest grads[2];
+    int np = 0;
+    for (int rows = 1; rows >= 0; --rows) {
+        int32_t *perm = rows ? B->rperm : B->cperm, *inv = rows ? B->rinv : B->cinv;
+        const int32_t n = rows ? M : N;
+        if (!(mode & (rows ? MXE_ROWS : MXE_COLS))) {
+            MXE_HIP(launch_iota_i32(perm, n, s));
+            MXE_HIP(launch_iota_i32(inv, n, s));
+            continue;
+        }
+        perms[np] = PermRequest{n, rows ? s_row : s_col, perm, inv};
+        grads[np++] = GradRequest{n, nullptr, rows ? s_row : s_col, perm, inv};
     }
-    if ((mode & MXE_COLS) && grad) {
-        MXE_HIP(gradient(false, N, s_col, B->cperm, B->cinv));
-    } else if (mode & MXE_COLS) {
-        MXE_HIP(launch_random_perm(N, s_col, B->cperm, B->cinv, ws.p, s));
+    // gradient formats (Section 8, G-R and G-C): per-line counts go first in
+    // the workspace, then what the column counts and after them the shuffles take
+    Scratch ws;
+    size_t counts = 0;
+    for (int i = 0; i < np && grad; ++i) counts += counts_bytes(grads[i].n);
+    size_t ws_bytes = std::max(random_perms_ws_bytes(perms, np), permuted_row_ptr_ws_bytes(M));
+    if (grad)
+        ws_bytes = std::max(ws_bytes, counts + std::max(gradient_perms_ws_bytes(grads, np),
+                                                        line_counts_ws_bytes(A->nnz, N)));
+    if ((st = ws.alloc(ctx->pool, ws_bytes, s))) return st;
+    if (grad) {
+        char *at = (char *)ws.p, *rest = at + counts;
+        for (int i = 0; i < np; ++i) {
+            const bool rows = grads[i].perm == B->rperm;
+            grads[i].counts = (const int32_t *)at;
+            MXE_HIP(launch_line_counts(rows, M, A->nnz, A->rp, A->col, (int32_t)grads[i].n, (int32_t *)at, rest, s));
+            at += counts_bytes(grads[i].n);
+        }
+        MXE_HIP(launch_gradient_perms(grads, np, (int32_t *)ctx->results, rest, s));
     } else {
-        MXE_HIP(launch_iota_i32(B->cperm, N, s));
-        MXE_HIP(launch_iota_i32(B->cinv, N, s));
+        MXE_HIP(launch_random_perms(perms, np, ws.p, s));
     }
     MXE_HIP(launch_permuted_row_ptr(M, A->rp, B->rperm, B->rp, ws.p, s));
     MXE_HIP(launch_gather_relabel_sort(M, N, A->rp, A->col, A->val, vb, B->rinv,

@@ -19,10 +19,15 @@ hipError_t launch_exclusive_scan(const int32_t *in, int32_t *out, int64_t n, voi
                                  hipStream_t s);
 
 // ---- random permutation (keys + LDS radix / bucket sort) --------------------
-// perm: new-to-old, inv: old-to-new. Workspace: random_perm_ws_bytes(n).
-size_t random_perm_ws_bytes(int64_t n);
-hipError_t launch_random_perm(int64_t n, uint64_t stream_seed, int32_t *perm, int32_t *inv,
-                              void *ws, hipStream_t s);
+// perm: new-to-old, inv (or null): old-to-new, of n indices in the order of
+// the stream's keys. Up to four at once.
+struct PermRequest {
+    int64_t n;
+    uint64_t seed;
+    int32_t *perm, *inv;
+};
+size_t random_perms_ws_bytes(const PermRequest *req, int count);
+hipError_t launch_random_perms(const PermRequest *req, int count, void *ws, hipStream_t s);
 
 // ---- gradient-based shuffle --------------------------------------------------
 // counts[i] = nonzeros of row i (rows) or of column i (!rows, n = ncols; ws:
@@ -32,11 +37,18 @@ hipError_t launch_line_counts(bool rows, int32_t nrows, int64_t nnz, const int32
                               const int32_t *col, int32_t n, int32_t *counts, void *ws,
                               hipStream_t s);
 // Pivot at the first maximum of counts[i+1] - counts[i], random permutation
-// of each part, riffle. Synchronizes s once (the pivot sizes the parts).
-// Workspace: gradient_perm_ws_bytes(n).
-size_t gradient_perm_ws_bytes(int64_t n);
-hipError_t launch_gradient_perm(int64_t n, const int32_t *counts, uint64_t stream_seed,
-                                int32_t *perm, int32_t *inv, void *ws, hipStream_t s);
+// of each part, riffle; rows and columns at once. Synchronizes s once (the
+// pivots size the parts); pivots: count ints that the device writes and the
+// host reads (pinned).
+struct GradRequest {
+    int64_t n;
+    const int32_t *counts;
+    uint64_t seed;
+    int32_t *perm, *inv;
+};
+size_t gradient_perms_ws_bytes(const GradRequest *req, int count);
+hipError_t launch_gradient_perms(const GradRequest *req, int count, int32_t *pivots, void *ws,
+                                 hipStream_t s);
 
 // ---- permuted CSR --------------------------------------------------------
 // rp_b[i'] = exclusive prefix of A's row lengths taken in rperm order.

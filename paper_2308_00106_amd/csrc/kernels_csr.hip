@@ -164,16 +164,38 @@ __global__ __launch_bounds__(kBlock) void k_bucket_scatter(int64_t n, uint64_t s
 // `bits` bits with per-workgroup LDS histograms (no device-wide atomics), then
 // one workgroup per bucket splits it by the next kSubBits bits in LDS and
 // ranks every item by (key, index) inside its sub-bucket, a handful of items.
-constexpr int kPermItems = 8192;                         // indices per bucketing workgroup
+// A range of up to kPermSmall indices is one workgroup's, split by 10 bits.
+// A launch takes several permutations at once (blockIdx.y, or blockIdx.x for the
+// small ones): a matrix's rows and columns, the parts of its gradient shuffles.
 constexpr int kPermMaxBits = 12;                         // at most 4096 buckets
 constexpr int kPermMeanBucket = 2048;
 constexpr int kBucketCap = 4096;                         // items a workgroup sorts in LDS
 constexpr int kSubBits = 8;                              // sub-buckets = kBlock
 constexpr int64_t kLdsPermMax = (int64_t)kPermMeanBucket << kPermMaxBits;
+// up to this many indices, buckets of 256 and 1024 indices to a bucketing
+// workgroup, beyond it 2048 and 8192: with the latter 100K indices would keep
+// 64 workgroups busy, 1.5M the count tables of the former
+constexpr int64_t kPermFew = 128 * 1024;
+constexpr int kPermSmall = 8192;
+constexpr int kSmallBlock = 1024;
+constexpr int kPermJobs = 4;
 
-inline int radix_bits(int64_t n) {                       // mean bucket <= kPermMeanBucket
+struct PermJob {
+    int64_t n;
+    uint64_t seed;
+    int32_t *perm, *inv;                                 // inv may be null
+    int32_t bits, nwg, chunk;                            // buckets' bits, workgroups and indices of each
+    int32_t base;                                        // indices of the jobs before (the scan's start)
+    int32_t *counts, *items;
+};
+struct PermJobs {
+    PermJob j[kPermJobs];
+};
+
+inline int radix_bits(int64_t n) {
+    const int64_t mean = n <= kPermFew ? 256 : kPermMeanBucket;
     int b = 0;
-    while (b < kPermMaxBits && (n >> b) > kPermMeanBucket) ++b;
+    while (b < kPermMaxBits && (n >> b) > mean) ++b;
     return b;
 }
 
@@ -185,34 +207,36 @@ __device__ inline uint32_t sub_digit(uint64_t key, int bits) {
 }
 
 // counts[d * nwg + w] = items of workgroup w's index range in bucket d
-__global__ __launch_bounds__(kBlock) void k_perm_count(int64_t n, uint64_t seed, int bits,
-                                                       int32_t nwg, int32_t *counts) {
+__global__ __launch_bounds__(kBlock) void k_perm_count(PermJobs jobs) {
     extern __shared__ int32_t hist[];
-    const int nd = 1 << bits;
+    const PermJob &J = jobs.j[blockIdx.y];
+    if ((int)blockIdx.x >= J.nwg) return;
+    const int nd = 1 << J.bits;
     for (int d = threadIdx.x; d < nd; d += kBlock) hist[d] = 0;
     __syncthreads();
-    const int64_t i0 = (int64_t)blockIdx.x * kPermItems;
-    const int64_t i1 = i0 + kPermItems < n ? i0 + kPermItems : n;
+    const int64_t i0 = (int64_t)blockIdx.x * J.chunk;
+    const int64_t i1 = std::min<int64_t>(i0 + J.chunk, J.n);
     for (int64_t i = i0 + threadIdx.x; i < i1; i += kBlock)
-        atomicAdd(&hist[top_digit(sm64_key(seed, (uint64_t)i), bits)], 1);
+        atomicAdd(&hist[top_digit(sm64_key(J.seed, (uint64_t)i), J.bits)], 1);
     __syncthreads();
-    for (int d = threadIdx.x; d < nd; d += kBlock) counts[(int64_t)d * nwg + blockIdx.x] = hist[d];
+    for (int d = threadIdx.x; d < nd; d += kBlock) J.counts[(int64_t)d * J.nwg + blockIdx.x] = hist[d];
 }
 
-// offsets: the exclusive scan of counts; items[pos] = index, in any order
-// inside a bucket (the bucket sort fixes the order)
-__global__ __launch_bounds__(kBlock) void k_perm_scatter(int64_t n, uint64_t seed, int bits,
-                                                         int32_t nwg, const int32_t *offsets,
-                                                         int32_t *items) {
+// counts now hold their exclusive scan over all jobs; items[pos] = index, in
+// any order inside a bucket (the bucket sort fixes the order)
+__global__ __launch_bounds__(kBlock) void k_perm_scatter(PermJobs jobs) {
     extern __shared__ int32_t cursor[];
-    const int nd = 1 << bits;
-    for (int d = threadIdx.x; d < nd; d += kBlock) cursor[d] = offsets[(int64_t)d * nwg + blockIdx.x];
+    const PermJob &J = jobs.j[blockIdx.y];
+    if ((int)blockIdx.x >= J.nwg) return;
+    const int nd = 1 << J.bits;
+    for (int d = threadIdx.x; d < nd; d += kBlock)
+        cursor[d] = J.counts[(int64_t)d * J.nwg + blockIdx.x] - J.base;
     __syncthreads();
-    const int64_t i0 = (int64_t)blockIdx.x * kPermItems;
-    const int64_t i1 = i0 + kPermItems < n ? i0 + kPermItems : n;
+    const int64_t i0 = (int64_t)blockIdx.x * J.chunk;
+    const int64_t i1 = std::min<int64_t>(i0 + J.chunk, J.n);
     for (int64_t i = i0 + threadIdx.x; i < i1; i += kBlock) {
-        const int32_t pos = atomicAdd(&cursor[top_digit(sm64_key(seed, (uint64_t)i), bits)], 1);
-        items[pos] = (int32_t)i;
+        const int32_t pos = atomicAdd(&cursor[top_digit(sm64_key(J.seed, (uint64_t)i), J.bits)], 1);
+        J.items[pos] = (int32_t)i;
     }
 }
 
@@ -224,19 +248,21 @@ __device__ inline bool key_less(uint64_t ka, int32_t ia, uint64_t kb, int32_t ib
 // start of its sub-bucket + its rank by (key, index) inside the sub-bucket.
 // A bucket above kBucketCap (not expected from uniform keys) is ranked
 // against the whole bucket in memory instead.
-// Bucket d spans items [offsets[d * stride], offsets[(d + 1) * stride]).
-__global__ __launch_bounds__(kBlock) void k_perm_bucket_sort(int32_t nd, int32_t stride, uint64_t seed,
-                                                             int bits, const int32_t *offsets,
-                                                             const int32_t *items, int32_t *perm,
-                                                             int32_t *inv) {
+// Bucket d starts at counts[d * nwg] - base and ends where the next one starts.
+__global__ __launch_bounds__(kBlock) void k_perm_bucket_sort(PermJobs jobs) {
     __shared__ uint64_t skey[kBucketCap];
     __shared__ int32_t sidx[kBucketCap];
     __shared__ int32_t sub[kBlock + 1];
     __shared__ int32_t cursor[kBlock];
     __shared__ int32_t wsum[kBlock / kWave];
-    const int32_t d = blockIdx.x;
-    const int32_t o = offsets[(int64_t)d * stride];
-    const int32_t m = offsets[(int64_t)(d + 1) * stride] - o;   // the scan's last entry is n
+    const PermJob &J = jobs.j[blockIdx.y];
+    const int32_t d = blockIdx.x, bits = J.bits;
+    if (d >= 1 << bits) return;
+    const uint64_t seed = J.seed;
+    const int32_t *items = J.items;
+    int32_t *perm = J.perm, *inv = J.inv;
+    const int32_t o = J.counts[(int64_t)d * J.nwg] - J.base;
+    const int32_t m = (d + 1 < 1 << bits ? J.counts[(int64_t)(d + 1) * J.nwg] - J.base : (int32_t)J.n) - o;
     if (m > kBucketCap) {
         for (int32_t t = threadIdx.x; t < m; t += kBlock) {
             const int32_t idx = items[o + t];
@@ -282,6 +308,64 @@ __global__ __launch_bounds__(kBlock) void k_perm_bucket_sort(int32_t nd, int32_t
     }
 }
 
+// exclusive scan of one int per thread of kSmallBlock threads
+__device__ inline int32_t small_exclusive_scan(int32_t v, int32_t *wsum) {
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    int32_t inc = v;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int32_t t = __shfl_up(inc, off);
+        if (lane >= off) inc += t;
+    }
+    if (lane == kWave - 1) wsum[wave] = inc;
+    __syncthreads();
+    int32_t woff = 0;
+    for (int w = 0; w < wave; ++w) woff += wsum[w];
+    return inc - v + woff;
+}
+
+// Up to kPermSmall indices by one workgroup: 4096 indices, rows and columns at
+// once, take one launch where the passes above took twelve.
+__global__ __launch_bounds__(kSmallBlock) void k_perm_small(PermJobs jobs) {
+    __shared__ uint64_t skey[kPermSmall];
+    __shared__ uint16_t sidx[kPermSmall];
+    __shared__ int32_t sub[kSmallBlock + 1], cursor[kSmallBlock];
+    __shared__ int32_t wsum[kSmallBlock / kWave];
+    constexpr int kPer = kPermSmall / kSmallBlock, kShift = 64 - 10;
+    const PermJob &J = jobs.j[blockIdx.x];
+    const int t = threadIdx.x, n = (int)J.n;
+    sub[t] = 0;
+    __syncthreads();
+    uint64_t key[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        key[k] = sm64_key(J.seed, (uint64_t)(t + k * kSmallBlock));
+        if (t + k * kSmallBlock < n) atomicAdd(&sub[key[k] >> kShift], 1);
+    }
+    __syncthreads();
+    const int32_t ex = small_exclusive_scan(sub[t], wsum);
+    sub[t] = ex;                                          // each thread's own counter
+    cursor[t] = ex;
+    if (t == 0) sub[kSmallBlock] = n;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+        if (t + k * kSmallBlock < n) {
+            const int32_t p = atomicAdd(&cursor[key[k] >> kShift], 1);
+            skey[p] = key[k];
+            sidx[p] = (uint16_t)(t + k * kSmallBlock);
+        }
+    __syncthreads();
+    for (int p = t; p < n; p += kSmallBlock) {
+        const uint64_t kp = skey[p];
+        const int32_t idx = sidx[p], d = (int32_t)(kp >> kShift);
+        int32_t r = sub[d];
+        for (int32_t q = sub[d]; q < sub[d + 1]; ++q) r += key_less(skey[q], sidx[q], kp, idx);
+        J.perm[r] = idx;
+        if (J.inv) J.inv[idx] = r;
+    }
+}
+
 // ---- permuted CSR --------------------------------------------------------------
 
 __global__ __launch_bounds__(kBlock) void k_perm_row_len(int32_t nrows, const int32_t *rp,
@@ -293,6 +377,36 @@ __global__ __launch_bounds__(kBlock) void k_perm_row_len(int32_t nrows, const in
     } else if (i == nrows) {
         len[i] = 0;
     }
+}
+
+// Permuted row starts of up to kPermSmall rows by one workgroup: one launch
+// where the lengths and their scan take four.
+__global__ __launch_bounds__(kSmallBlock) void k_perm_row_ptr_small(int32_t nrows, const int32_t *__restrict__ rp,
+                                                                    const int32_t *__restrict__ rperm,
+                                                                    int32_t *__restrict__ rp_b) {
+    constexpr int kPer = kPermSmall / kSmallBlock;
+    __shared__ int32_t len[kPermSmall];
+    __shared__ int32_t wsum[kSmallBlock / kWave];
+    const int t = threadIdx.x;
+    int32_t src[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) src[k] = t + k * kSmallBlock < nrows ? rperm[t + k * kSmallBlock] : -1;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) len[t + k * kSmallBlock] = src[k] >= 0 ? rp[src[k] + 1] - rp[src[k]] : 0;
+    __syncthreads();
+    int32_t v[kPer], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        v[k] = len[t * kPer + k];
+        sum += v[k];
+    }
+    int32_t at = small_exclusive_scan(sum, wsum);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        if (t * kPer + k <= nrows) rp_b[t * kPer + k] = at;
+        at += v[k];
+    }
+    if (nrows == kPermSmall && t == kSmallBlock - 1) rp_b[nrows] = at;
 }
 
 constexpr int kSortRows = 16;                           // rows of A per wavefront, at most
@@ -717,45 +831,54 @@ __device__ inline ArgMax block_argmax(ArgMax v, ArgMax *sh) {
     return sh[0];
 }
 
+// one dimension's shuffle; a launch takes rows and columns together (blockIdx.y)
+constexpr int kGradJobs = 2;
+struct GradDim {
+    int64_t n, na;
+    const int32_t *counts;                               // entries per row or column
+    const int32_t *parts;                                // pa, then pb
+    int32_t *perm, *inv;
+};
+struct GradDims {
+    GradDim d[kGradJobs];
+};
 // gradient g_i = h[i+1] - h[i], i < n - 1 (n >= 2)
-__global__ __launch_bounds__(kBlock) void k_grad_argmax_partial(int64_t n, const int32_t *h,
-                                                                ArgMax *part) {
+__global__ __launch_bounds__(kBlock) void k_grad_argmax_partial(GradDims dims, ArgMax *part) {
     __shared__ ArgMax sh[kBlock];
+    const int64_t n = dims.d[blockIdx.y].n;
+    const int32_t *h = dims.d[blockIdx.y].counts;
     ArgMax best{INT64_MIN, INT64_MAX};
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n - 1;
          i += (int64_t)gridDim.x * blockDim.x)
         best = better(best, ArgMax{(int64_t)h[i + 1] - h[i], i});
     best = block_argmax(best, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = best;
+    if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = best;
 }
 
 __global__ __launch_bounds__(kBlock) void k_grad_argmax_final(int32_t nparts, const ArgMax *part,
                                                               int32_t *pivot) {
     __shared__ ArgMax sh[kBlock];
     ArgMax best{INT64_MIN, INT64_MAX};
-    for (int i = threadIdx.x; i < nparts; i += kBlock) best = better(best, part[i]);
+    for (int i = threadIdx.x; i < nparts; i += kBlock) best = better(best, part[(int64_t)blockIdx.x * nparts + i]);
     best = block_argmax(best, sh);
-    if (threadIdx.x == 0) *pivot = (int32_t)best.i;
+    if (threadIdx.x == 0) pivot[blockIdx.x] = (int32_t)best.i;
 }
 
 // Riffle: A (local permutation pa of [0, na)) and B (pb of [0, nb), offset
 // by na) alternate while both last; the longer part's remainder follows.
-__global__ __launch_bounds__(kBlock) void k_riffle(int64_t na, int64_t nb, const int32_t *pa,
-                                                   const int32_t *pb, int32_t *perm) {
-    const int64_t m = na < nb ? na : nb, n = na + nb;
+// Dimension blockIdx.y.
+__global__ __launch_bounds__(kBlock) void k_riffle(GradDims dims) {
+    const GradDim &D = dims.d[blockIdx.y];
+    const int64_t n = D.n, na = D.na, nb = n - na, m = na < nb ? na : nb;
+    const int32_t *pa = D.parts, *pb = D.parts + na;
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n;
          t += (int64_t)gridDim.x * blockDim.x) {
         int32_t v;
         if (t < 2 * m) v = (t & 1) ? (int32_t)(na + pb[t >> 1]) : pa[t >> 1];
         else v = na > m ? pa[m + (t - 2 * m)] : (int32_t)(na + pb[m + (t - 2 * m)]);
-        perm[t] = v;
+        D.perm[t] = v;
+        D.inv[v] = (int32_t)t;
     }
-}
-
-__global__ __launch_bounds__(kBlock) void k_invert(int64_t n, const int32_t *perm, int32_t *inv) {
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x)
-        inv[perm[k]] = (int32_t)k;
 }
 
 }  // namespace
@@ -788,42 +911,56 @@ hipError_t launch_exclusive_scan(const int32_t *in, int32_t *out, int64_t n, voi
     return hipGetLastError();
 }
 
-size_t random_perm_ws_bytes(int64_t n) {
-    if (n <= kLdsPermMax) {
-        const int64_t nwg = std::max<int64_t>(1, cdiv(n, kPermItems));
-        const int64_t ncounts = (nwg << radix_bits(n)) + 1;
-        return align256(sizeof(int32_t) * ncounts) + align256(sizeof(int32_t) * (n + 1)) +
-               scan_ws_bytes(ncounts);
+namespace {
+
+// The jobs of the LDS radix path among `count` requests, laid out in ws (or
+// with ws null only measured); *small the ones of a single workgroup.
+struct PermPlan {
+    PermJobs mid, small;
+    int nmid = 0, nsmall = 0;
+    int64_t ncounts = 0;
+    size_t bytes = 0;
+    int max_bits = 0, max_nwg = 0;
+};
+PermPlan perm_plan(const PermRequest *req, int count, void *ws) {
+    PermPlan p{};
+    int64_t items = 0;
+    for (int i = 0; i < count; ++i) {
+        const PermRequest &r = req[i];
+        if (r.n <= 0 || r.n > kLdsPermMax) continue;
+        PermJob j{r.n, r.seed, r.perm, r.inv, 0, 1, 0, 0, nullptr, nullptr};
+        if (r.n <= kPermSmall) {
+            p.small.j[p.nsmall++] = j;
+            continue;
+        }
+        j.bits = radix_bits(r.n);
+        j.chunk = r.n <= kPermFew ? 1024 : 8192;
+        j.nwg = (int32_t)cdiv(r.n, j.chunk);
+        j.base = (int32_t)items;
+        j.counts = (int32_t *)(uintptr_t)(sizeof(int32_t) * (size_t)p.ncounts);      // offsets, until ws is known
+        j.items = (int32_t *)(uintptr_t)(sizeof(int32_t) * (size_t)items);
+        p.ncounts += (int64_t)j.nwg << j.bits;
+        items += r.n;
+        p.max_bits = std::max(p.max_bits, (int)j.bits);
+        p.max_nwg = std::max(p.max_nwg, (int)j.nwg);
+        p.mid.j[p.nmid++] = j;
     }
-    int64_t nb = int64_t(1) << bucket_bits(n);
-    return align256(sizeof(int32_t) * (nb + 1)) + 2 * align256(sizeof(int32_t) * (n + 1)) +
-           scan_ws_bytes(nb + 1);
+    const size_t cb = align256(sizeof(int32_t) * (size_t)p.ncounts), ib = align256(sizeof(int32_t) * (size_t)items);
+    p.bytes = p.nmid ? cb + ib + scan_ws_bytes(p.ncounts) : 0;
+    for (int i = 0; i < p.nmid && ws; ++i) {
+        p.mid.j[i].counts = (int32_t *)((char *)ws + (uintptr_t)p.mid.j[i].counts);
+        p.mid.j[i].items = (int32_t *)((char *)ws + cb + (uintptr_t)p.mid.j[i].items);
+    }
+    return p;
 }
 
-hipError_t launch_random_perm(int64_t n, uint64_t stream_seed, int32_t *perm, int32_t *inv,
-                              void *ws, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    if (n <= kLdsPermMax) {
-        const int bits = radix_bits(n);
-        const int32_t nd = 1 << bits;
-        const int32_t nwg = (int32_t)std::max<int64_t>(1, cdiv(n, kPermItems));
-        const int64_t ncounts = (int64_t)nwg * nd + 1;
-        char *w = (char *)ws;
-        int32_t *counts = (int32_t *)w;  w += align256(sizeof(int32_t) * ncounts);
-        int32_t *items = (int32_t *)w;   w += align256(sizeof(int32_t) * (n + 1));
-        void *scan_ws = w;
-        const size_t lds = sizeof(int32_t) * (size_t)nd;
-        hipLaunchKernelGGL(k_perm_count, dim3(nwg), dim3(kBlock), lds, s, n, stream_seed, bits, nwg,
-                           counts);
-        hipError_t e = launch_fill_i32(counts + ncounts - 1, 1, 0, s);
-        if (e != hipSuccess) return e;
-        if ((e = launch_exclusive_scan(counts, counts, ncounts, scan_ws, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_perm_scatter, dim3(nwg), dim3(kBlock), lds, s, n, stream_seed, bits, nwg,
-                           (const int32_t *)counts, items);
-        hipLaunchKernelGGL(k_perm_bucket_sort, dim3(nd), dim3(kBlock), 0, s, nd, nwg, stream_seed,
-                           bits, (const int32_t *)counts, (const int32_t *)items, perm, inv);
-        return hipGetLastError();
-    }
+size_t bucket_perm_ws_bytes(int64_t n) {                 // n > kLdsPermMax
+    const int64_t nb = int64_t(1) << bucket_bits(n);
+    return align256(sizeof(int32_t) * (nb + 1)) + 2 * align256(sizeof(int32_t) * (n + 1)) + scan_ws_bytes(nb + 1);
+}
+
+hipError_t launch_bucket_perm(const PermRequest &r, void *ws, hipStream_t s) {
+    const int64_t n = r.n;
     const int bits = bucket_bits(n);
     const int64_t nb = int64_t(1) << bits;
     char *w = (char *)ws;
@@ -834,14 +971,43 @@ hipError_t launch_random_perm(int64_t n, uint64_t stream_seed, int32_t *perm, in
     hipError_t e = launch_fill_i32(counts, nb + 1, 0, s);
     if (e != hipSuccess) return e;
     const int g = grid_for(n, kBlock, 8192);
-    hipLaunchKernelGGL(k_bucket_count, dim3(g), dim3(kBlock), 0, s, n, stream_seed, bits, counts,
-                       slot);
+    hipLaunchKernelGGL(k_bucket_count, dim3(g), dim3(kBlock), 0, s, n, r.seed, bits, counts, slot);
     e = launch_exclusive_scan(counts, counts, nb + 1, scan_ws, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bucket_scatter, dim3(g), dim3(kBlock), 0, s, n, stream_seed, bits,
+    hipLaunchKernelGGL(k_bucket_scatter, dim3(g), dim3(kBlock), 0, s, n, r.seed, bits,
                        (const int32_t *)counts, (const int32_t *)slot, items);
-    hipLaunchKernelGGL(k_perm_bucket_sort, dim3((unsigned)nb), dim3(kBlock), 0, s, (int32_t)nb, 1,
-                       stream_seed, bits, (const int32_t *)counts, (const int32_t *)items, perm, inv);
+    PermJobs jobs{};
+    jobs.j[0] = PermJob{n, r.seed, r.perm, r.inv, bits, 1, 0, 0, counts, items};
+    hipLaunchKernelGGL(k_perm_bucket_sort, dim3((unsigned)nb), dim3(kBlock), 0, s, jobs);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+size_t random_perms_ws_bytes(const PermRequest *req, int count) {
+    size_t b = perm_plan(req, count, nullptr).bytes;
+    for (int i = 0; i < count; ++i)
+        if (req[i].n > kLdsPermMax) b = std::max(b, bucket_perm_ws_bytes(req[i].n));
+    return b;
+}
+
+hipError_t launch_random_perms(const PermRequest *req, int count, void *ws, hipStream_t s) {
+    if (count > kPermJobs) return hipErrorInvalidValue;
+    hipError_t e;
+    const PermPlan p = perm_plan(req, count, ws);
+    if (p.nsmall) hipLaunchKernelGGL(k_perm_small, dim3(p.nsmall), dim3(kSmallBlock), 0, s, p.small);
+    if (p.nmid) {
+        const size_t lds = sizeof(int32_t) << p.max_bits;
+        hipLaunchKernelGGL(k_perm_count, dim3(p.max_nwg, p.nmid), dim3(kBlock), lds, s, p.mid);
+        int32_t *counts = p.mid.j[0].counts;
+        if ((e = launch_exclusive_scan(counts, counts, p.ncounts, (char *)ws + p.bytes - scan_ws_bytes(p.ncounts),
+                                       s)) != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(k_perm_scatter, dim3(p.max_nwg, p.nmid), dim3(kBlock), lds, s, p.mid);
+        hipLaunchKernelGGL(k_perm_bucket_sort, dim3(1 << p.max_bits, p.nmid), dim3(kBlock), 0, s, p.mid);
+    }
+    for (int i = 0; i < count; ++i)                      // one after the other, on the workspace of all
+        if (req[i].n > kLdsPermMax && (e = launch_bucket_perm(req[i], ws, s)) != hipSuccess) return e;
     return hipGetLastError();
 }
 
@@ -849,6 +1015,10 @@ size_t permuted_row_ptr_ws_bytes(int32_t nrows) { return scan_ws_bytes((int64_t)
 
 hipError_t launch_permuted_row_ptr(int32_t nrows, const int32_t *rp, const int32_t *rperm,
                                    int32_t *rp_b, void *ws, hipStream_t s) {
+    if (nrows <= kPermSmall) {
+        hipLaunchKernelGGL(k_perm_row_ptr_small, dim3(1), dim3(kSmallBlock), 0, s, nrows, rp, rperm, rp_b);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_perm_row_len, dim3(grid_for((int64_t)nrows + 1, kBlock, 1 << 30)),
                        dim3(kBlock), 0, s, nrows, rp, rperm, rp_b);
     hipError_t e = hipGetLastError();
@@ -1048,39 +1218,68 @@ namespace {
 constexpr int kArgParts = 1024;
 }
 
-size_t gradient_perm_ws_bytes(int64_t n) {
-    return align256(sizeof(ArgMax) * kArgParts) + 256 + align256(sizeof(int32_t) * (n + 1)) +
-           random_perm_ws_bytes(n);
+namespace {
+// [partial maxima | the parts' permutations, dimension by dimension | the permutations' own workspace]
+size_t grad_parts_bytes(const GradRequest *req, int count) {
+    size_t b = 0;
+    for (int i = 0; i < count; ++i) b += align256(sizeof(int32_t) * (size_t)(req[i].n + 1));
+    return b;
+}
+constexpr size_t kArgBytes = (sizeof(ArgMax) * kArgParts * kGradJobs + 255) / 256 * 256;
+}  // namespace
+
+size_t gradient_perms_ws_bytes(const GradRequest *req, int count) {
+    // the pivots may lie anywhere: each part as large as the whole, on either
+    // path, and with the count table of a part of few indices, whose workgroups
+    // and buckets are smaller
+    PermRequest p[2 * kGradJobs] = {};
+    for (int i = 0; i < 2 * count; ++i) p[i].n = std::max<int64_t>(req[i / 2].n, 1);
+    size_t w = random_perms_ws_bytes(p, 2 * count);
+    for (int i = 0; i < 2 * count; ++i) p[i].n = std::min<int64_t>(p[i].n, kLdsPermMax);
+    w = std::max(w, random_perms_ws_bytes(p, 2 * count));
+    PermRequest few = {kPermFew, 0, nullptr, nullptr};
+    w += 2 * count * random_perms_ws_bytes(&few, 1);
+    return kArgBytes + grad_parts_bytes(req, count) + w;
 }
 
-hipError_t launch_gradient_perm(int64_t n, const int32_t *counts, uint64_t stream_seed,
-                                int32_t *perm, int32_t *inv, void *ws, hipStream_t s) {
-    if (n < 2) {
-        hipError_t e = launch_iota_i32(perm, n, s);
-        return e != hipSuccess ? e : launch_iota_i32(inv, n, s);
+hipError_t launch_gradient_perms(const GradRequest *req, int count, int32_t *pivots, void *ws, hipStream_t s) {
+    if (count > kGradJobs) return hipErrorInvalidValue;
+    hipError_t e;
+    ArgMax *part = (ArgMax *)ws;
+    char *w = (char *)ws + kArgBytes;
+    GradDims dims{};
+    PermRequest parts[2 * kGradJobs];
+    int nd = 0;
+    int64_t n_max = 0;
+    for (int i = 0; i < count; ++i) {
+        if (req[i].n < 2) {                              // nothing to cut
+            if ((e = launch_iota_i32(req[i].perm, req[i].n, s)) != hipSuccess ||
+                (e = launch_iota_i32(req[i].inv, req[i].n, s)) != hipSuccess)
+                return e;
+            continue;
+        }
+        dims.d[nd] = GradDim{req[i].n, 0, req[i].counts, (const int32_t *)w, req[i].perm, req[i].inv};
+        parts[2 * nd].seed = req[i].seed;
+        w += align256(sizeof(int32_t) * (size_t)(req[i].n + 1));
+        n_max = std::max(n_max, req[i].n);
+        ++nd;
     }
-    char *w = (char *)ws;
-    ArgMax *part = (ArgMax *)w;  w += align256(sizeof(ArgMax) * kArgParts);
-    int32_t *pivot = (int32_t *)w;  w += 256;
-    int32_t *pab = (int32_t *)w;  w += align256(sizeof(int32_t) * (n + 1));
-    void *rws = w;
-    const int g = grid_for(n - 1, kBlock, kArgParts);
-    hipLaunchKernelGGL(k_grad_argmax_partial, dim3(g), dim3(kBlock), 0, s, n, counts, part);
-    hipLaunchKernelGGL(k_grad_argmax_final, dim3(1), dim3(kBlock), 0, s, g, (const ArgMax *)part,
-                       pivot);
-    int32_t p = 0;
-    hipError_t e = hipMemcpyAsync(&p, pivot, sizeof p, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);     // the pivot sizes the two parts
-    if (e != hipSuccess) return e;
-    const int64_t na = (int64_t)p + 1, nb = n - na;
-    // part B's keys continue the stream at index na: key(s, na + i) = key(s + na*gamma, i)
-    const uint64_t seed_b = stream_seed + (uint64_t)na * 0x9e3779b97f4a7c15ull;
-    if ((e = launch_random_perm(na, stream_seed, pab, nullptr, rws, s)) != hipSuccess) return e;
-    if ((e = launch_random_perm(nb, seed_b, pab + na, nullptr, rws, s)) != hipSuccess) return e;
-    const int gr = grid_for(n, kBlock, 16384);
-    hipLaunchKernelGGL(k_riffle, dim3(gr), dim3(kBlock), 0, s, na, nb, (const int32_t *)pab,
-                       (const int32_t *)(pab + na), perm);
-    hipLaunchKernelGGL(k_invert, dim3(gr), dim3(kBlock), 0, s, n, (const int32_t *)perm, inv);
+    if (nd == 0) return hipSuccess;
+    const int g = grid_for(n_max - 1, kBlock, kArgParts);
+    hipLaunchKernelGGL(k_grad_argmax_partial, dim3(g, nd), dim3(kBlock), 0, s, dims, part);
+    hipLaunchKernelGGL(k_grad_argmax_final, dim3(nd), dim3(kBlock), 0, s, g, (const ArgMax *)part, pivots);
+    if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    for (int i = 0; i < nd; ++i) {                       // the pivots size the parts
+        GradDim &D = dims.d[i];
+        D.na = (int64_t)pivots[i] + 1;
+        int32_t *pab = const_cast<int32_t *>(D.parts);
+        const uint64_t seed = parts[2 * i].seed;
+        parts[2 * i] = PermRequest{D.na, seed, pab, nullptr};
+        // part B's keys continue the stream at index na: key(s, na + i) = key(s + na*gamma, i)
+        parts[2 * i + 1] = PermRequest{D.n - D.na, seed + (uint64_t)D.na * 0x9e3779b97f4a7c15ull, pab + D.na, nullptr};
+    }
+    if ((e = launch_random_perms(parts, 2 * nd, w, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_riffle, dim3(grid_for(n_max, kBlock, 16384), nd), dim3(kBlock), 0, s, dims);
     return hipGetLastError();
 }
 
