@@ -925,10 +925,15 @@ mxe_status mxe_permute(mxe_ctx *ctx, mxe_mat a, uint64_t seed, uint32_t mode, vo
     } else {
         MXE_HIP(launch_random_perms(perms, np, ws.p, s));
     }
-    MXE_HIP(launch_permuted_row_ptr(M, A->rp, B->rperm, B->rp, ws.p, s));
+    // where the longest row is known and short, no group of rows is long
+    Scratch list;
+    if (const size_t db = sort_deferred_bytes(M); db && (A->max_row < 0 || A->max_row > 32))
+        if ((st = list.alloc(ctx->pool, db, s))) return st;
+    int32_t *deferred = (int32_t *)list.p;
+    MXE_HIP(launch_permuted_row_ptr(M, A->rp, B->rperm, B->rp, deferred, ws.p, s));
     MXE_HIP(launch_gather_relabel_sort(M, N, A->rp, A->col, A->val, vb, B->rinv,
                                        (mode & MXE_COLS) ? B->cinv : nullptr, B->rp, B->col,
-                                       B->val, s));
+                                       B->val, deferred, s));
     if ((st = note_use(*A, s)) || (st = note_use(*B, s))) return st;
     B->id = ctx->next_id++;
     ctx->mats[B->id] = B;

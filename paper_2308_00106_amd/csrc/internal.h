@@ -53,16 +53,20 @@ hipError_t launch_gradient_perms(const GradRequest *req, int count, int32_t *piv
 // ---- permuted CSR --------------------------------------------------------
 // rp_b[i'] = exclusive prefix of A's row lengths taken in rperm order.
 // Workspace: permuted_row_ptr_ws_bytes(nrows).
+// deferred (or null): memory of sort_deferred_bytes(nrows) for the launch below,
+// its count cleared on the way.
 size_t permuted_row_ptr_ws_bytes(int32_t nrows);
 hipError_t launch_permuted_row_ptr(int32_t nrows, const int32_t *rp, const int32_t *rperm,
-                                   int32_t *rp_b, void *ws, hipStream_t s);
+                                   int32_t *rp_b, int32_t *deferred, void *ws, hipStream_t s);
 // Row i of A -> row rinv[i] of B (at rp_b[rinv[i]]) with column j -> cinv[j]
 // (cinv may be NULL: no column permutation), re-sorted by new column.
-// val_bytes: 8, 4, 2.
+// val_bytes: 8, 4, 2. deferred (or null, where no sixteen rows hold more than 512
+// entries): groups of long rows are moved by a launch of their own.
+size_t sort_deferred_bytes(int32_t nrows);
 hipError_t launch_gather_relabel_sort(int32_t nrows, int32_t ncols, const int32_t *rp, const int32_t *col,
                                       const void *val, int val_bytes, const int32_t *rinv,
                                       const int32_t *cinv, const int32_t *rp_b, int32_t *col_b,
-                                      void *val_b, hipStream_t s);
+                                      void *val_b, int32_t *deferred, hipStream_t s);
 
 // ---- vectors --------------------------------------------------------------
 // Xp row j = X row perm[j], n rows of k values of elem_bytes 8 (FP64) or 4 (FP32).

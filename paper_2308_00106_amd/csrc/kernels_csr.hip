@@ -369,13 +369,14 @@ __global__ __launch_bounds__(kSmallBlock) void k_perm_small(PermJobs jobs) {
 // ---- permuted CSR --------------------------------------------------------------
 
 __global__ __launch_bounds__(kBlock) void k_perm_row_len(int32_t nrows, const int32_t *rp,
-                                                         const int32_t *rperm, int32_t *len) {
+                                                         const int32_t *rperm, int32_t *len, int32_t *zero) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < nrows) {
         int32_t src = rperm[i];
         len[i] = rp[src + 1] - rp[src];
     } else if (i == nrows) {
         len[i] = 0;
+        if (zero) *zero = 0;
     }
 }
 
@@ -433,29 +434,36 @@ __device__ inline void wave_sync() {
 // counters, an entry's is the one at c / ncols of them, so that after a random
 // column permutation most hold one entry and a rank takes a few steps instead
 // of L. A band of 10,000 rows of 256 entries in 1M rows of 8 made the kernel
-// take 885 us when its wavefronts ranked them pair by pair, 194 us now; 2M rows of
-// 10 FP64 entries take 289 us either way. A row longer than the stage is ranked pair by pair, from LDS up to kSortLong
+// take 885 us when its wavefronts ranked them pair by pair; 2M rows of 10 FP64
+// entries take 284 us either way. A row longer than the stage is ranked pair by pair, from LDS up to kSortLong
 // entries, else against cinv in memory.
-template <typename V, int ROWS>
-__global__ __launch_bounds__(kBlock, 8) void k_gather_relabel_sort(
-    int32_t nrows, float inv_ncols, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-    const V *__restrict__ val, const int32_t *__restrict__ rinv, const int32_t *__restrict__ cinv,
-    const int32_t *__restrict__ rp_b, int32_t *__restrict__ col_b, V *__restrict__ val_b) {
-    __shared__ int32_t buffer[kSortWaves][kSortLong];
-    __shared__ uint32_t counts[kSortWaves][kSortStage / 2];
-    __shared__ int32_t rstart[kSortWaves][ROWS + 1];   // row starts, relative to e0
-    __shared__ int32_t rdest[kSortWaves][ROWS];        // where each row goes in B
+// A group of rows that overfills the stage is left to k_sort_deferred where
+// `deferred` is given: its count, then the groups.
+struct SortShared {
+    int32_t buffer[kSortWaves][kSortLong];
+    uint32_t counts[kSortWaves][kSortStage / 2];
+    int32_t rstart[kSortWaves][kSortRows + 1];              // row starts, relative to e0
+    int32_t rdest[kSortWaves][kSortRows];                   // where each row goes in B
+};
+template <typename V>
+__device__ __attribute__((always_inline)) inline void sort_rows(
+    SortShared &sh, int64_t r0, int nr, float inv_ncols, const int32_t *__restrict__ rp,
+    const int32_t *__restrict__ col, const V *__restrict__ val, const int32_t *__restrict__ rinv,
+    const int32_t *__restrict__ cinv, const int32_t *__restrict__ rp_b, int32_t *__restrict__ col_b,
+    V *__restrict__ val_b, int32_t *__restrict__ deferred) {
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int64_t r0 = ((int64_t)blockIdx.x * kSortWaves + wave) * ROWS;
-    if (r0 >= nrows) return;                            // uniform per wavefront
-    const int nr = (int)std::min<int64_t>(ROWS, nrows - r0);
     const int32_t e0 = rp[r0];
-    int32_t *stage = buffer[wave], *sorted = buffer[wave] + kSortStage;
-    uint32_t *cnt = counts[wave];
-    const int32_t *rs = rstart[wave];
+    int32_t *stage = sh.buffer[wave];
+    uint32_t *cnt = sh.counts[wave];
+    const int32_t *rs = sh.rstart[wave];
+    int32_t *rdest = sh.rdest[wave];
     const int32_t start = lane <= nr ? rp[r0 + lane] - e0 : 0;
-    if (lane <= nr) rstart[wave][lane] = start;
-    if (lane < nr) rdest[wave][lane] = rp_b[rinv[r0 + lane]];
+    if (deferred && __shfl(start, nr) > kSortStage) {
+        if (lane == 0) deferred[1 + atomicAdd(deferred, 1)] = (int32_t)(r0 / kSortRows);
+        return;
+    }
+    if (lane <= nr) sh.rstart[wave][lane] = start;
+    if (lane < nr) rdest[lane] = rp_b[rinv[r0 + lane]];
     wave_sync();
     auto relabel = [&](int32_t j) { return cinv ? cinv[j] : j; };
     for (int j0 = 0, j1; j0 < nr; j0 = j1) {            // rows [j0, j1): at most kSortStage entries
@@ -463,7 +471,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_gather_relabel_sort(
         const uint64_t fit = __ballot(lane > j0 && lane <= nr && start - b0 <= kSortStage);
         if (fit == 0) {                                 // a row longer than the stage
             j1 = j0 + 1;
-            const int32_t b = e0 + b0, len = rs[j1] - b0, d0 = rdest[wave][j0];
+            const int32_t b = e0 + b0, len = rs[j1] - b0, d0 = rdest[j0];
             const bool staged = len <= kSortLong;
             if (staged)
                 for (int32_t t = lane; t < len; t += kWave) stage[t] = relabel(col[b + t]);
@@ -509,33 +517,32 @@ __global__ __launch_bounds__(kBlock, 8) void k_gather_relabel_sort(
                     r = 0;
                     for (int32_t u = b; u < e; ++u) r += stage[u] < c;
                 }
-                col_b[rdest[wave][j] + r] = c;
-                val_b[rdest[wave][j] + r] = val[e0 + b0 + i];
+                col_b[rdest[j] + r] = c;
+                val_b[rdest[j] + r] = val[e0 + b0 + i];
             }
             wave_sync();
             continue;
         }
         // two counters to a word; after the last pass a counter holds its bucket's end
+        constexpr int kPer = kSortStage / kWave;
         for (int32_t i = lane; i < kSortStage / 2; i += kWave) cnt[i] = 0;
-        for (int32_t i = lane; i < n; i += 4 * kWave) {
-            int32_t j[4];
+        int32_t c[kPer];
+        uint32_t at[kPer];                              // row of the group << 16 | counter
 #pragma unroll
-            for (int u = 0; u < 4; ++u) j[u] = i + u * kWave < n ? col[e0 + b0 + i + u * kWave] : 0;
+        for (int k = 0; k < kPer; ++k) c[k] = lane + k * kWave < n ? col[e0 + b0 + lane + k * kWave] : 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) j[u] = cinv[j[u]];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i + u * kWave < n) stage[i + u * kWave] = j[u];
-        }
+        for (int k = 0; k < kPer; ++k) c[k] = cinv[c[k]];
         wave_sync();
-        // rounding keeps the order of the products, hence of the counters
-        auto bucket_of = [&](int32_t c, int j) {
-            const int32_t len = rs[j + 1] - rs[j];
-            return rs[j] - b0 + min((int32_t)((float)c * inv_ncols * (float)len), len - 1);
-        };
-        for (int32_t i = lane; i < n; i += kWave) {
-            const int32_t k = bucket_of(stage[i], row_of(i));
-            atomicAdd(&cnt[k >> 1], 1u << (k & 1) * 16);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int32_t i = lane + k * kWave;
+            if (i >= n) continue;
+            const int j = row_of(i);
+            const int32_t b = rs[j], len = rs[j + 1] - b;
+            // rounding keeps the order of the products, hence of the counters
+            const uint32_t q = (uint32_t)(b - b0 + min((int32_t)((float)c[k] * inv_ncols * (float)len), len - 1));
+            at[k] = (uint32_t)j << 16 | q;
+            atomicAdd(&cnt[q >> 1], 1u << (q & 1) * 16);
         }
         wave_sync();
         uint32_t v[kSortStage / 2 / kWave], sum = 0;    // counts to starts
@@ -557,23 +564,64 @@ __global__ __launch_bounds__(kBlock, 8) void k_gather_relabel_sort(
             inc += (v[k] & 0xffffu) + (v[k] >> 16);
         }
         wave_sync();
-        for (int32_t i = lane; i < n; i += kWave) {
-            const int32_t c = stage[i], k = bucket_of(c, row_of(i));
-            sorted[atomicAdd(&cnt[k >> 1], 1u << (k & 1) * 16) >> (k & 1) * 16 & 0xffffu] = c;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const uint32_t q = at[k] & 0xffffu;
+            if (lane + k * kWave < n)
+                stage[atomicAdd(&cnt[q >> 1], 1u << (q & 1) * 16) >> (q & 1) * 16 & 0xffffu] = c[k];
         }
         wave_sync();
         const uint16_t *end = reinterpret_cast<const uint16_t *>(cnt);
-        for (int32_t i = lane; i < n; i += kWave) {
-            const int j = row_of(i);
-            const int32_t c = stage[i], k = bucket_of(c, j);
-            const int32_t first = k ? end[k - 1] : 0, past = end[k];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int32_t i = lane + k * kWave;
+            if (i >= n) continue;
+            const int j = at[k] >> 16;
+            const uint32_t q = at[k] & 0xffffu;
+            const int32_t first = q ? end[q - 1] : 0, past = end[q];
             int32_t r = first;
-            for (int32_t u = first; u < past; ++u) r += sorted[u] < c;
-            const int32_t d = rdest[wave][j] - (rs[j] - b0) + r;
-            col_b[d] = c;
+            for (int32_t u = first; u < past; ++u) r += stage[u] < c[k];
+            const int32_t d = rdest[j] - (rs[j] - b0) + r;
+            col_b[d] = c[k];
             val_b[d] = val[e0 + b0 + i];
         }
         wave_sync();
+    }
+}
+
+template <typename V, int ROWS>
+__global__ __launch_bounds__(kBlock, 8) void k_gather_relabel_sort(
+    int32_t nrows, float inv_ncols, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+    const V *__restrict__ val, const int32_t *__restrict__ rinv, const int32_t *__restrict__ cinv,
+    const int32_t *__restrict__ rp_b, int32_t *__restrict__ col_b, V *__restrict__ val_b,
+    int32_t *__restrict__ deferred) {
+    __shared__ SortShared sh;
+    const int64_t r0 = ((int64_t)blockIdx.x * kSortWaves + threadIdx.x / kWave) * ROWS;
+    if (r0 >= nrows) return;                            // uniform per wavefront
+    sort_rows<V>(sh, r0, (int)std::min<int64_t>(ROWS, nrows - r0), inv_ncols, rp, col, val, rinv, cinv, rp_b, col_b,
+                 val_b, deferred);
+}
+
+// The groups left out, kDeferredRows rows to a wavefront: a band of long rows is
+// a few groups among many, whose wavefronts would still be moving sixteen of
+// them when all others have ended (the band above: 178 us in one launch, 110 +
+// 43 in two; a launch that finds no group takes 3).
+constexpr int kDeferredRows = 2, kDeferredGrid = 512;
+template <typename V>
+__global__ __launch_bounds__(kBlock, 8) void k_sort_deferred(
+    int32_t nrows, float inv_ncols, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+    const V *__restrict__ val, const int32_t *__restrict__ rinv, const int32_t *__restrict__ cinv,
+    const int32_t *__restrict__ rp_b, int32_t *__restrict__ col_b, V *__restrict__ val_b,
+    const int32_t *__restrict__ deferred) {
+    __shared__ SortShared sh;
+    constexpr int kUnits = kSortRows / kDeferredRows;
+    const int64_t units = (int64_t)deferred[0] * kUnits;
+    for (int64_t u = blockIdx.x * (int64_t)kSortWaves + threadIdx.x / kWave; u < units;
+         u += (int64_t)gridDim.x * kSortWaves) {        // uniform per wavefront
+        const int64_t r0 = (int64_t)deferred[1 + u / kUnits] * kSortRows + u % kUnits * kDeferredRows;
+        if (r0 < nrows)
+            sort_rows<V>(sh, r0, (int)std::min<int64_t>(kDeferredRows, nrows - r0), inv_ncols, rp, col, val, rinv,
+                         cinv, rp_b, col_b, val_b, nullptr);
     }
 }
 
@@ -1011,16 +1059,20 @@ hipError_t launch_random_perms(const PermRequest *req, int count, void *ws, hipS
     return hipGetLastError();
 }
 
+size_t sort_deferred_bytes(int32_t nrows) {
+    return nrows < kSortFew ? 0 : align256(sizeof(int32_t) * (size_t)(cdiv(nrows, kSortRows) + 1));
+}
+
 size_t permuted_row_ptr_ws_bytes(int32_t nrows) { return scan_ws_bytes((int64_t)nrows + 1); }
 
 hipError_t launch_permuted_row_ptr(int32_t nrows, const int32_t *rp, const int32_t *rperm,
-                                   int32_t *rp_b, void *ws, hipStream_t s) {
+                                   int32_t *rp_b, int32_t *deferred, void *ws, hipStream_t s) {
     if (nrows <= kPermSmall) {
         hipLaunchKernelGGL(k_perm_row_ptr_small, dim3(1), dim3(kSmallBlock), 0, s, nrows, rp, rperm, rp_b);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_perm_row_len, dim3(grid_for((int64_t)nrows + 1, kBlock, 1 << 30)),
-                       dim3(kBlock), 0, s, nrows, rp, rperm, rp_b);
+                       dim3(kBlock), 0, s, nrows, rp, rperm, rp_b, deferred);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_exclusive_scan(rp_b, rp_b, (int64_t)nrows + 1, ws, s);
@@ -1029,7 +1081,7 @@ hipError_t launch_permuted_row_ptr(int32_t nrows, const int32_t *rp, const int32
 hipError_t launch_gather_relabel_sort(int32_t nrows, int32_t ncols, const int32_t *rp, const int32_t *col,
                                       const void *val, int val_bytes, const int32_t *rinv,
                                       const int32_t *cinv, const int32_t *rp_b, int32_t *col_b,
-                                      void *val_b, hipStream_t s) {
+                                      void *val_b, int32_t *deferred, hipStream_t s) {
     if (nrows <= 0) return hipSuccess;
     const float inv_n = 1.0f / (float)std::max(ncols, 1);
     // few rows leave CUs idle at kSortRows per wavefront: 4096 rows of 16 took
@@ -1039,10 +1091,16 @@ hipError_t launch_gather_relabel_sort(int32_t nrows, int32_t ncols, const int32_
     const unsigned g = (unsigned)cdiv(nrows, (int64_t)(few ? kSortRows / 2 : kSortRows) * kSortWaves);
 #define MXE_SORT(V, ROWS)                                                                                \
     hipLaunchKernelGGL((k_gather_relabel_sort<V, ROWS>), dim3(g), dim3(kBlock), 0, s, nrows, inv_n, rp, col, \
-                       (const V *)val, rinv, cinv, rp_b, col_b, (V *)val_b)
-#define MXE_SORT_FEW(V)                   \
-    if (few) MXE_SORT(V, kSortRows / 2);  \
-    else MXE_SORT(V, kSortRows);
+                       (const V *)val, rinv, cinv, rp_b, col_b, (V *)val_b, few ? nullptr : deferred)
+#define MXE_SORT_FEW(V)                                                                                  \
+    if (few) {                                                                                           \
+        MXE_SORT(V, kSortRows / 2);                                                                      \
+    } else {                                                                                             \
+        MXE_SORT(V, kSortRows);                                                                          \
+        if (deferred)                                                                                    \
+            hipLaunchKernelGGL(k_sort_deferred<V>, dim3(kDeferredGrid), dim3(kBlock), 0, s, nrows, inv_n, rp, col, \
+                               (const V *)val, rinv, cinv, rp_b, col_b, (V *)val_b, (const int32_t *)deferred);    \
+    }
     switch (val_bytes) {
     case 8: MXE_SORT_FEW(uint64_t) break;
     case 4: MXE_SORT_FEW(uint32_t) break;

@@ -1,7 +1,7 @@
 """GPU: permuted CSR and gradient shuffles at the edges of their kernels, bit for
 bit against the oracle: rows around the lengths where the ranking of a row's new
 columns changes (32 entries, 512, 1024) and groups of rows that fill a
-wavefront's stage exactly, overflow it or are empty; column counts of more than
+wavefront's stage exactly, overflow it or are empty, few rows and many; column counts of more than
 a million entries, with one column per bucket edge, heavy columns and fewer
 columns than a bucket."""
 import numpy as np
@@ -44,6 +44,25 @@ ROWS = {
     "all_columns": lambda: _rows(64, [64] * 50, 6),
     "two_columns": lambda: _rows(2, [2, 0, 1, 2, 2] * 30, 7),
 }
+
+
+def _many_rows(nrows):
+    """Enough rows for groups of long ones to be moved by a launch of their
+    own: in the middle, one row past the stage, and the last, partial group."""
+    rng = np.random.default_rng(nrows)
+    lens = rng.integers(0, 4, nrows)
+    lens[160:176] = 40
+    lens[176:192] = 32                                     # exactly the stage
+    lens[5000:5004] = [600, 1025, 512, 1]
+    lens[-3:] = 300
+    r = np.repeat(np.arange(nrows), lens)
+    c = rng.integers(0, 5000, len(r))
+    c = synth._dedupe(r, c, 5000, lambda idx: rng.integers(0, 5000, len(idx)))
+    return synth.from_entries(nrows, 5000, r, c, rng.uniform(-1, 1, len(r)))
+
+
+for _n in (131_071, 131_072, 131_075):
+    ROWS[f"many_{_n}"] = lambda n=_n: _many_rows(n)
 
 
 @pytest.mark.parametrize("mode", [mx.ROWS | mx.COLS, mx.COLS, mx.ROWS, mx.ROWS | mx.COLS | mx.GRADIENT])
