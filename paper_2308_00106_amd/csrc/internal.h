@@ -12,8 +12,9 @@ namespace mxe {
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_iota_i32(int32_t *p, int64_t n, hipStream_t s);
 
-// Exclusive scan of n int32 values (in may equal out). The running total
-// must stay below 2^31. Workspace: scan_ws_bytes(n).
+// Exclusive scan of n int32 values (in may equal out); the last is not read,
+// so the total's place behind a table of counts need not be set. The running
+// total must stay below 2^31. Workspace: scan_ws_bytes(n).
 size_t scan_ws_bytes(int64_t n);
 hipError_t launch_exclusive_scan(const int32_t *in, int32_t *out, int64_t n, void *ws,
                                  hipStream_t s);

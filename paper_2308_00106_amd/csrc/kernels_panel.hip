@@ -498,8 +498,7 @@ hipError_t launch_panel_build(const PanelGeom &g, const int32_t *rp, const int32
     int32_t *off = (int32_t *)ws;
     void *scan_ws = (char *)ws + (sizeof(int32_t) * (size_t)n + 255) / 256 * 256;
     hipLaunchKernelGGL(k_panel_chunks, dim3((unsigned)cdiv(g.chunks + 1, 256)), dim3(256), 0, s, g, rp, l.crow);
-    hipError_t e = launch_fill_i32(off + n - 1, 1, 0, s);
-    if (e != hipSuccess) return e;
+    hipError_t e;
     hipLaunchKernelGGL(k_panel_count, dim3(g.chunks), dim3(kPanelBlock), 0, s, g, rp, col,
                        (const int32_t *)l.crow, off);
     if ((e = launch_exclusive_scan(off, off, n, scan_ws, s)) != hipSuccess) return e;

@@ -350,8 +350,7 @@ hipError_t launch_slab_build(const SlabGeom &g, const int32_t *rp, const int32_t
                              int val_bytes, int32_t *off, uint32_t *idx_out, void *val_out, void *ws,
                              hipStream_t s) {
     const int64_t n = (int64_t)slab_offsets_count(g);
-    hipError_t e = launch_fill_i32(off, n, 0, s);
-    if (e != hipSuccess) return e;
+    hipError_t e;
     hipLaunchKernelGGL(k_slab_count, dim3(g.blocks), dim3(kSlabBlock), 0, s, g, rp, col, off);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_exclusive_scan(off, off, n, ws, s)) != hipSuccess) return e;
