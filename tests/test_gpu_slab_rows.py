@@ -126,3 +126,37 @@ def test_not_finite_x_stays_in_its_rows(ctx, k):
             bad = ~np.isfinite(Y.cpu().numpy())
             assert np.array_equal(bad.any(1), touched) and np.array_equal(bad.all(1), touched), (k, storage, hex(v))
         ctx.release(A)
+
+
+# rows of the layout's build: batches of 256 entries cut inside and between rows,
+# more than 64 rows (or empty rows) starting in one batch, rows of several batches
+BUILDS = {
+    "empty_runs": [5] + [0] * 200 + [3, 0, 1],
+    "all_single": [1],
+    "batch_sized": [256, 256, 0, 255, 1, 257],
+    "long_and_short": [1500] + [1] * 90 + [0] * 70 + [513, 2],
+    "last_rows_empty": [4] * 40 + [0] * 500,
+}
+
+
+@pytest.mark.parametrize("ncols,unit", [(8192, 1), (8193, 1), (40_001, 1), (500_000, 1), (40_001, 16)])   # 1, 2, 5, 62 and 1 slabs
+@pytest.mark.parametrize("name", list(BUILDS))
+def test_rows_of_the_layout(ctx, name, ncols, unit):
+    """Whole numbers, so that every row's sum is exact."""
+    for nrows in (1, 17, 4003):
+        rng = np.random.default_rng(nrows + ncols)
+        lens = np.resize(np.asarray(BUILDS[name], np.int64), nrows)
+        r = np.repeat(np.arange(nrows), lens)
+        c = rng.integers(0, ncols, len(r))
+        c = synth._dedupe(r, c, ncols, lambda idx: rng.integers(0, ncols, len(idx)))
+        A0 = synth.from_entries(nrows, ncols, r, c, rng.integers(-9, 10, len(r)).astype(np.float64))
+        x = rng.integers(-9, 10, ncols).astype(np.float64)
+        A = ctx.register(A0)
+        ctx.set_variant(A, 1, mx.variant(mx.VAR_SLAB, unit))
+        Y = torch.full((nrows,), float("nan"), dtype=torch.float64, device="cuda")
+        ctx.spmv(A, torch_vec(x, torch.float64), Y)
+        torch.cuda.synchronize()
+        rows = np.repeat(np.arange(nrows), np.diff(A0.row_ptr))
+        want = np.bincount(rows, A0.val * x[A0.col], nrows)
+        assert np.array_equal(Y.cpu().numpy(), want)
+        ctx.release(A)
