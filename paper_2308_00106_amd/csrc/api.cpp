@@ -570,7 +570,14 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
     }
     // stage 2: the candidates within 8% of the fastest (two to five of them)
     // again, interleaved over two rounds of 10 products each, so candidates a
-    // few percent apart are told apart
+    // few percent apart are told apart. The column panels have to win by 5% in
+    // FP64, where they write and read 16 bytes of products an entry: what they
+    // gain on back-to-back products of one matrix is lost between others (1.7M
+    // rows of 14: 137 us against the slabs' 142, three matrices in turn 148
+    // against 145). With 4-byte products they lead either way.
+    auto handicap = [&](int v) {
+        return (v & 0xf00) == MXE_VAR_PANEL && A.storage == MXE_F64 ? 1.05f : 1.0f;
+    };
     if (result == MXE_OK && !timed.empty()) {
         std::stable_sort(timed.begin(), timed.end());
         size_t top = 1;
@@ -581,7 +588,8 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
         for (int round = 0; round < 2 && result == MXE_OK; ++round)
             for (size_t i = 0; i < top && result == MXE_OK; ++i) {
                 float ms = 0;
-                if ((result = time_variant(timed[i].second, 10, &ms)) == MXE_OK) total[i] += ms;
+                if ((result = time_variant(timed[i].second, 10, &ms)) == MXE_OK)
+                    total[i] += ms * handicap(timed[i].second);
             }
         if (result == MXE_OK) {
             const size_t b = std::min_element(total.begin(), total.end()) - total.begin();
