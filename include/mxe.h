@@ -130,7 +130,7 @@ mxe_status mxe_register_matrix(mxe_ctx *ctx, int32_t nrows, int32_t ncols, int64
  * h[i+1] - h[i]; the parts [0, p] and [p+1, n) are each ordered by the
  * stream's keys (random order within each part) and riffled, the two parts
  * alternating and the longer part's remainder appended. Synchronizes
- * `stream` once per gradient shuffle (the pivot sizes the parts). */
+ * `stream` once (the pivots size the parts). */
 mxe_status mxe_permute(mxe_ctx *ctx, mxe_mat a, uint64_t seed, uint32_t mode,
                        void *stream, mxe_mat *out_b);
 
@@ -252,7 +252,7 @@ mxe_status mxe_scatter_y(mxe_ctx *ctx, mxe_mat b, int32_t k, const void *Yp, int
  * into column panels whose x fits the LDS and into chunks of consecutive
  * rows. One pass multiplies every entry with its x from LDS and streams the
  * products out (a workspace of one value per entry, taken for the call from
- * the stream-ordered pool; the call runs as a row-group product when there is
+ * the context's device memory; the call runs as a row-group product when there is
  * no room for it), a second sums them by row, so no x is gathered from
  * memory. MXE_ERR_UNSUPPORTED from mxe_set_variant when k > 1 or the layout
  * does not fit. A batch runs its items on slab layouts instead. */
@@ -265,7 +265,7 @@ mxe_status mxe_scatter_y(mxe_ctx *ctx, mxe_mat b, int32_t k, const void *Yp, int
  * table of `table_bytes` (8 .. 2^34, a multiple of 64), each XCD confined to
  * its own eighth of the table when per_xcd != 0 (as the column-slab product
  * confines it to a slab). *gathers_per_s = loads issued / kernel time (HIP
- * events on `stream`). Allocates the table from the stream-ordered pool;
+ * events on `stream`). Takes the table from the context's device memory;
  * synchronizes. A diagnostic: no result of the method depends on it. */
 mxe_status mxe_probe_gather(mxe_ctx *ctx, int64_t table_bytes, int64_t gathers, int32_t per_xcd,
                             void *stream, double *gathers_per_s);

@@ -5,7 +5,7 @@
 // The persistent batch kernel needs a little device memory besides its
 // inputs and outputs: the descriptor table of the batch's pieces, the per-XCD
 // queue entries and the queue counters. mxe_spmv_batch takes them from the
-// stream-ordered pool; here they live in `scratch`, a static device array of
+// context's device memory; here they live in `scratch`, a static device array of
 // fixed size. Every GPU holds its own copy of it until the process ends, at
 // its own address, which noalloc_init looks up once per device
 // (hipGetSymbolAddress) when a context is created on it. Host code only ever
