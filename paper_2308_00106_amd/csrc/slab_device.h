@@ -191,7 +191,12 @@ slab_block(const SlabGeom &g, int32_t block, int xcd, const int32_t *__restrict_
 #pragma unroll
                 for (int q = 0; q < KM; ++q) prod[q] = S::mul(aj, xv[j][q]);
                 bool tail;                                    // the last lane of each row
-                if constexpr (KM == 1) {
+                // every step up to two right-hand sides: their chunks hold rows of
+                // several entries, and finding the idle steps costs more than they
+                // do (k = 2, 800K skewed FP32 rows in their own order 41.7 us, so
+                // 38.9; 700K permuted rows of 8 38.5 and 37.3); not in the batch,
+                // where small groups leave more steps idle (391 us, so 396)
+                if constexpr (KM == 1 || (KM == 2 && IF == 0)) {
                     if constexpr (SR == 0) segmented_scan<true>(key, 0, prod);
                     else segmented_scan_op<true, S>(key, 0, prod);
                     const uint32_t nxt = __shfl_down(key, 1);
