@@ -160,18 +160,16 @@ static mxe_status ensure_bins(mxe_ctx *, Matrix &A, hipStream_t s) {
     mxe_status st = dev_alloc(A, &p, sizeof(int32_t) * ((size_t)A.nrows + 1), s);
     if (st) return st;
     A.bin_list = (int32_t *)p;
-    st = dev_alloc(A, &p, sizeof(int32_t) * (kNumBins + 2), s);
+    st = dev_alloc(A, &p, sizeof(int32_t) * (kNumBins + 1), s);
     if (st) return st;
     A.bin_off_dev = (int32_t *)p;
     Scratch ws;
     if ((st = ws.alloc(*A.pool, row_bins_ws_bytes(A.nrows), s))) return st;
     MXE_HIP(launch_row_bins(A.nrows, A.rp, A.bin_list, A.bin_off_dev, ws.p, s));
-    MXE_HIP(launch_row_max(A.nrows, A.rp, A.bin_off_dev + kNumBins + 1, s));
-    int32_t host[kNumBins + 2];
+    int32_t host[kNumBins + 1];
     MXE_HIP(hipMemcpyAsync(host, A.bin_off_dev, sizeof host, hipMemcpyDeviceToHost, s));
     if ((st = settle(A, s))) return st;
     std::memcpy(A.bin_off, host, sizeof A.bin_off);
-    A.max_row = host[kNumBins + 1];
     A.bins_ready = true;
     return MXE_OK;
 }
@@ -360,21 +358,26 @@ static mxe_status ensure_window(mxe_ctx *ctx, Matrix &A, Matrix::Slab &sl, hipSt
 
 // ---- column-panel layout (built once per matrix) -------------------------------------
 
-// Longest row of A; a permuted matrix has its parent's.
+// Longest row of A, taken from the registered matrix that A was permuted from,
+// once or several times: the same rows, and complete since its registration
+// returned. A's own row starts may still be on their way on the stream it was
+// permuted on, in memory that holds an earlier matrix's, and the panel layout's
+// LDS is sized by this number.
 static mxe_status ensure_max_row(Matrix &A, hipStream_t s) {
     if (A.max_row >= 0) return MXE_OK;
-    Matrix &R = A.parent ? *A.parent : A;
-    if (R.max_row < 0) {
+    Matrix *R = &A;
+    while (R->parent) R = R->parent.get();
+    if (R->max_row < 0) {
         Scratch m;
         mxe_status st = m.alloc(*A.pool, sizeof(int32_t), s);
         if (st) return st;
         int32_t v = 0;
-        MXE_HIP(launch_row_max(R.nrows, R.rp, (int32_t *)m.p, s));
+        MXE_HIP(launch_row_max(R->nrows, R->rp, (int32_t *)m.p, s));
         MXE_HIP(hipMemcpyAsync(&v, m.p, sizeof v, hipMemcpyDeviceToHost, s));
         MXE_HIP(hipStreamSynchronize(s));
-        R.max_row = v;
+        R->max_row = v;
     }
-    A.max_row = R.max_row;
+    A.max_row = R->max_row;
     return MXE_OK;
 }
 
@@ -999,7 +1002,7 @@ mxe_status mxe_matrix_info(mxe_ctx *ctx, mxe_mat m, mxe_matrix_desc *out) {
     DeviceGuard g(ctx->device);
     auto A = find_matrix(ctx, m);
     if (!A) return fail(MXE_ERR_NOT_FOUND, "unknown matrix handle");
-    mxe_status st = ensure_bins(ctx, *A, nullptr);
+    mxe_status st = ensure_max_row(*A, nullptr);
     if (st) return st;
     out->nrows = A->nrows;
     out->ncols = A->ncols;

@@ -57,7 +57,7 @@ struct Matrix {
     uint32_t mode = 0;
     uint64_t bytes = 0;                 // HBM held
     // lazily built
-    int32_t max_row = -1;
+    int32_t max_row = -1;               // longest row (ensure_max_row), -1: not known yet
     int32_t *bin_list = nullptr;
     int32_t *bin_off_dev = nullptr;
     int32_t bin_off[kNumBins + 1] = {};
