@@ -3,10 +3,13 @@
 // in turn, hipMallocAsync takes about 20 us a block and hipFreeAsync 60 to 100
 // (9 us where only one size is ever asked for), more than most kernels here.
 //
-// Blocks are rounded up to an eighth of a power of two and reused by size. A
-// block given back after work on the legacy stream is reused on that stream
-// without a wait, one given back on another stream behind an event recorded
-// there, an idle one anywhere. What lies unused is bounded by kPoolKeep bytes
+// Blocks are rounded up to an eighth of a power of two and reused by size, but
+// never so that one stream waits for another's work: a block given back is
+// reused on the stream of its last use, or anywhere once the event recorded
+// there has passed; without such a block the call takes a new one. (Taking the
+// newest block behind a wait, two streams that issued the same product in turn
+// ran one after the other for good.) Blocks last used on the legacy stream
+// carry no event and stay with it. What lies unused is bounded by kPoolKeep bytes
 // and goes back to the runtime past that, when an allocation fails, and with
 // the context. While a stream is captured its blocks come from the runtime, as
 // nodes of the graph, and so do those of the per-thread stream, whose handle
@@ -47,14 +50,7 @@ class DevicePool {
         if (by != by_size_.end())
             for (auto it = by->second.rbegin(); it != by->second.rend(); ++it) {
                 Free &f = **it;
-                if (f.kind == kLegacy && !legacy(s)) continue;
-                if (f.kind == kEvent && hipEventQuery(f.ev) != hipSuccess) {
-                    (void)hipGetLastError();                 // hipErrorNotReady
-                    if (hipStreamWaitEvent(s, f.ev, 0) != hipSuccess) {
-                        (void)hipGetLastError();
-                        continue;
-                    }
-                }
+                if (!free_on(f, s)) continue;
                 *p = f.p;
                 live_[f.p] = size;
                 kept_ -= size;
@@ -86,7 +82,7 @@ class DevicePool {
             (void)hipFreeAsync(p, s);
             return;
         }
-        Free f{p, it->second, kLegacy, nullptr};
+        Free f{p, it->second, kLegacy, nullptr, s};
         live_.erase(it);
         if (!legacy(s)) {
             f.kind = kEvent;
@@ -113,7 +109,7 @@ class DevicePool {
             (void)hipFreeAsync(p, nullptr);
             return;
         }
-        Free f{p, it->second, kIdle, nullptr};
+        Free f{p, it->second, kIdle, nullptr, nullptr};
         live_.erase(it);
         keep(f, nullptr);
     }
@@ -138,6 +134,7 @@ class DevicePool {
         size_t size;
         Kind kind;
         hipEvent_t ev;
+        hipStream_t s;                                       // kEvent: where it was recorded
     };
     using Node = std::list<Free>::iterator;
 
@@ -154,6 +151,17 @@ class DevicePool {
         size_t step = 256;
         while (step * 16 <= bytes) step *= 2;                // bytes in [8 step, 16 step)
         return (bytes + step - 1) / step * step;
+    }
+    // Whether s may use the block without waiting for another stream. The wait on
+    // its own stream costs that stream nothing; it is there for a stream that was
+    // made after the one of this handle was destroyed.
+    static bool free_on(const Free &f, hipStream_t s) {
+        if (f.kind == kIdle) return true;
+        if (f.kind == kLegacy) return legacy(s);
+        if ((f.s == s && hipStreamWaitEvent(s, f.ev, 0) == hipSuccess) || hipEventQuery(f.ev) == hipSuccess)
+            return true;
+        (void)hipGetLastError();                             // hipErrorNotReady
+        return false;
     }
     void keep(const Free &f, hipStream_t s) {
         free_.push_back(f);
