@@ -9,9 +9,11 @@
 // there has passed; without such a block the call takes a new one. (Taking the
 // newest block behind a wait, two streams that issued the same product in turn
 // ran one after the other for good.) Blocks last used on the legacy stream
-// carry no event and stay with it. What lies unused is bounded by kPoolKeep bytes
-// and goes back to the runtime past that, when an allocation fails, and with
-// the context. While a stream is captured its blocks come from the runtime, as
+// carry no event and stay with it. What lies unused is bounded (kPoolKeep) and goes
+// back to the runtime past that, when an allocation fails, and with the
+// context: the oldest blocks that are free by now go first, and where they are
+// not enough the block being given back, again without a stream waiting for
+// another. While a stream is captured its blocks come from the runtime, as
 // nodes of the graph, and so do those of the per-thread stream, whose handle
 // does not say which stream it is.
 #pragma once
@@ -32,12 +34,12 @@ constexpr size_t kPoolKeep = size_t(4) << 30;
 
 class DevicePool {
   public:
-    DevicePool() = default;
+    explicit DevicePool(size_t keep = kPoolKeep) : limit_(keep) {}
     DevicePool(const DevicePool &) = delete;
     DevicePool &operator=(const DevicePool &) = delete;
     // The owner has synchronized the device and made it current.
     ~DevicePool() {
-        for (auto &f : free_) give_back(f, nullptr);
+        drop_all(nullptr);
         for (hipEvent_t e : events_) (void)hipEventDestroy(e);
     }
 
@@ -53,11 +55,7 @@ class DevicePool {
                 if (!free_on(f, s)) continue;
                 *p = f.p;
                 live_[f.p] = size;
-                kept_ -= size;
-                if (f.ev) events_.push_back(f.ev);
-                const auto node = *it;
-                by->second.erase(std::next(it).base());
-                free_.erase(node);
+                forget(*it);
                 return hipSuccess;
             }
         hipError_t e = hipMallocAsync(p, size, s);
@@ -76,42 +74,18 @@ class DevicePool {
     // The block's last use was queued on s.
     void put(void *p, hipStream_t s) {
         std::lock_guard<std::mutex> lk(mu_);
-        auto it = live_.find(p);
-        if (it == live_.end() || !ordered(s)) {              // captured, or not the pool's
-            if (it != live_.end()) live_.erase(it);
-            (void)hipFreeAsync(p, s);
-            return;
-        }
-        Free f{p, it->second, kLegacy, nullptr, s};
-        live_.erase(it);
-        if (!legacy(s)) {
-            f.kind = kEvent;
-            if (!events_.empty()) {
-                f.ev = events_.back();
-                events_.pop_back();
-            } else if (hipEventCreateWithFlags(&f.ev, hipEventDisableTiming) != hipSuccess) {
-                f.ev = nullptr;
-            }
-            if (!f.ev || hipEventRecord(f.ev, s) != hipSuccess) {
-                if (f.ev) events_.push_back(f.ev);
-                (void)hipFreeAsync(p, s);
-                return;
-            }
-        }
-        keep(f, s);
+        Free f{p, forget_live(p), legacy(s) ? kLegacy : kEvent, nullptr, s};
+        const bool pooled = f.size > 0 && ordered(s);        // not in a capture
+        if (pooled && make_room_for(f.size, s) && record(f)) keep(f);
+        else if (!release(p, s) && pooled && (f.ev || record(f))) keep(f);
     }
 
     // No work on the block is queued any more.
     void put_idle(void *p) {
         std::lock_guard<std::mutex> lk(mu_);
-        auto it = live_.find(p);
-        if (it == live_.end()) {
-            (void)hipFreeAsync(p, nullptr);
-            return;
-        }
-        Free f{p, it->second, kIdle, nullptr, nullptr};
-        live_.erase(it);
-        keep(f, nullptr);
+        const Free f{p, forget_live(p), kIdle, nullptr, nullptr};
+        if (f.size > 0 && make_room_for(f.size, nullptr)) keep(f);
+        else if (!release(p, nullptr) && f.size > 0) keep(f);
     }
 
     // An event without timing, from those given back.
@@ -158,43 +132,76 @@ class DevicePool {
     static bool free_on(const Free &f, hipStream_t s) {
         if (f.kind == kIdle) return true;
         if (f.kind == kLegacy) return legacy(s);
-        if ((f.s == s && hipStreamWaitEvent(s, f.ev, 0) == hipSuccess) || hipEventQuery(f.ev) == hipSuccess)
-            return true;
+        if (f.s == s) {
+            if (hipStreamWaitEvent(s, f.ev, 0) == hipSuccess) return true;
+            (void)hipGetLastError();                         // the next launch is not to report it
+        }
+        if (hipEventQuery(f.ev) == hipSuccess) return true;
         (void)hipGetLastError();                             // hipErrorNotReady
         return false;
     }
-    void keep(const Free &f, hipStream_t s) {
+    // bytes of a block handed out, 0 for one that is not the pool's
+    size_t forget_live(void *p) {
+        auto it = live_.find(p);
+        if (it == live_.end()) return 0;
+        const size_t size = it->second;
+        live_.erase(it);
+        return size;
+    }
+    static bool release(void *p, hipStream_t s) {
+        if (hipFreeAsync(p, s) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    }
+    bool record(Free &f) {
+        if (f.kind != kEvent) return true;
+        if (!events_.empty()) {
+            f.ev = events_.back();
+            events_.pop_back();
+        } else if (hipEventCreateWithFlags(&f.ev, hipEventDisableTiming) != hipSuccess) {
+            f.ev = nullptr;
+        }
+        if (f.ev && hipEventRecord(f.ev, f.s) == hipSuccess) return true;
+        (void)hipGetLastError();
+        if (f.ev) events_.push_back(f.ev);
+        f.ev = nullptr;
+        return false;
+    }
+    // Frees the oldest blocks until `size` more bytes stay within the limit. A
+    // block of the legacy stream is freed there, any other on s if s may use it.
+    bool make_room_for(size_t size, hipStream_t s) {
+        if (size > limit_) return false;
+        for (Node it = free_.begin(); kept_ + size > limit_ && it != free_.end();) {
+            const Node at = it++;
+            const hipStream_t on = at->kind == kLegacy ? nullptr : s;
+            if (free_on(*at, on) && release(at->p, on)) forget(at);
+        }
+        return kept_ + size <= limit_;
+    }
+    void keep(const Free &f) {
         free_.push_back(f);
         by_size_[f.size].push_back(std::prev(free_.end()));
         kept_ += f.size;
-        // oldest first; on a stream ordered behind each block's last use
-        for (Node it = free_.begin(); kept_ > kPoolKeep && it != free_.end();) {
-            const Node at = it++;
-            if (at->kind == kLegacy && !legacy(s)) continue;
-            if (at->kind == kEvent && hipStreamWaitEvent(s, at->ev, 0) != hipSuccess) continue;
-            forget(at);
-            give_back(*at, s);
-            free_.erase(at);
-        }
     }
     void forget(Node at) {
-        auto &v = by_size_[at->size];
+        auto by = by_size_.find(at->size);
+        auto &v = by->second;
         for (size_t i = 0; i < v.size(); ++i)
             if (v[i] == at) {
                 v.erase(v.begin() + i);
                 break;
             }
+        if (v.empty()) by_size_.erase(by);
         kept_ -= at->size;
+        if (at->ev) events_.push_back(at->ev);
+        free_.erase(at);
     }
-    void give_back(Free &f, hipStream_t s) {
-        (void)hipFreeAsync(f.p, s);
-        if (f.ev) events_.push_back(f.ev);
-    }
+    // Every use of the blocks has ended.
     void drop_all(hipStream_t s) {
-        for (auto &f : free_) give_back(f, s);
-        free_.clear();
-        by_size_.clear();
-        kept_ = 0;
+        for (Node it = free_.begin(); it != free_.end();) {
+            const Node at = it++;
+            if (release(at->p, s)) forget(at);
+        }
     }
 
     std::mutex mu_;
@@ -202,7 +209,8 @@ class DevicePool {
     std::list<Free> free_;                                   // oldest first
     std::map<size_t, std::vector<Node>> by_size_;
     std::vector<hipEvent_t> events_;
-    size_t kept_ = 0;
+    const size_t limit_;
+    size_t kept_ = 0;                                        // bytes of free_
 };
 
 }  // namespace mxe

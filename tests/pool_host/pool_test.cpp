@@ -4,6 +4,8 @@
 
 #include <cstdio>
 #include <cstring>
+#include <utility>
+#include <vector>
 
 using mxe::DevicePool;
 
@@ -74,6 +76,110 @@ bool legacy_blocks_stay() {
     return true;
 }
 
+// What lies unused stays within the limit whatever stream gives blocks back,
+// and none waits for another: legacy blocks go on the legacy stream, blocks in
+// use elsewhere are left alone.
+bool limit_of_unused_blocks() {
+    DevicePool pool(4 * kMiB);
+    SimStream a, b;
+    std::vector<void *> taken(8);
+    for (auto &p : taken) CHECK(pool.get(&p, kMiB, nullptr) == hipSuccess);
+    work(sim::legacy);
+    for (int i = 0; i < 3; ++i) pool.put(taken[i], nullptr);
+    for (int i = 3; i < 8; ++i) pool.put(taken[i], &a);
+    CHECK(sim::held <= 4 * kMiB);
+    for (size_t i = 0; i < sim::freed_on.size(); ++i)
+        if (sim::freed_on[i].first == taken[0]) CHECK(sim::freed_on[i].second == &sim::legacy);
+    for (int i = 0; i < 6; ++i) {                      // more of another stream, a's not finished
+        work(a);
+        void *p;
+        CHECK(pool.get(&p, (i % 3 + 1) * kMiB, &b) == hipSuccess);
+        work(b);
+        pool.put(p, &b);
+        CHECK(sim::held <= 4 * kMiB);
+    }
+    CHECK(a.waited_for.empty() && b.waited_for.empty() && sim::legacy.waited_for.empty());
+    void *big;                                         // larger than the limit: not kept, nothing else dropped
+    const size_t before = sim::held;
+    CHECK(pool.get(&big, 16 * kMiB, &b) == hipSuccess);
+    pool.put(big, &b);
+    CHECK(sim::held == before);
+    return true;
+}
+
+// Blocks of the legacy stream that fill the limit make way for those of others.
+bool legacy_blocks_make_way() {
+    DevicePool pool(4 * kMiB);
+    SimStream a;
+    void *p[4];
+    for (auto &q : p) CHECK(pool.get(&q, kMiB, nullptr) == hipSuccess);
+    for (auto &q : p) pool.put(q, nullptr);
+    void *first = call(pool, a, kMiB);
+    CHECK(call(pool, a, kMiB) == first && sim::held == 4 * kMiB);
+    CHECK(sim::freed_on.size() == 1 && sim::freed_on[0] == std::make_pair(p[0], &sim::legacy));
+    return true;
+}
+
+// The limit holds for blocks given back idle too, and where every older block
+// is still in use.
+bool limit_where_all_are_in_use() {
+    DevicePool pool(2 * kMiB);
+    SimStream a, b;
+    void *p[4];
+    for (auto &q : p) CHECK(pool.get(&q, kMiB, &a) == hipSuccess);
+    work(a);
+    pool.put(p[0], &a);
+    pool.put(p[1], &a);
+    CHECK(sim::held == 4 * kMiB);
+    work(b);
+    pool.put(p[2], &b);
+    CHECK(sim::held == 3 * kMiB);
+    CHECK(sim::freed_on.back() == std::make_pair(p[2], &b));
+    pool.put_idle(p[3]);
+    CHECK(sim::held == 2 * kMiB && b.waited_for.empty() && sim::legacy.waited_for.empty());
+    return true;
+}
+
+// A failing runtime call leaves no error behind and loses no block.
+bool failing_calls() {
+    DevicePool pool(2 * kMiB);
+    SimStream a;
+    void *p[3];
+    for (auto &q : p) CHECK(pool.get(&q, kMiB, &a) == hipSuccess);
+    pool.put(p[0], &a);
+    pool.put(p[1], &a);
+    finish(a);
+    sim::fail_free = true;
+    pool.put(p[2], &a);
+    CHECK(sim::last == hipSuccess);
+    sim::fail_free = false;
+    sim::fail_wait = true;
+    void *q = nullptr;
+    CHECK(pool.get(&q, kMiB, &a) == hipSuccess && sim::last == hipSuccess && sim::mallocs == 3);
+    sim::fail_wait = false;
+    pool.put(q, &a);
+    work(a);                                           // at the limit, and the runtime refuses the block
+    sim::fail_free = true;
+    CHECK(pool.get(&q, 2 * kMiB, &a) == hipSuccess);
+    pool.put(q, &a);
+    sim::fail_free = false;
+    CHECK(call(pool, a, 2 * kMiB) == q && sim::last == hipSuccess);
+    return true;
+}
+
+// Everything goes back with the pool, events too.
+bool all_returned() {
+    {
+        DevicePool pool;
+        SimStream a;
+        for (size_t i = 1; i < 6; ++i) call(pool, a, i * kMiB);
+        call(pool, sim::legacy, kMiB);
+        CHECK(sim::held > 0);
+    }
+    CHECK(sim::held == 0 && sim::events == 0);
+    return true;
+}
+
 const struct {
     const char *name;
     bool (*run)();
@@ -81,6 +187,11 @@ const struct {
     {"streams_in_turn", streams_in_turn},
     {"finished_blocks_go_anywhere", finished_blocks_go_anywhere},
     {"legacy_blocks_stay", legacy_blocks_stay},
+    {"limit_of_unused_blocks", limit_of_unused_blocks},
+    {"legacy_blocks_make_way", legacy_blocks_make_way},
+    {"limit_where_all_are_in_use", limit_where_all_are_in_use},
+    {"failing_calls", failing_calls},
+    {"all_returned", all_returned},
 };
 
 }  // namespace
