@@ -57,11 +57,7 @@ struct Scratch {
         s = stream;
         pool = &from;
         hipError_t e = from.get(&p, std::max<size_t>(bytes, 256), stream);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();             // a launch that does without is not to report it
-            return hip_fail(e, "hipMallocAsync(workspace)");
-        }
-        return MXE_OK;
+        return e == hipSuccess ? MXE_OK : hip_fail(e, "hipMallocAsync(workspace)");
     }
 };
 
@@ -766,8 +762,7 @@ mxe_status mxe_create(int32_t device, uint64_t hbm_budget_bytes, mxe_ctx **out) 
     if (st) return st;
     double *results = nullptr;
     MXE_HIP(hipHostMalloc((void **)&results, sizeof(double) * kResultDoubles, hipHostMallocDefault));
-    auto *ctx = new mxe_ctx();
-    ctx->device = device;
+    auto *ctx = new mxe_ctx(device);
     ctx->results = results;
     ctx->budget = hbm_budget_bytes;
     ctx->cu_count = prop.multiProcessorCount;

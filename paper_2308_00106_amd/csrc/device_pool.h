@@ -13,7 +13,8 @@
 // back to the runtime past that, when an allocation fails, and with the
 // context: the oldest blocks that are free by now go first, and where they are
 // not enough the block being given back, again without a stream waiting for
-// another. While a stream is captured its blocks come from the runtime, as
+// another. An allocation that fails takes back what lies unused in every
+// context of the device. While a stream is captured its blocks come from the runtime, as
 // nodes of the graph, and so do those of the per-thread stream, whose handle
 // does not say which stream it is.
 #pragma once
@@ -34,40 +35,43 @@ constexpr size_t kPoolKeep = size_t(4) << 30;
 
 class DevicePool {
   public:
-    explicit DevicePool(size_t keep = kPoolKeep) : limit_(keep) {}
+    explicit DevicePool(int device, size_t keep = kPoolKeep) : device_(device), limit_(keep) {
+        Registry &r = registry();
+        std::lock_guard<std::mutex> lk(r.mu);
+        r.pools.push_back(this);
+    }
     DevicePool(const DevicePool &) = delete;
     DevicePool &operator=(const DevicePool &) = delete;
     // The owner has synchronized the device and made it current.
     ~DevicePool() {
-        drop_all(nullptr);
+        {
+            Registry &r = registry();
+            std::lock_guard<std::mutex> lk(r.mu);
+            r.pools.remove(this);
+        }
+        drop(nullptr, true);
         for (hipEvent_t e : events_) (void)hipEventDestroy(e);
     }
 
     hipError_t get(void **p, size_t bytes, hipStream_t s) {
         *p = nullptr;
-        if (!ordered(s)) return hipMallocAsync(p, bytes, s);
-        const size_t size = rounded(bytes);
-        std::lock_guard<std::mutex> lk(mu_);
-        auto by = by_size_.find(size);
-        if (by != by_size_.end())
-            for (auto it = by->second.rbegin(); it != by->second.rend(); ++it) {
-                Free &f = **it;
-                if (!free_on(f, s)) continue;
-                *p = f.p;
-                live_[f.p] = size;
-                forget(*it);
-                return hipSuccess;
-            }
+        const bool pooled = ordered(s);
+        const size_t size = pooled ? rounded(bytes) : bytes;
+        if (pooled && take(p, size, s)) return hipSuccess;
         hipError_t e = hipMallocAsync(p, size, s);
-        if (e != hipSuccess && !free_.empty()) {             // make room
+        // a capture neither waits nor frees
+        if (e == hipErrorOutOfMemory && (pooled || s == hipStreamPerThread) && !capturing(s)) {
             (void)hipGetLastError();
-            (void)hipDeviceSynchronize();
-            drop_all(s);
-            (void)hipStreamSynchronize(s);
+            make_room(s);
             e = hipMallocAsync(p, size, s);
         }
-        if (e == hipSuccess) live_[*p] = size;
-        else *p = nullptr;
+        if (e != hipSuccess) {
+            (void)hipGetLastError();                         // the next launch is not to report it
+            *p = nullptr;
+        } else if (pooled) {
+            std::lock_guard<std::mutex> lk(mu_);
+            live_[*p] = size;
+        }
         return e;
     }
 
@@ -111,15 +115,27 @@ class DevicePool {
         hipStream_t s;                                       // kEvent: where it was recorded
     };
     using Node = std::list<Free>::iterator;
+    // every context's pool; never destroyed, contexts may outlive static objects
+    struct Registry {
+        std::mutex mu;                                       // taken before any pool's
+        std::list<DevicePool *> pools;
+    };
+    static Registry &registry() {
+        static Registry *r = new Registry;
+        return *r;
+    }
 
     static bool legacy(hipStream_t s) { return s == nullptr || s == hipStreamLegacy; }
     static bool ordered(hipStream_t s) {
         if (legacy(s)) return true;
-        if (s == hipStreamPerThread) return false;
+        return s != hipStreamPerThread && !capturing(s);
+    }
+    static bool capturing(hipStream_t s) {
+        if (legacy(s)) return false;                         // it cannot be captured
         hipStreamCaptureStatus cs;
-        if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs == hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
         (void)hipGetLastError();
-        return false;
+        return true;
     }
     static size_t rounded(size_t bytes) {
         size_t step = 256;
@@ -139,6 +155,44 @@ class DevicePool {
         if (hipEventQuery(f.ev) == hipSuccess) return true;
         (void)hipGetLastError();                             // hipErrorNotReady
         return false;
+    }
+    // A block of this size that s may use without waiting, the newest.
+    bool take(void **p, size_t size, hipStream_t s) {
+        std::lock_guard<std::mutex> lk(mu_);
+        auto by = by_size_.find(size);
+        if (by == by_size_.end()) return false;
+        for (auto it = by->second.rbegin(); it != by->second.rend(); ++it) {
+            if (!free_on(**it, s)) continue;
+            *p = (*it)->p;
+            live_[*p] = size;
+            forget(*it);
+            return true;
+        }
+        return false;
+    }
+    // Gives the device back what lies unused in its pools, for an allocation on s,
+    // and then what the runtime itself holds unused. Waits for the blocks' last
+    // uses, not for the device.
+    void make_room(hipStream_t s) {
+        Registry &r = registry();
+        {
+            std::lock_guard<std::mutex> lk(r.mu);
+            for (DevicePool *q : r.pools)
+                if (q->device_ == device_) q->drop(s, false);
+        }
+        hipMemPool_t runtime;
+        if (hipStreamSynchronize(nullptr) != hipSuccess || hipStreamSynchronize(s) != hipSuccess ||
+            hipDeviceGetDefaultMemPool(&runtime, device_) != hipSuccess || hipMemPoolTrimTo(runtime, 0) != hipSuccess)
+            (void)hipGetLastError();
+    }
+    // Every unused block; ended: no use of one is still running.
+    void drop(hipStream_t s, bool ended) {
+        std::lock_guard<std::mutex> lk(mu_);
+        for (Node it = free_.begin(); it != free_.end();) {
+            const Node at = it++;
+            if (!ended && at->kind == kEvent && hipEventSynchronize(at->ev) != hipSuccess) (void)hipGetLastError();
+            else if (release(at->p, at->kind == kLegacy ? nullptr : s)) forget(at);
+        }
     }
     // bytes of a block handed out, 0 for one that is not the pool's
     size_t forget_live(void *p) {
@@ -196,19 +250,13 @@ class DevicePool {
         if (at->ev) events_.push_back(at->ev);
         free_.erase(at);
     }
-    // Every use of the blocks has ended.
-    void drop_all(hipStream_t s) {
-        for (Node it = free_.begin(); it != free_.end();) {
-            const Node at = it++;
-            if (release(at->p, s)) forget(at);
-        }
-    }
 
     std::mutex mu_;
     std::unordered_map<void *, size_t> live_;                // blocks handed out
     std::list<Free> free_;                                   // oldest first
     std::map<size_t, std::vector<Node>> by_size_;
     std::vector<hipEvent_t> events_;
+    const int device_;
     const size_t limit_;
     size_t kept_ = 0;                                        // bytes of free_
 };

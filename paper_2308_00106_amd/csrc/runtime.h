@@ -168,7 +168,8 @@ struct Server;
 constexpr size_t kResultDoubles = 8192;
 
 struct mxe_ctx {
-    int device = 0;
+    explicit mxe_ctx(int dev) : device(dev), pool(dev) {}
+    const int device;
     mxe::DevicePool pool;               // outlives the matrices below
     uint64_t budget = 0;                // 0: no cap
     std::atomic<uint64_t> used{0};      // resident bytes

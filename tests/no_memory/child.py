@@ -1,0 +1,66 @@
+"""python child.py SHIM NAME: one case of the library without device memory to
+give, in a process whose hipMallocAsync goes through the shim. Prints 'ok'."""
+import ctypes
+import os
+import sys
+
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)     # before the HIP runtime
+shim.shim_fail.argtypes = [ctypes.c_size_t, ctypes.c_int]
+sys.path[:0] = [os.path.dirname(os.path.dirname(os.path.dirname(os.path.abspath(__file__)))),
+                os.path.dirname(os.path.dirname(os.path.abspath(__file__)))]
+
+import numpy as np                                           # noqa: E402
+import torch                                                 # noqa: E402
+
+import synth                                                 # noqa: E402
+from gpu_common import TOL, spmv_error, torch_vec            # noqa: E402
+from paper_2308_00106_amd import mxe as mx                   # noqa: E402
+
+mx.load_library()
+runtime = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+assert shim.shim_runtime(runtime.encode()), runtime
+MiB = 1 << 20
+
+
+def product(ctx, B, A0, seed, flags=mx.SPACE_ORIGINAL, dt=torch.float64):
+    x = synth.vector(A0.ncols, seed)
+    y = torch.full((A0.nrows,), float("nan"), dtype=dt, device="cuda")
+    ctx.spmv(B, torch_vec(x, dt), y, flags=flags)
+    torch.cuda.synchronize()
+    return x, y
+
+
+def room_from_another_context():
+    """A failed allocation gets back what another context holds unused, and the
+    call goes on as if nothing had happened."""
+    A0 = synth.skewed_clustered(300_000, 2.0, 1.0, 64, 500.0, 1)
+    with mx.Context(0) as one, mx.Context(0) as two:
+        A = one.register(A0)
+        B = one.permute(A, 2)
+        one.set_variant(B, 1, mx.variant(mx.VAR_GROUP, 8))
+        product(one, B, A0, 3)
+        one.release(B)                                       # about 60 MB unused
+        free0 = torch.cuda.mem_get_info()[0]
+        shim.shim_fail(4 * MiB, 1)
+        A2 = two.register(A0)
+        assert shim.shim_failed() == 1
+        assert torch.cuda.mem_get_info()[0] > free0 - 16 * MiB
+        B2 = two.permute(A2, 2)
+        two.set_variant(B2, 1, mx.variant(mx.VAR_GROUP, 8))
+        x, y = product(two, B2, A0, 4)
+        assert spmv_error(A0, x, y.cpu().numpy(), "f64") <= TOL["f64"]
+        shim.shim_fail(4 * MiB, -1)                          # no memory at all: reported, nothing lost
+        try:
+            two.permute(A2, 5)
+            raise AssertionError("a permutation without memory")
+        except mx.MxeError as e:
+            assert e.status == mx.ERR_OUT_OF_MEMORY
+        shim.shim_fail(0, 0)
+        x, y = product(two, B2, A0, 6)
+        assert spmv_error(A0, x, y.cpu().numpy(), "f64") <= TOL["f64"]
+        two.release(two.permute(A2, 5))
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[2]]()
+    print("ok", flush=True)

@@ -36,7 +36,7 @@ void *call(DevicePool &pool, SimStream &s, size_t bytes) {
 // Two streams that issue calls of the same size in turn, none of them finished:
 // neither waits for the other, and after the first two no memory is taken.
 bool streams_in_turn() {
-    DevicePool pool;
+    DevicePool pool(0);
     SimStream a, b;
     void *pa = call(pool, a, kMiB), *pb = call(pool, b, kMiB);
     CHECK(pa && pb && pa != pb);
@@ -52,7 +52,7 @@ bool streams_in_turn() {
 // A block whose last use has finished goes to any stream, behind a newer one
 // that is still in use; so does an idle one.
 bool finished_blocks_go_anywhere() {
-    DevicePool pool;
+    DevicePool pool(0);
     SimStream a, b, c;
     void *pa = call(pool, a, kMiB), *pb = call(pool, b, kMiB);
     CHECK(pa != pb);
@@ -68,7 +68,7 @@ bool finished_blocks_go_anywhere() {
 
 // What was last used on the legacy stream stays with it.
 bool legacy_blocks_stay() {
-    DevicePool pool;
+    DevicePool pool(0);
     SimStream a;
     void *p = call(pool, sim::legacy, kMiB);
     CHECK(call(pool, a, kMiB) != p);
@@ -80,7 +80,7 @@ bool legacy_blocks_stay() {
 // and none waits for another: legacy blocks go on the legacy stream, blocks in
 // use elsewhere are left alone.
 bool limit_of_unused_blocks() {
-    DevicePool pool(4 * kMiB);
+    DevicePool pool(0, 4 * kMiB);
     SimStream a, b;
     std::vector<void *> taken(8);
     for (auto &p : taken) CHECK(pool.get(&p, kMiB, nullptr) == hipSuccess);
@@ -109,7 +109,7 @@ bool limit_of_unused_blocks() {
 
 // Blocks of the legacy stream that fill the limit make way for those of others.
 bool legacy_blocks_make_way() {
-    DevicePool pool(4 * kMiB);
+    DevicePool pool(0, 4 * kMiB);
     SimStream a;
     void *p[4];
     for (auto &q : p) CHECK(pool.get(&q, kMiB, nullptr) == hipSuccess);
@@ -123,7 +123,7 @@ bool legacy_blocks_make_way() {
 // The limit holds for blocks given back idle too, and where every older block
 // is still in use.
 bool limit_where_all_are_in_use() {
-    DevicePool pool(2 * kMiB);
+    DevicePool pool(0, 2 * kMiB);
     SimStream a, b;
     void *p[4];
     for (auto &q : p) CHECK(pool.get(&q, kMiB, &a) == hipSuccess);
@@ -142,7 +142,7 @@ bool limit_where_all_are_in_use() {
 
 // A failing runtime call leaves no error behind and loses no block.
 bool failing_calls() {
-    DevicePool pool(2 * kMiB);
+    DevicePool pool(0, 2 * kMiB);
     SimStream a;
     void *p[3];
     for (auto &q : p) CHECK(pool.get(&q, kMiB, &a) == hipSuccess);
@@ -167,10 +167,47 @@ bool failing_calls() {
     return true;
 }
 
+// An allocation that fails gets back what lies unused in every context of its
+// device, in use or not, but not another device's, and leaves no error behind.
+bool room_from_other_contexts() {
+    DevicePool one(0), two(0), other(1);
+    SimStream a, b;
+    call(one, a, 4 * kMiB);
+    call(two, b, 3 * kMiB);
+    call(two, sim::legacy, 2 * kMiB);
+    call(other, a, kMiB);
+    sim::capacity = 10 * kMiB;
+    void *p = nullptr;
+    CHECK(one.get(&p, 8 * kMiB, &a) == hipSuccess && p);
+    CHECK(sim::held == 9 * kMiB && sim::device_syncs == 0 && sim::trims == 1);
+    CHECK(sim::freed_on.size() == 3 && sim::freed_on.back().second == &sim::legacy);
+    void *q = p;
+    CHECK(two.get(&q, 8 * kMiB, &b) == hipErrorOutOfMemory && !q && sim::last == hipSuccess);
+    one.put(p, &a);
+    CHECK(two.get(&q, 8 * kMiB, hipStreamPerThread) == hipSuccess);        // not a pooled stream
+    CHECK(sim::held == 9 * kMiB);
+    two.put(q, hipStreamPerThread);
+    CHECK(sim::held == kMiB);
+    return true;
+}
+
+// A call in a capture takes its block from the runtime and asks for no room.
+bool no_room_in_a_capture() {
+    DevicePool pool(0);
+    SimStream a, b;
+    call(pool, a, 4 * kMiB);
+    sim::capacity = 4 * kMiB;
+    b.capturing = true;
+    void *p;
+    CHECK(pool.get(&p, 4 * kMiB, &b) == hipErrorOutOfMemory && sim::last == hipSuccess);
+    CHECK(sim::frees == 0 && sim::event_waits == 0 && sim::trims == 0);
+    return true;
+}
+
 // Everything goes back with the pool, events too.
 bool all_returned() {
     {
-        DevicePool pool;
+        DevicePool pool(0);
         SimStream a;
         for (size_t i = 1; i < 6; ++i) call(pool, a, i * kMiB);
         call(pool, sim::legacy, kMiB);
@@ -191,6 +228,8 @@ const struct {
     {"legacy_blocks_make_way", legacy_blocks_make_way},
     {"limit_where_all_are_in_use", limit_where_all_are_in_use},
     {"failing_calls", failing_calls},
+    {"room_from_other_contexts", room_from_other_contexts},
+    {"no_room_in_a_capture", no_room_in_a_capture},
     {"all_returned", all_returned},
 };
 
