@@ -73,7 +73,7 @@ Matrix::Use *use_of(Matrix &m, hipStream_t s) {
 mxe_status dev_alloc(Matrix &m, void **p, size_t bytes, hipStream_t s) {
     Matrix::Use *u = use_of(m, s);
     if (!u) return fail(MXE_ERR_DEVICE, "no event for a matrix");
-    hipError_t e = m.pool->get(p, std::max<size_t>(bytes, 256), s);
+    hipError_t e = m.pool->get(p, std::max<size_t>(bytes, 256), s, m.counted);
     if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(matrix)");
     u->late = true;
     m.allocs.push_back(*p);
@@ -123,6 +123,7 @@ std::shared_ptr<Matrix> make_matrix(mxe_ctx *ctx) {
         delete m;
     });
     A->pool = &ctx->pool;
+    A->counted = ctx->budget > 0;
     return A;
 }
 

@@ -3,8 +3,8 @@
 // in turn, hipMallocAsync takes about 20 us a block and hipFreeAsync 60 to 100
 // (9 us where only one size is ever asked for), more than most kernels here.
 //
-// Blocks are rounded up to an eighth of a power of two and reused by size, but
-// never so that one stream waits for another's work: a block given back is
+// Blocks are rounded up to an eighth of a power of two, where a budget counts
+// them or memory is short to whole pages only, and reused by size, but never so that one stream waits for another's work: a block given back is
 // reused on the stream of its last use, or anywhere once the event recorded
 // there has passed; without such a block the call takes a new one. (Taking the
 // newest block behind a wait, two streams that issued the same product in turn
@@ -53,10 +53,11 @@ class DevicePool {
         for (hipEvent_t e : events_) (void)hipEventDestroy(e);
     }
 
-    hipError_t get(void **p, size_t bytes, hipStream_t s) {
+    // counted: the bytes are held against a budget.
+    hipError_t get(void **p, size_t bytes, hipStream_t s, bool counted = false) {
         *p = nullptr;
         const bool pooled = ordered(s);
-        const size_t size = pooled ? rounded(bytes) : bytes;
+        size_t size = !pooled ? bytes : counted ? paged(bytes) : rounded(bytes);
         if (pooled && take(p, size, s)) return hipSuccess;
         hipError_t e = hipMallocAsync(p, size, s);
         // a capture neither waits nor frees
@@ -64,6 +65,11 @@ class DevicePool {
             (void)hipGetLastError();
             make_room(s);
             e = hipMallocAsync(p, size, s);
+            if (e == hipErrorOutOfMemory && pooled && size > paged(bytes)) {
+                (void)hipGetLastError();
+                size = paged(bytes);
+                e = hipMallocAsync(p, size, s);
+            }
         }
         if (e != hipSuccess) {
             (void)hipGetLastError();                         // the next launch is not to report it
@@ -136,6 +142,10 @@ class DevicePool {
         if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
         (void)hipGetLastError();
         return true;
+    }
+    static size_t paged(size_t bytes) {                      // small blocks to 256 bytes
+        const size_t step = bytes < 32768 ? 256 : 4096;
+        return (bytes + step - 1) / step * step;
     }
     static size_t rounded(size_t bytes) {
         size_t step = 256;

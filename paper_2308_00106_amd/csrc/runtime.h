@@ -86,6 +86,7 @@ struct Matrix {
     Panel panel;
     std::atomic<int> busy{0};           // serving requests queued or running
     DevicePool *pool = nullptr;         // its context's
+    bool counted = false;               // the context has a budget
     std::vector<void *> allocs;         // device allocations to give back
     // per stream, an event recorded after the last work queued there on this
     // matrix: freeing waits for these, never for the whole device. late: work

@@ -204,6 +204,32 @@ bool no_room_in_a_capture() {
     return true;
 }
 
+// Memory of a budget takes no more than its pages, and so does any block where
+// the device has no room for the rounded size.
+bool counted_blocks_fit() {
+    for (size_t bytes : {size_t(1), size_t(255), size_t(257), size_t(5000), size_t(100'001), 9 * kMiB + 1, 1000 * kMiB + 77}) {
+        DevicePool pool(0);
+        SimStream a;
+        void *p, *q;
+        CHECK(pool.get(&p, bytes, &a, true) == hipSuccess);
+        CHECK(sim::held >= bytes && sim::held - bytes < (bytes < 32768 ? 256 : 4096));
+        pool.put(p, &a);
+        CHECK(pool.get(&q, bytes, &a, true) == hipSuccess && p == q);
+        pool.put(q, &a);
+    }
+    CHECK(sim::held == 0);
+    DevicePool pool(0);
+    SimStream a;
+    sim::capacity = 9 * kMiB + 4096;
+    void *p = nullptr;
+    CHECK(pool.get(&p, 9 * kMiB + 1, &a) == hipSuccess && sim::held == 9 * kMiB + 4096);
+    pool.put(p, &a);
+    finish(a);
+    CHECK(pool.get(&p, 9 * kMiB + 1, &a) == hipSuccess && sim::last == hipSuccess);
+    pool.put(p, &a);
+    return true;
+}
+
 // Everything goes back with the pool, events too.
 bool all_returned() {
     {
@@ -230,6 +256,7 @@ const struct {
     {"failing_calls", failing_calls},
     {"room_from_other_contexts", room_from_other_contexts},
     {"no_room_in_a_capture", no_room_in_a_capture},
+    {"counted_blocks_fit", counted_blocks_fit},
     {"all_returned", all_returned},
 };
 
