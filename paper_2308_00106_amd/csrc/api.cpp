@@ -511,10 +511,14 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
     }
     // last, so that no other candidate's layout misses its place in the budget
     if (kc == 1) {
-        if ((st = ensure_max_row(A, s))) return st;
+        if ((st = ensure_max_row(A, s)) && st != MXE_ERR_OUT_OF_MEMORY) return st;
         PanelGeom g;
-        if (matrix_panel_geometry(ctx, A, &g)) cands.push_back(MXE_VARIANT(MXE_VAR_PANEL, 0));
+        if (!st && matrix_panel_geometry(ctx, A, &g)) cands.push_back(MXE_VARIANT(MXE_VAR_PANEL, 0));
     }
+    // nor does a lack of memory for its layout or its products fail the tuning
+    auto no_room = [](int v, mxe_status e) {
+        return e == MXE_ERR_OUT_OF_MEMORY && (v & 0xf00) == MXE_VAR_PANEL;
+    };
     std::set<std::tuple<int, int, int>> had;          // layouts other work may be using
     for (const auto &kv : A.slabs) had.insert(kv.first);
     const bool had_panel = A.panel.ready;
@@ -552,7 +556,7 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
         float ms = 0;
         if ((result = time_variant(v, reps, &ms))) {
             // a layout that does not fit the matrix or the HBM budget is not a candidate
-            if (result == MXE_ERR_UNSUPPORTED || result == MXE_ERR_BUDGET) {
+            if (result == MXE_ERR_UNSUPPORTED || result == MXE_ERR_BUDGET || no_room(v, result)) {
                 result = MXE_OK;
                 continue;
             }
@@ -588,8 +592,12 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
         for (int round = 0; round < 2 && result == MXE_OK; ++round)
             for (size_t i = 0; i < top && result == MXE_OK; ++i) {
                 float ms = 0;
-                if ((result = time_variant(timed[i].second, 10, &ms)) == MXE_OK)
+                if ((result = time_variant(timed[i].second, 10, &ms)) == MXE_OK) {
                     total[i] += ms * handicap(timed[i].second);
+                } else if (no_room(timed[i].second, result)) {
+                    total[i] = std::numeric_limits<float>::infinity();
+                    result = MXE_OK;
+                }
             }
         if (result == MXE_OK) {
             const size_t b = std::min_element(total.begin(), total.end()) - total.begin();

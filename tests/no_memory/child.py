@@ -61,6 +61,32 @@ def room_from_another_context():
         two.release(two.permute(A2, 5))
 
 
+def tuning_without_room_for_the_panels():
+    """The tuner tries the column panels last; without room for their layout, or
+    for their products alone, it chooses among the others."""
+    A0 = synth.skewed_clustered(300_000, 2.0, 1.0, 64, 500.0, 1)
+    # budget: exact sizes. FP64: no room for the layout's values; BF16: for the
+    # workspace of FP32 products, larger than every other variant's largest block
+    for storage, largest in (("f64", 8 * A0.nnz), ("bf16", 4 * A0.nnz)):
+        dt = torch.float64 if storage == "f64" else torch.float32
+        with mx.Context(0, budget_bytes=1 << 34) as ctx:
+            A = ctx.register(A0, storage)
+            B = ctx.permute(A, 2)
+            shim.shim_fail(largest + 8192, -1)
+            x, y = product(ctx, B, A0, 3, dt=dt)
+            assert shim.shim_failed() > 0
+            assert spmv_error(A0, x, y.cpu().numpy().astype(np.float64), storage) <= TOL[storage]
+            assert ctx.tune(B, 1) & 0xf00 != mx.VAR_PANEL
+            held = ctx.matrix_info(B).device_bytes
+            shim.shim_fail(0, 0)
+            ctx.set_variant(B, 1, mx.variant(mx.VAR_PANEL))  # it was the memory alone
+            x, y = product(ctx, B, A0, 4, dt=dt)
+            assert spmv_error(A0, x, y.cpu().numpy().astype(np.float64), storage) <= TOL[storage]
+            assert ctx.matrix_info(B).device_bytes > held
+            ctx.release(B)
+            ctx.release(A)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]]()
     print("ok", flush=True)
