@@ -252,9 +252,9 @@ mxe_status mxe_scatter_y(mxe_ctx *ctx, mxe_mat b, int32_t k, const void *Yp, int
  * into column panels whose x fits the LDS and into chunks of consecutive
  * rows. One pass multiplies every entry with its x from LDS and streams the
  * products out (a workspace of one value per entry, taken for the call from
- * the context's device memory; the call runs as a row-group product when there is
- * no room for it), a second sums them by row, so no x is gathered from
- * memory. MXE_ERR_UNSUPPORTED from mxe_set_variant when k > 1 or the layout
+ * the context's device memory), a second sums them by row, so no x is gathered
+ * from memory. Where there is no room for the workspace one slower pass gathers
+ * x and returns the same bits. MXE_ERR_UNSUPPORTED from mxe_set_variant when k > 1 or the layout
  * does not fit. A batch runs its items on slab layouts instead. */
 #define MXE_VAR_PANEL   0x700
 #define MXE_VARIANT(family, lanes) ((family) | (lanes))

@@ -53,10 +53,10 @@ struct Scratch {
     ~Scratch() {
         if (p) pool->put(p, s);
     }
-    mxe_status alloc(DevicePool &from, size_t bytes, hipStream_t stream) {
+    mxe_status alloc(DevicePool &from, size_t bytes, hipStream_t stream, bool optional = false) {
         s = stream;
         pool = &from;
-        hipError_t e = from.get(&p, std::max<size_t>(bytes, 256), stream);
+        hipError_t e = from.get(&p, std::max<size_t>(bytes, 256), stream, false, optional);
         return e == hipSuccess ? MXE_OK : hip_fail(e, "hipMallocAsync(workspace)");
     }
 };
@@ -657,15 +657,13 @@ static mxe_status spmv_core(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, i
                                (char *)Y + (size_t)c0 * eb, ldy, s, &a)))
             return st;
         Scratch cw;                             // this launch's workspace (MERGE, COO, PANEL)
-        int variant = r.variant;
-        if (const size_t cb = carry_bytes(A, variant, kc)) {
-            st = cw.alloc(ctx->pool, cb, s);
-            if (st && (variant & 0xf00) != MXE_VAR_PANEL) return st;
-            // no room for the products: the row kernel needs none
-            if (st) variant = MXE_VARIANT(MXE_VAR_GROUP, r.group_lanes);
+        if (const size_t cb = carry_bytes(A, r.variant, kc)) {
+            const bool optional = (r.variant & 0xf00) == MXE_VAR_PANEL;
+            st = cw.alloc(ctx->pool, cb, s, optional);
+            if (st && !(optional && st == MXE_ERR_OUT_OF_MEMORY)) return st;
             a.carry_ws = cw.p;
         }
-        MXE_HIP(launch_spmv(a, variant, s));
+        MXE_HIP(launch_spmv(a, r.variant, s));
     }
     return MXE_OK;
 }
@@ -1157,11 +1155,10 @@ static mxe_status semiring_core(mxe_ctx *ctx, Matrix &A, int semiring, int32_t k
             SpmvArgs a;
             if ((st = prepare_args(ctx, A, r.variant, kc, Xc, ldx, Yc, ldy, s, &a))) return st;
             Scratch cw;
-            if (cw.alloc(ctx->pool, carry_bytes(A, r.variant, kc), s) == MXE_OK)
-                MXE_HIP(launch_spmv_panel(*a.panel, *a.panel_layout, a.vtype, semiring, a.rp, Xc, ldx, Yc,
-                                          ldy, cw.p, s));
-            else                                    // no room for the products
-                MXE_HIP(launch_spmv_semiring(a, semiring, s));
+            st = cw.alloc(ctx->pool, carry_bytes(A, r.variant, kc), s, true);
+            if (st && st != MXE_ERR_OUT_OF_MEMORY) return st;
+            MXE_HIP(launch_spmv_panel(*a.panel, *a.panel_layout, a.vtype, semiring, a.rp, Xc, ldx, Yc,
+                                      ldy, cw.p, s));
         } else if (slab_family(r.variant)) {        // the layout; the window is (+, *) only
             SpmvArgs a;
             if ((st = prepare_args(ctx, A, r.variant, kc, Xc, ldx, Yc, ldy, s, &a))) return st;

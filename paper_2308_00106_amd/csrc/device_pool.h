@@ -53,8 +53,9 @@ class DevicePool {
         for (hipEvent_t e : events_) (void)hipEventDestroy(e);
     }
 
-    // counted: the bytes are held against a budget.
-    hipError_t get(void **p, size_t bytes, hipStream_t s, bool counted = false) {
+    // counted: the bytes are held against a budget. optional: the caller can do
+    // without, so the call waits for nothing.
+    hipError_t get(void **p, size_t bytes, hipStream_t s, bool counted = false, bool optional = false) {
         *p = nullptr;
         const bool pooled = ordered(s);
         size_t size = !pooled ? bytes : counted ? paged(bytes) : rounded(bytes);
@@ -63,7 +64,8 @@ class DevicePool {
         // a capture neither waits nor frees
         if (e == hipErrorOutOfMemory && (pooled || s == hipStreamPerThread) && !capturing(s)) {
             (void)hipGetLastError();
-            make_room(s);
+            if (optional) drop_unused(s);
+            else make_room(s);
             e = hipMallocAsync(p, size, s);
             if (e == hipErrorOutOfMemory && pooled && size > paged(bytes)) {
                 (void)hipGetLastError();
@@ -194,6 +196,15 @@ class DevicePool {
         if (hipStreamSynchronize(nullptr) != hipSuccess || hipStreamSynchronize(s) != hipSuccess ||
             hipDeviceGetDefaultMemPool(&runtime, device_) != hipSuccess || hipMemPoolTrimTo(runtime, 0) != hipSuccess)
             (void)hipGetLastError();
+    }
+    // The unused blocks that s, or the legacy stream, may free without waiting.
+    void drop_unused(hipStream_t s) {
+        std::lock_guard<std::mutex> lk(mu_);
+        for (Node it = free_.begin(); it != free_.end();) {
+            const Node at = it++;
+            const hipStream_t on = at->kind == kLegacy ? nullptr : s;
+            if (free_on(*at, on) && release(at->p, on)) forget(at);
+        }
     }
     // Every unused block; ended: no use of one is still running.
     void drop(hipStream_t s, bool ended) {

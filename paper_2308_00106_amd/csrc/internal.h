@@ -193,7 +193,8 @@ size_t panel_build_ws_bytes(const PanelGeom &g);
 hipError_t launch_panel_build(const PanelGeom &g, const int32_t *rp, const int32_t *col, const void *val,
                               int val_bytes, const PanelLayout &l, void *ws, hipStream_t s);
 // semiring: MXE_SR_* (mxe.h); k = 1. prod: panel_entries values of the
-// accumulation type, this launch's own.
+// accumulation type, this launch's own; null: none are kept, the same result bit
+// for bit from a slower kernel.
 hipError_t launch_spmv_panel(const PanelGeom &g, const PanelLayout &l, int vtype, int semiring,
                              const int32_t *rp, const void *X, int64_t ldx, void *Y, int64_t ldy,
                              void *prod, hipStream_t s);
@@ -229,7 +230,8 @@ struct SpmvArgs {
     int32_t slab_win;
     // COO variant: row index per entry (built once, read only)
     const int32_t *coo_row;
-    // panel variant layout (null when not built); its products go to carry_ws
+    // panel variant layout (null when not built); its products go to carry_ws, if
+    // that is not null
     const PanelGeom *panel;
     const PanelLayout *panel_layout;
 };

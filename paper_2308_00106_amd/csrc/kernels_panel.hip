@@ -28,6 +28,10 @@
 // With several right-hand sides the products grow with k while a gather of k
 // values stays one request, so those stay with the slab kernel.
 //
+// Without memory for the products the second pass makes them itself, x gathered
+// from memory (launch_spmv_panel): the same products summed the same way, so the
+// same bits, but at a gather per entry.
+//
 // Rows are summed in a fixed order (positions in groups, groups in row
 // order), so results are deterministic.
 
@@ -201,6 +205,14 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_fill(
 // Entries per lane and load: 16 bytes of value where that is at most 4 entries.
 template <typename V> struct PanelVec { static constexpr int N = sizeof(V) == 8 ? 2 : 4; };  // divides the runs' 4
 
+// One entry's product; a NaN is no path in (min, +).
+template <int SR, typename V, typename T>
+__device__ inline T panel_product(V v, T x) {
+    const T m = Semiring<SR, T>::mul(PanelVal<V, T>::get(v), x);
+    if constexpr (SR == 1) return m == m ? m : Semiring<SR, T>::identity();
+    else return m;
+}
+
 // First pass. Bound by memory bandwidth: value and offset read and product
 // written once, x copied to LDS by each of the panel's `split` workgroups
 // (blockIdx / split is the panel). The entries' loads run two groups ahead of
@@ -210,7 +222,6 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_products(
     PanelGeom g, const int32_t *__restrict__ offt, const uint16_t *__restrict__ c16,
     const V *__restrict__ val, const T *__restrict__ X, int64_t ldx, T *__restrict__ prod) {
     __shared__ T xs[kPanelBytes / sizeof(T)];
-    using S = Semiring<SR, T>;
     constexpr int N = PanelVec<V>::N, U = 2;
     typedef V vv __attribute__((ext_vector_type(N)));
     typedef uint16_t cv __attribute__((ext_vector_type(N)));
@@ -261,9 +272,7 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_products(
 #pragma unroll
                 for (int n = 0; n < N; ++n) {
                     const T x = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(xs) + c[u][n]);
-                    T m = S::mul(PanelVal<V, T>::get(a[u][n]), x);
-                    if constexpr (SR == 1) m = m == m ? m : S::identity();   // NaN is no path
-                    r[u][n] = m;
+                    r[u][n] = panel_product<SR, V>(V(a[u][n]), x);
                 }
             }
         const int64_t at = q;
@@ -280,6 +289,39 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_products(
 // stay in flight across it (__syncthreads would wait for them).
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Where the second pass takes four consecutive products of panel p from: the
+// first pass's workspace, or the entries and x. Quads by 32-bit byte offsets from
+// uniform bases (panel_geometry bounds them).
+template <typename T> struct StoredProducts {
+    static constexpr int kAhead = sizeof(T) == 8 ? 3 : 5;  // groups of fours of a run in flight per lane
+    typedef T tv __attribute__((ext_vector_type(4)));
+    const T *prod;
+    __device__ tv quad(int32_t a, int) const {
+        return *reinterpret_cast<const tv *>(reinterpret_cast<const char *>(prod) + (uint32_t)a * (uint32_t)sizeof(tv));
+    }
+};
+template <typename V, typename T, int SR> struct OwnProducts {
+    static constexpr int kAhead = 1;                       // no registers left for more, no memory to spill to
+    typedef T tv __attribute__((ext_vector_type(4)));
+    typedef V vv __attribute__((ext_vector_type(4)));
+    typedef uint16_t cv __attribute__((ext_vector_type(4)));
+    const V *val;
+    const uint16_t *c16;
+    const T *X;
+    int64_t ldx;
+    int32_t wbits;
+    __device__ tv quad(int32_t a, int p) const {
+        const vv v = reinterpret_cast<const vv *>(val)[a];
+        const cv c = reinterpret_cast<const cv *>(c16)[a];
+        const T *xp = X + ((int64_t)p << wbits) * ldx;
+        tv r;
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+            r[n] = panel_product<SR, V>(V(v[n]), xp[(int64_t)(c[n] / sizeof(T)) * ldx]);
+        return r;
+    }
+};
+
 // Second pass: a workgroup per CU walks its chunks, the next chunk's products
 // on their way to registers while it sums the current one. G lanes share a run,
 // each lane taking four entries at a time; R runs of up to U groups of G fours
@@ -290,10 +332,10 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 // sum of each group of E it spans. Summing with one to eight lanes per row
 // over its places instead took 13% longer (rows of 1 to 256 entries: the longest
 // row of a wavefront held up the others).
-template <typename T, int SR, int G, int R, int U>
+template <typename Src, typename T, int SR, int G, int R, int U>
 __global__ __launch_bounds__(kPanelBlock) void k_panel_rows(
     PanelGeom g, const int32_t *__restrict__ offt, const int32_t *__restrict__ crow,
-    const int32_t *__restrict__ rp, const uint16_t *__restrict__ pos16, const T *__restrict__ prod,
+    const int32_t *__restrict__ rp, const uint16_t *__restrict__ pos16, Src products,
     T *__restrict__ Y, int64_t ldy) {
     constexpr int E = kChunkBytes / (int)sizeof(T) / kPanelBlock;     // positions per thread
     constexpr int RP = 3;                                             // row starts per thread held ahead
@@ -313,10 +355,6 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_rows(
     const int32_t c0 = (int32_t)(blockIdx.x % 8) * per, c1 = min(c0 + per, g.chunks);
     int32_t b = c0 + (int32_t)(blockIdx.x / 8);
     if (b >= c1) return;
-    // quads by 32-bit byte offsets from uniform bases (panel_geometry bounds them)
-    auto prodv = [&](int32_t a) {
-        return *reinterpret_cast<const tv *>(reinterpret_cast<const char *>(prod) + (uint32_t)a * (uint32_t)sizeof(tv));
-    };
     auto posv = [&](int32_t a) {
         return *reinterpret_cast<const pv *>(reinterpret_cast<const char *>(pos16) + (uint32_t)a * (uint32_t)sizeof(pv));
     };
@@ -354,7 +392,7 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_rows(
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (a[r] + u * G < n[r]) {
-                    v[r][u] = prodv(a[r] + u * G);
+                    v[r][u] = products.quad(a[r] + u * G, t / G + r * NG);
                     w[r][u] = posv(a[r] + u * G);
                 }
         }
@@ -378,11 +416,11 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_rows(
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (a[r] + u * G < n[r]) put(v[r][u], w[r][u]);
-            for (int32_t q = a[r] + U * G; q < n[r]; q += G) put(prodv(q), posv(q));
+            for (int32_t q = a[r] + U * G; q < n[r]; q += G) put(products.quad(q, t / G + r * NG), posv(q));
         }
         for (int p = t / G + R * NG; p < g.panels; p += NG) {
             const int32_t o = offt[(int64_t)b * g.panels + p] >> 2, e = offt[(int64_t)(b + 1) * g.panels + p] >> 2;
-            for (int32_t q = o + lane; q < e; q += G) put(prodv(q), posv(q));
+            for (int32_t q = o + lane; q < e; q += G) put(products.quad(q, p), posv(q));
         }
         const int32_t row0 = r0, nrow = rows, first = e0;
         b += side;
@@ -414,21 +452,25 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_rows(
     }
 }
 
-template <typename T, int SR, int G, int R, int U>
-void rows_launch(const PanelGeom &g, const PanelLayout &l, const int32_t *rp, const void *prod, void *Y,
+template <typename T, int SR, typename Src>
+void rows_launch(const PanelGeom &g, const PanelLayout &l, const int32_t *rp, const Src &products, void *Y,
                  int64_t ldy, hipStream_t s) {
     const int32_t per = (g.chunks + 7) / 8, side = std::max(1, std::min(per, g.cus / 8));
-    hipLaunchKernelGGL((k_panel_rows<T, SR, G, R, U>), dim3(8 * side), dim3(kPanelBlock), 0, s, g, l.offt, l.crow,
-                       rp, l.pos16, (const T *)prod, (T *)Y, ldy);
+    hipLaunchKernelGGL((k_panel_rows<Src, T, SR, 8, 2, Src::kAhead>), dim3(8 * side), dim3(kPanelBlock), 0,
+                       s, g, l.offt, l.crow, rp, l.pos16, products, (T *)Y, ldy);
 }
 
 template <typename V, typename T, int SR>
 hipError_t panel_launch(const PanelGeom &g, const PanelLayout &l, const int32_t *rp, const void *X,
                         int64_t ldx, void *Y, int64_t ldy, void *prod, hipStream_t s) {
-    hipLaunchKernelGGL((k_panel_products<V, T, SR>), dim3(g.panels * g.split), dim3(kPanelBlock), 0, s,
-                       g, l.offt, l.c16, (const V *)l.val, (const T *)X, ldx, (T *)prod);
-    if constexpr (sizeof(T) == 8) rows_launch<T, SR, 8, 2, 3>(g, l, rp, prod, Y, ldy, s);
-    else rows_launch<T, SR, 8, 2, 5>(g, l, rp, prod, Y, ldy, s);
+    if (prod) {
+        hipLaunchKernelGGL((k_panel_products<V, T, SR>), dim3(g.panels * g.split), dim3(kPanelBlock), 0, s,
+                           g, l.offt, l.c16, (const V *)l.val, (const T *)X, ldx, (T *)prod);
+        rows_launch<T, SR>(g, l, rp, StoredProducts<T>{(const T *)prod}, Y, ldy, s);
+    } else {
+        const OwnProducts<V, T, SR> own{(const V *)l.val, l.c16, (const T *)X, ldx, g.wbits};
+        rows_launch<T, SR>(g, l, rp, own, Y, ldy, s);
+    }
     return hipGetLastError();
 }
 
@@ -520,7 +562,6 @@ hipError_t launch_panel_build(const PanelGeom &g, const int32_t *rp, const int32
 hipError_t launch_spmv_panel(const PanelGeom &g, const PanelLayout &l, int vtype, int semiring,
                              const int32_t *rp, const void *X, int64_t ldx, void *Y, int64_t ldy,
                              void *prod, hipStream_t s) {
-    if (!prod) return hipErrorInvalidValue;
     switch (vtype) {
     case VAL_F64: return panel_by_semiring<double, double>(g, l, semiring, rp, X, ldx, Y, ldy, prod, s);
     case VAL_F32: return panel_by_semiring<float, float>(g, l, semiring, rp, X, ldx, Y, ldy, prod, s);

@@ -87,6 +87,42 @@ def tuning_without_room_for_the_panels():
             ctx.release(A)
 
 
+def products_without_a_workspace():
+    """A panel product without room for its workspace: the same bits, over each
+    semiring, with infinities and NaN in x, a strided X and Y, and so on the next
+    call with room. A new stream finds no block of the context's to reuse."""
+    from test_gpu_panel import CASES
+    for name in ("one_panel", "8193_columns", "many_panels", "mostly_empty", "all_but_one_empty", "long_rows",
+                 "several_waves", "wide"):
+        A0 = CASES[name]()
+        for storage in ("f64", "f32", "bf16"):
+            dt = torch.float64 if storage == "f64" else torch.float32
+            x = synth.vector(A0.ncols, 2)
+            x[:: 7] = 0.0
+            x[0], x[A0.ncols // 2], x[-1] = np.inf, np.nan, -np.inf
+            X = torch.zeros((A0.ncols, 3), dtype=dt, device="cuda")
+            X[:, 1] = torch_vec(x, dt)
+            with mx.Context(0) as ctx:
+                A = ctx.register(A0, storage)
+                ctx.set_variant(A, 1, mx.variant(mx.VAR_PANEL))
+                for semiring in (mx.SR_PLUS_TIMES, mx.SR_MIN_PLUS, mx.SR_OR_AND):
+                    Y = torch.full((3, A0.nrows, 2), 7.0, dtype=dt, device="cuda")
+                    side = torch.cuda.Stream()
+                    torch.cuda.synchronize()
+                    ctx.spmv_semiring(A, semiring, X[:, 1:2], Y[0][:, 0:1])
+                    shim.shim_fail(0, -1)
+                    ctx.spmv_semiring(A, semiring, X[:, 1:2], Y[1][:, 0:1], stream=side)
+                    assert shim.shim_failed() > 0
+                    shim.shim_fail(0, 0)
+                    ctx.spmv_semiring(A, semiring, X[:, 1:2], Y[2][:, 0:1], stream=side)
+                    torch.cuda.synchronize()
+                    bits = Y.view(torch.int64 if storage == "f64" else torch.int32)
+                    for other in (1, 2):
+                        assert torch.equal(bits[0], bits[other]), (name, storage, semiring, other)
+                    assert bool((Y[:, :, 1] == 7.0).all())
+            print(name, storage, flush=True)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]]()
     print("ok", flush=True)

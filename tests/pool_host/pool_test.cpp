@@ -191,6 +191,23 @@ bool room_from_other_contexts() {
     return true;
 }
 
+// A block that the caller can do without waits for nothing: it gets back what
+// is free by now and no more.
+bool optional_blocks_wait_for_nothing() {
+    DevicePool pool(0);
+    SimStream a, b;
+    call(pool, a, 4 * kMiB);
+    call(pool, b, 2 * kMiB);
+    finish(a);
+    sim::capacity = 8 * kMiB;
+    void *p;
+    CHECK(pool.get(&p, 5 * kMiB, &a, false, true) == hipSuccess && sim::held == 7 * kMiB);
+    pool.put(p, &a);
+    CHECK(pool.get(&p, 8 * kMiB, &a, false, true) == hipErrorOutOfMemory && sim::last == hipSuccess);
+    CHECK(sim::event_waits == 0 && sim::device_syncs == 0 && sim::trims == 0 && a.waited_for.empty());
+    return true;
+}
+
 // A call in a capture takes its block from the runtime and asks for no room.
 bool no_room_in_a_capture() {
     DevicePool pool(0);
@@ -255,6 +272,7 @@ const struct {
     {"limit_where_all_are_in_use", limit_where_all_are_in_use},
     {"failing_calls", failing_calls},
     {"room_from_other_contexts", room_from_other_contexts},
+    {"optional_blocks_wait_for_nothing", optional_blocks_wait_for_nothing},
     {"no_room_in_a_capture", no_room_in_a_capture},
     {"counted_blocks_fit", counted_blocks_fit},
     {"all_returned", all_returned},
