@@ -659,8 +659,7 @@ static mxe_status spmv_core(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, i
         Scratch cw;                             // this launch's workspace (MERGE, COO, PANEL)
         if (const size_t cb = carry_bytes(A, r.variant, kc)) {
             const bool optional = (r.variant & 0xf00) == MXE_VAR_PANEL;
-            st = cw.alloc(ctx->pool, cb, s, optional);
-            if (st && !(optional && st == MXE_ERR_OUT_OF_MEMORY)) return st;
+            if ((st = cw.alloc(ctx->pool, cb, s, optional)) && !optional) return st;
             a.carry_ws = cw.p;
         }
         MXE_HIP(launch_spmv(a, r.variant, s));
@@ -1155,8 +1154,7 @@ static mxe_status semiring_core(mxe_ctx *ctx, Matrix &A, int semiring, int32_t k
             SpmvArgs a;
             if ((st = prepare_args(ctx, A, r.variant, kc, Xc, ldx, Yc, ldy, s, &a))) return st;
             Scratch cw;
-            st = cw.alloc(ctx->pool, carry_bytes(A, r.variant, kc), s, true);
-            if (st && st != MXE_ERR_OUT_OF_MEMORY) return st;
+            (void)cw.alloc(ctx->pool, carry_bytes(A, r.variant, kc), s, true);
             MXE_HIP(launch_spmv_panel(*a.panel, *a.panel_layout, a.vtype, semiring, a.rp, Xc, ldx, Yc,
                                       ldy, cw.p, s));
         } else if (slab_family(r.variant)) {        // the layout; the window is (+, *) only
