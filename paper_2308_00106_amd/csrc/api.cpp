@@ -438,6 +438,16 @@ static mxe_status ensure_panel(mxe_ctx *ctx, Matrix &A, hipStream_t s) {
     return MXE_OK;
 }
 
+// A tuned choice whose panel layout has no room in the budget or on the device:
+// a row kernel, which needs none. A forced choice fails.
+static mxe_status ensure_panel_or_rows(mxe_ctx *ctx, Matrix &A, TuneResult *r, hipStream_t s) {
+    if ((r->variant & 0xf00) != MXE_VAR_PANEL) return MXE_OK;
+    const mxe_status st = ensure_panel(ctx, A, s);
+    if (r->forced || (st != MXE_ERR_OUT_OF_MEMORY && st != MXE_ERR_BUDGET)) return st;
+    r->variant = MXE_VARIANT(MXE_VAR_GROUP, r->group_lanes);
+    return MXE_OK;
+}
+
 static bool slab_family(int variant) {
     return (variant & 0xf00) == MXE_VAR_SLAB || (variant & 0xf00) == MXE_VAR_WINDOW;
 }
@@ -651,7 +661,7 @@ static mxe_status spmv_core(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, i
         const int32_t kc = std::min<int32_t>(16, k - c0);
         TuneResult r;
         mxe_status st = ensure_variant(ctx, A, kc, s, &r);
-        if (st) return st;
+        if (st || (st = ensure_panel_or_rows(ctx, A, &r, s))) return st;
         SpmvArgs a;
         if ((st = prepare_args(ctx, A, r.variant, kc, (const char *)X + (size_t)c0 * eb, ldx,
                                (char *)Y + (size_t)c0 * eb, ldy, s, &a)))
@@ -1149,7 +1159,7 @@ static mxe_status semiring_core(mxe_ctx *ctx, Matrix &A, int semiring, int32_t k
         void *Yc = (char *)Y + (size_t)c0 * eb;
         TuneResult r;
         mxe_status st = ensure_variant(ctx, A, kc, s, &r);
-        if (st) return st;
+        if (st || (st = ensure_panel_or_rows(ctx, A, &r, s))) return st;
         if ((r.variant & 0xf00) == MXE_VAR_PANEL) {
             SpmvArgs a;
             if ((st = prepare_args(ctx, A, r.variant, kc, Xc, ldx, Yc, ldy, s, &a))) return st;

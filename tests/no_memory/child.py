@@ -123,6 +123,64 @@ def products_without_a_workspace():
             print(name, storage, flush=True)
 
 
+def tuned_panels_without_room_for_the_layout():
+    """A matrix made again with the seed it was tuned for, whose panel layout is
+    not built yet and finds no room, on the device or in the budget: the product
+    runs all the same. A forced choice says what is missing."""
+    A0 = synth.skewed_clustered(1_200_000, 2.0, 1.0, 256, 2000.0, 5)
+    csr, f32 = 8 * A0.nnz, torch.float32
+    budget = 16 * csr                                        # for every layout of the tuning at once
+    with mx.Context(0, budget_bytes=budget) as ctx:
+        A = ctx.register(A0, "f32")
+        B = ctx.permute(A, 2)
+        assert ctx.tune(B, 1) == mx.variant(mx.VAR_PANEL)
+        x, y = product(ctx, B, A0, 3, dt=f32)
+        for semiring in (mx.SR_PLUS_TIMES, mx.SR_MIN_PLUS):
+            ctx.release(B)
+            B = ctx.permute(A, 2)                            # the same key; its layout is to be built
+            held = ctx.matrix_info(B).device_bytes
+            shim.shim_fail(1 << 31, 1)                       # empties the pool of the last one's layout
+            ctx.probe_gather(1 << 31, 1 << 20)
+            assert shim.shim_failed() == 1
+            Y = [torch.empty_like(y) for _ in range(2)]
+            side = torch.cuda.Stream()
+            torch.cuda.synchronize()
+            shim.shim_fail(0, -1)
+            ctx.spmv_semiring(B, semiring, torch_vec(x, f32), Y[0], stream=side)
+            assert shim.shim_failed() > 0 and ctx.matrix_info(B).device_bytes == held
+            shim.shim_fail(0, 0)
+            ctx.spmv_semiring(B, semiring, torch_vec(x, f32), Y[1], stream=side)
+            torch.cuda.synchronize()
+            assert ctx.matrix_info(B).device_bytes > held
+            if semiring == mx.SR_MIN_PLUS:
+                assert torch.equal(Y[0], Y[1])
+            else:
+                Bo = synth.CSR(A0.nrows, A0.ncols, *ctx.export_csr(B))
+                for got in Y:
+                    assert spmv_error(Bo, x, got.cpu().numpy().astype(np.float64), "f32") <= TOL["f32"]
+        ctx.release(B)                                       # the budget used up but for half a layout
+        B = ctx.permute(A, 2)
+        n = A0.nrows
+        left = budget - sum(ctx.matrix_info(m).device_bytes for m in (A, B)) - csr // 2
+        while left > 8 * n:
+            nnz = min((left - 4 * (n + 1)) // 12, 20 * n)
+            rp = np.minimum(np.arange(n + 1, dtype=np.int64) * 20, nnz).astype(np.int32)
+            M = ctx.register_matrix(n, n, rp, np.arange(nnz, dtype=np.int32) % 20, np.ones(nnz))
+            left -= ctx.matrix_info(M).device_bytes
+        held = ctx.matrix_info(B).device_bytes
+        z = torch.empty_like(y)
+        ctx.spmv(B, torch_vec(x, f32), z)
+        torch.cuda.synchronize()
+        assert ctx.matrix_info(B).device_bytes == held
+        assert spmv_error(Bo, x, z.cpu().numpy().astype(np.float64), "f32") <= TOL["f32"]
+        ctx.set_variant(B, 1, mx.variant(mx.VAR_PANEL))
+        try:
+            ctx.spmv(B, torch_vec(x, f32), z)
+            raise AssertionError("a forced layout without room")
+        except mx.MxeError as e:
+            assert e.status == mx.ERR_BUDGET
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]]()
     print("ok", flush=True)
