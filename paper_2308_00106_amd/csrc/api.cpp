@@ -276,6 +276,8 @@ static bool layout_geometry(const mxe_ctx *ctx, const Matrix &A, int kclass, int
                          slab_y_lds(ctx), slab_resident(ctx, cus), g);
 }
 
+static void drop_slab(mxe_ctx *ctx, Matrix &A, const Matrix::Slab &sl, hipStream_t s);
+
 // cus: the compute units whose workgroups share the matrix, which sizes the
 // row blocks (all of the device for a single product, one XCD's in a batch)
 static mxe_status ensure_slab(mxe_ctx *ctx, Matrix &A, int kclass, int units, int cus,
@@ -295,17 +297,23 @@ static mxe_status ensure_slab(mxe_ctx *ctx, Matrix &A, int kclass, int units, in
     mxe_status st;
     if ((st = reserve(ctx, bytes))) return st;
     A.bytes += bytes;
-    void *p;
-    if ((st = dev_alloc(A, &p, 4 * noff, s))) return st;
-    sl.off = (int32_t *)p;
-    if ((st = dev_alloc(A, &p, 4 * (size_t)A.nnz, s))) return st;
-    sl.idx = (uint32_t *)p;
-    if ((st = dev_alloc(A, &p, (size_t)vb * A.nnz, s))) return st;
-    sl.val = p;
-    Scratch ws;
-    if ((st = ws.alloc(ctx->pool, slab_build_ws_bytes(sl.g), s))) return st;
-    MXE_HIP(launch_slab_build(sl.g, A.rp, A.col, A.val, vb, sl.off, sl.idx, sl.val, ws.p, s));
-    if ((st = settle(A, s))) return st;
+    auto build = [&]() -> mxe_status {
+        void *p;
+        if ((st = dev_alloc(A, &p, 4 * noff, s))) return st;
+        sl.off = (int32_t *)p;
+        if ((st = dev_alloc(A, &p, 4 * (size_t)A.nnz, s))) return st;
+        sl.idx = (uint32_t *)p;
+        if ((st = dev_alloc(A, &p, (size_t)vb * A.nnz, s))) return st;
+        sl.val = p;
+        Scratch ws;
+        if ((st = ws.alloc(ctx->pool, slab_build_ws_bytes(sl.g), s))) return st;
+        MXE_HIP(launch_slab_build(sl.g, A.rp, A.col, A.val, vb, sl.off, sl.idx, sl.val, ws.p, s));
+        return settle(A, s);
+    };
+    if ((st = build())) {
+        drop_slab(ctx, A, sl, s);
+        return st;
+    }
     *out = &(A.slabs[key] = sl);
     return MXE_OK;
 }
@@ -1427,8 +1435,9 @@ constexpr int kBatchSlabUnits = 8;
 // tiles of its tuned GROUP lane count, when that layout does not fit the
 // matrix or the HBM budget. An
 // item whose variant was forced to a row family (mxe_set_variant) runs as row
-// tiles. lds: the dynamic LDS the launch needs (the largest slab block's
-// partial y).
+// tiles. An item tuned to the column panels keeps only their layout, so its slab
+// layouts may find no room: row tiles then. lds: the dynamic LDS the launch
+// needs (the largest slab block's partial y).
 // The work unit a batch runs A's k-column products as (see build_batch_descs):
 // *r the tuning, *out the column-slab layout (null: row tiles). With `prepare`
 // it tunes and builds what is missing (stream s); without it, it only looks
@@ -1483,9 +1492,11 @@ static mxe_status batch_layout(mxe_ctx *ctx, Matrix &A, int32_t k, int32_t index
         }
     }
     if (!sl && slab_tuned) {
-        if (prepare) return st;
-        return fail(MXE_ERR_UNSUPPORTED, "batch item " + std::to_string(index) +
-                                             " has no slab layout built yet");
+        const bool panel = (r->variant & 0xf00) == MXE_VAR_PANEL;
+        if (prepare && !(panel && (st == MXE_ERR_BUDGET || st == MXE_ERR_OUT_OF_MEMORY))) return st;
+        if (!panel)
+            return fail(MXE_ERR_UNSUPPORTED, "batch item " + std::to_string(index) +
+                                                 " has no slab layout built yet");
     }
     *out = sl;
     return MXE_OK;

@@ -181,6 +181,54 @@ def tuned_panels_without_room_for_the_layout():
             assert e.status == mx.ERR_BUDGET
 
 
+def batches_of_panel_matrices_without_room_for_slabs():
+    """A matrix tuned to the column panels, whose slab layouts find no room in the
+    budget or on the device any more: batches, the allocation-free ones too, and
+    serving rounds run it as row tiles."""
+    A0 = synth.skewed_clustered(1_200_000, 2.0, 1.0, 256, 2000.0, 5)
+    csr, f32 = 8 * A0.nnz, torch.float32
+    budget = 16 * csr
+    with mx.Context(0, budget_bytes=budget) as ctx:
+        A = ctx.register(A0, "f32")
+        B = ctx.permute(A, 2)
+        assert ctx.tune(B, 1) == mx.variant(mx.VAR_PANEL)
+        x, y = product(ctx, B, A0, 3, dt=f32)
+        Bo = synth.CSR(A0.nrows, A0.ncols, *ctx.export_csr(B))
+        X = torch_vec(x, f32)
+
+        def batches():
+            Y = torch.full((2, A0.nrows), float("nan"), dtype=f32, device="cuda")
+            ctx.spmv_batch([(B, X, Y[0])])
+            ctx.spmv_batch_noalloc([(B, X, Y[1])])
+            torch.cuda.synchronize()
+            assert torch.equal(Y[0], Y[1])
+            assert spmv_error(Bo, x, Y[0].cpu().numpy().astype(np.float64), "f32") <= TOL["f32"]
+
+        held = ctx.matrix_info(B).device_bytes
+        shim.shim_fail(1 << 31, 1)                           # empties the pool
+        ctx.probe_gather(1 << 31, 1 << 20)
+        shim.shim_fail(csr // 4, -1)
+        batches()
+        batches()
+        assert shim.shim_failed() > 0 and ctx.matrix_info(B).device_bytes == held
+        shim.shim_fail(0, 0)
+        n = A0.nrows                                         # the budget used up but for half a layout
+        left = budget - sum(ctx.matrix_info(m).device_bytes for m in (A, B)) - csr // 2
+        while left > 8 * n:
+            nnz = min((left - 4 * (n + 1)) // 12, 20 * n)
+            rp = np.minimum(np.arange(n + 1, dtype=np.int64) * 20, nnz).astype(np.int32)
+            M = ctx.register_matrix(n, n, rp, np.arange(nnz, dtype=np.int32) % 20, np.ones(nnz))
+            left -= ctx.matrix_info(M).device_bytes
+        held = ctx.matrix_info(B).device_bytes
+        batches()
+        plan = ctx.batch_create([(B, X, y)])
+        ctx.batch_launch(plan)
+        torch.cuda.synchronize()
+        assert spmv_error(Bo, x, y.cpu().numpy().astype(np.float64), "f32") <= TOL["f32"]
+        ctx.batch_destroy(plan)
+        assert ctx.matrix_info(B).device_bytes == held
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]]()
     print("ok", flush=True)
