@@ -363,7 +363,8 @@ typedef struct mxe_serve_config {
  * widest resident matrix's columns times max_merge_k rounded up to a power of
  * two, at least 64 MiB, counted in the HBM budget; all allocated here). Requests are admitted
  * in arrival order while the in-flight vector bytes fit the context budget
- * beside the resident matrices. Each admission round takes up to max_batch
+ * beside the resident matrices; a product's MXE_VAR_PANEL workspace is counted
+ * too, and left out (same bits, slower) where it does not fit. Each admission round takes up to max_batch
  * items, each taking one of max_inflight slots: an item is one request, or
  * queued permuted-space requests on the same matrix merged into one product
  * of at most max_merge_k right-hand sides (the matrix streams once for all of

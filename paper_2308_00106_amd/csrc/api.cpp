@@ -53,10 +53,11 @@ struct Scratch {
     ~Scratch() {
         if (p) pool->put(p, s);
     }
-    mxe_status alloc(DevicePool &from, size_t bytes, hipStream_t stream, bool optional = false) {
+    mxe_status alloc(DevicePool &from, size_t bytes, hipStream_t stream, bool counted = false,
+                     bool optional = false) {
         s = stream;
         pool = &from;
-        hipError_t e = from.get(&p, std::max<size_t>(bytes, 256), stream, false, optional);
+        hipError_t e = from.get(&p, std::max<size_t>(bytes, 256), stream, counted, optional);
         return e == hipSuccess ? MXE_OK : hip_fail(e, "hipMallocAsync(workspace)");
     }
 };
@@ -662,8 +663,19 @@ mxe_status ensure_variant(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, Tun
 
 // ---- products -------------------------------------------------------------------------
 
+uint64_t product_workspace_bytes(mxe_ctx *ctx, Matrix &A, int32_t k) {
+    const int32_t last = (k - 1) % 16 + 1;                 // columns of the last launch, the one that may be single
+    const auto it = ctx->tuned.find(tune_key(A, last));
+    PanelGeom g;
+    if (last > 1 || it == ctx->tuned.end() || (it->second.variant & 0xf00) != MXE_VAR_PANEL ||
+        ensure_max_row(A, nullptr) != MXE_OK || !matrix_panel_geometry(ctx, A, &g))
+        return 0;
+    return panel_entries(g) * (uint64_t)elem_bytes_of(A.storage);
+}
+
+// workspace: whether optional ones may be taken.
 static mxe_status spmv_core(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, int64_t ldx,
-                            void *Y, int64_t ldy, hipStream_t s) {
+                            void *Y, int64_t ldy, bool workspace, hipStream_t s) {
     const int eb = elem_bytes_of(A.storage);
     for (int32_t c0 = 0; c0 < k; c0 += 16) {
         const int32_t kc = std::min<int32_t>(16, k - c0);
@@ -677,7 +689,9 @@ static mxe_status spmv_core(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, i
         Scratch cw;                             // this launch's workspace (MERGE, COO, PANEL)
         if (const size_t cb = carry_bytes(A, r.variant, kc)) {
             const bool optional = (r.variant & 0xf00) == MXE_VAR_PANEL;
-            if ((st = cw.alloc(ctx->pool, cb, s, optional)) && !optional) return st;
+            if ((workspace || !optional) &&
+                (st = cw.alloc(ctx->pool, cb, s, optional && A.counted, optional)) && !optional)
+                return st;
             a.carry_ws = cw.p;
         }
         MXE_HIP(launch_spmv(a, r.variant, s));
@@ -686,9 +700,9 @@ static mxe_status spmv_core(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, i
 }
 
 mxe_status spmv_internal(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, int64_t ldx, void *Y,
-                         int64_t ldy, uint32_t flags, hipStream_t s) {
+                         int64_t ldy, uint32_t flags, hipStream_t s, bool workspace) {
     if (!(flags & MXE_SPACE_ORIGINAL) || !A.rperm) {
-        mxe_status st = spmv_core(ctx, A, k, X, ldx, Y, ldy, s);
+        mxe_status st = spmv_core(ctx, A, k, X, ldx, Y, ldy, workspace, s);
         return st ? st : note_use(A, s);
     }
     // Eq. 1: y = P_r^-1 (B (P_c^-1 x))
@@ -698,7 +712,7 @@ mxe_status spmv_internal(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, int6
     if ((st = xp.alloc(ctx->pool, (size_t)eb * std::max(A.ncols, 1) * k, s))) return st;
     if ((st = yp.alloc(ctx->pool, (size_t)eb * std::max(A.nrows, 1) * k, s))) return st;
     MXE_HIP(launch_gather_rows(A.ncols, k, A.cperm, X, ldx, xp.p, k, eb, s));
-    if ((st = spmv_core(ctx, A, k, xp.p, k, yp.p, k, s))) return st;
+    if ((st = spmv_core(ctx, A, k, xp.p, k, yp.p, k, workspace, s))) return st;
     MXE_HIP(launch_scatter_rows(A.nrows, k, A.rperm, A.rinv, yp.p, k, Y, ldy, eb, s));
     return note_use(A, s);
 }
@@ -1172,7 +1186,7 @@ static mxe_status semiring_core(mxe_ctx *ctx, Matrix &A, int semiring, int32_t k
             SpmvArgs a;
             if ((st = prepare_args(ctx, A, r.variant, kc, Xc, ldx, Yc, ldy, s, &a))) return st;
             Scratch cw;
-            (void)cw.alloc(ctx->pool, carry_bytes(A, r.variant, kc), s, true);
+            (void)cw.alloc(ctx->pool, carry_bytes(A, r.variant, kc), s, A.counted, true);
             MXE_HIP(launch_spmv_panel(*a.panel, *a.panel_layout, a.vtype, semiring, a.rp, Xc, ldx, Yc,
                                       ldy, cw.p, s));
         } else if (slab_family(r.variant)) {        // the layout; the window is (+, *) only

@@ -193,8 +193,11 @@ namespace mxe {
 std::shared_ptr<Matrix> find_matrix(mxe_ctx *ctx, mxe_mat m);
 // Records that work on A was queued on s (see Matrix::uses).
 mxe_status note_use(Matrix &A, hipStream_t s);
+// workspace: false leaves out workspaces that the product can do without.
 mxe_status spmv_internal(mxe_ctx *ctx, Matrix &A, int32_t k, const void *X, int64_t ldx, void *Y,
-                         int64_t ldy, uint32_t flags, hipStream_t s);
+                         int64_t ldy, uint32_t flags, hipStream_t s, bool workspace = true);
+// Bytes of the workspaces that a tuned product of k columns can do without.
+uint64_t product_workspace_bytes(mxe_ctx *ctx, Matrix &A, int32_t k);
 mxe_status ensure_variant(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneResult *out);
 int elem_bytes_of(mxe_dtype d);
 uint64_t request_bytes(const Matrix &A, int32_t k);

@@ -4,7 +4,8 @@
 //
 // One scheduler thread per context. It admits queued requests while a slot
 // is free and the HBM budget covers the resident matrices plus the vectors of
-// every request in flight. Each admission round takes up to max_batch items
+// every request in flight; a product's workspace is counted too, and left out
+// where it would not fit. Each admission round takes up to max_batch items
 // from the queue: an item is one request, or several queued requests on the
 // same matrix (permuted index space) merged into one product of up to
 // max_merge_k right-hand sides, so the matrix streams once for all of them
@@ -43,6 +44,8 @@ struct Request {
     mxe_ticket id = 0;
     mxe_item item{};
     std::shared_ptr<Matrix> mat;
+    uint64_t workspace_bytes = 0;       // that it takes as a product of its own
+    bool workspace = true;              // whether the budget has room for them
     Clock::time_point t_submit, t_done;
     int state = 0;                      // 0 queued, 1 running, 2 done
     mxe_status status = MXE_OK;
@@ -129,6 +132,16 @@ static uint64_t vector_bytes(const Matrix &A, int32_t k) {
 
 static bool batchable(const Request &r) {
     return r.item.flags == MXE_SPACE_PERMUTED && r.item.k <= 16;
+}
+
+// Whether an item of a round goes to its batch launch: a merged one, or one of
+// several that may; the others run as products of their own.
+static bool batched(const std::vector<Item> &round, const Item &it) {
+    if (it.reqs.size() > 1) return true;
+    if (!batchable(*it.reqs[0])) return false;
+    for (const Item &other : round)
+        if (&other != &it && (other.reqs.size() > 1 || batchable(*other.reqs[0]))) return true;
+    return false;
 }
 
 // staging a merged item on A may take: max_merge_k columns rounded up to their class
@@ -268,12 +281,8 @@ mxe_status Server::issue(std::vector<Item> &round, StreamSlot &slot, bool *table
     std::vector<Item> batch;
     std::vector<std::shared_ptr<Request>> single;
     for (Item &it : round) {
-        if (it.reqs.size() > 1 || batchable(*it.reqs[0])) batch.push_back(it);
+        if (batched(round, it)) batch.push_back(it);
         else single.push_back(it.reqs[0]);
-    }
-    if (batch.size() == 1 && batch[0].reqs.size() == 1) {
-        single.push_back(batch[0].reqs[0]);
-        batch.clear();
     }
     if (!batch.empty()) {
         mxe_status st = issue_batch(batch, slot);
@@ -282,7 +291,8 @@ mxe_status Server::issue(std::vector<Item> &round, StreamSlot &slot, bool *table
     }
     for (auto &r : single) {
         const mxe_item &it = r->item;
-        mxe_status st = spmv_internal(ctx, *r->mat, it.k, it.X, it.ldx, it.Y, it.ldy, it.flags, slot.s);
+        mxe_status st = spmv_internal(ctx, *r->mat, it.k, it.X, it.ldx, it.Y, it.ldy, it.flags, slot.s,
+                                      r->workspace);
         if (st) return st;
     }
     return MXE_OK;
@@ -354,6 +364,12 @@ bool Server::admit_round(std::unique_lock<std::mutex> &lk) {
         if (si < 0 || streams[i].work < streams[si].work) si = i;
     }
     if (si < 0) return false;
+    for (Item &it : round) {                            // those that run as products of their own
+        if (batched(round, it)) continue;
+        Request &r = *it.reqs[0];
+        r.workspace = !ctx->budget || resident + inflight_bytes + bytes + r.workspace_bytes <= ctx->budget;
+        if (r.workspace) bytes += r.workspace_bytes;
+    }
     for (size_t j = taken.size(); j-- > 0;) queue.erase(queue.begin() + taken[j]);
     std::vector<std::shared_ptr<Request>> reqs_of_round;
     uint64_t work = 0;
@@ -557,6 +573,7 @@ mxe_status serve_submit(mxe_ctx *ctx, const mxe_item *req, mxe_ticket *out) {
         return fail(MXE_ERR_INVALID_ARG, "bad k or leading dimension");
     if (req->flags & ~MXE_SPACE_ORIGINAL) return fail(MXE_ERR_INVALID_ARG, "unknown flags");
     std::shared_ptr<Matrix> A;
+    uint64_t workspace_bytes = 0;
     {
         std::lock_guard<std::recursive_mutex> lk(ctx->mu);
         A = find_matrix(ctx, req->mat);
@@ -566,10 +583,12 @@ mxe_status serve_submit(mxe_ctx *ctx, const mxe_item *req, mxe_ticket *out) {
         DeviceGuard g(ctx->device);
         mxe_status st = prepare_request(ctx, srv->cfg, *A, *req);
         if (st) return st;
+        workspace_bytes = product_workspace_bytes(ctx, *A, req->k);
     }
     auto r = std::make_shared<Request>();
     r->item = *req;
     r->mat = A;
+    r->workspace_bytes = workspace_bytes;
     r->t_submit = Clock::now();
     {
         std::lock_guard<std::mutex> lk(srv->mu);

@@ -229,6 +229,45 @@ def batches_of_panel_matrices_without_room_for_slabs():
         assert ctx.matrix_info(B).device_bytes == held
 
 
+def serving_within_the_budget():
+    """A lone request on a panel matrix takes its workspace where the budget has
+    room for it beside the vectors, and runs without it, same bits, where not. The
+    shim refuses blocks of the workspace's size: it counts who asks for them."""
+    A0 = synth.skewed_clustered(200_000, 2.0, 1.0, 64, 500.0, 1)
+    n, panel = A0.nrows, mx.variant(mx.VAR_PANEL)
+    x = synth.vector(n, 3)
+    X = torch_vec(x, torch.float64)
+    with mx.Context(0) as ctx:
+        A = ctx.register(A0)
+        B = ctx.permute(A, 2)
+        ctx.set_variant(B, 1, panel)
+        want = torch.empty_like(X)
+        ctx.spmv(B, X, want, flags=mx.SPACE_ORIGINAL)
+        torch.cuda.synchronize()
+        resident = sum(ctx.matrix_info(m).device_bytes for m in (A, B))
+    vectors, workspace = 16 * n, 8 * A0.nnz                  # and its padding
+    for budget, asks in ((0, True), (resident + vectors + 2 * workspace, True), (resident + vectors + 1024, False),
+                         (resident + vectors + workspace // 2, False)):
+        with mx.Context(0, budget_bytes=budget) as ctx:
+            A = ctx.register(A0)
+            B = ctx.permute(A, 2)
+            ctx.set_variant(B, 1, panel)
+            y = torch.empty_like(X)
+            ctx.spmv(B, X, y, flags=mx.SPACE_ORIGINAL)       # builds the layout
+            torch.cuda.synchronize()
+            ctx.serve_start(streams=2, max_inflight=8, max_batch=4, max_merge_k=1)
+            shim.shim_fail(workspace, -1)
+            Y = torch.full((6, n), float("nan"), dtype=torch.float64, device="cuda")
+            torch.cuda.synchronize()
+            for t in [ctx.submit(B, X, Y[i], flags=mx.SPACE_ORIGINAL) for i in range(6)]:
+                ctx.wait(t)
+            assert (shim.shim_failed() > 0) == asks, (budget, shim.shim_failed())
+            shim.shim_fail(0, 0)
+            ctx.serve_stop()
+            torch.cuda.synchronize()
+            assert all(torch.equal(row, want) for row in Y)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]]()
     print("ok", flush=True)

@@ -26,7 +26,8 @@ def shim(tmp_path_factory):
 @pytest.mark.parametrize("name", ["room_from_another_context", "tuning_without_room_for_the_panels",
                                   "products_without_a_workspace",
                                   "tuned_panels_without_room_for_the_layout",
-                                  "batches_of_panel_matrices_without_room_for_slabs"])
+                                  "batches_of_panel_matrices_without_room_for_slabs",
+                                  "serving_within_the_budget"])
 def test_without_memory(shim, name):
     r = subprocess.run([sys.executable, os.path.join(HERE, "child.py"), shim, name],
                        capture_output=True, text=True, timeout=100)
