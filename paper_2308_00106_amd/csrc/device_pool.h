@@ -164,9 +164,17 @@ class DevicePool {
             if (hipStreamWaitEvent(s, f.ev, 0) == hipSuccess) return true;
             (void)hipGetLastError();                         // the next launch is not to report it
         }
-        if (hipEventQuery(f.ev) == hipSuccess) return true;
-        (void)hipGetLastError();                             // hipErrorNotReady
-        return false;
+        return passed(f.ev);
+    }
+    // Asked in the relaxed mode: in the others the question itself ends a capture
+    // that is under way on any stream.
+    static bool passed(hipEvent_t ev) {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        const bool yes = hipEventQuery(ev) == hipSuccess;
+        if (!yes) (void)hipGetLastError();                   // hipErrorNotReady
+        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        return yes;
     }
     // A block of this size that s may use without waiting, the newest.
     bool take(void **p, size_t size, hipStream_t s) {

@@ -20,6 +20,11 @@ enum hipError_t {
     hipErrorStreamCaptureUnsupported = 900
 };
 enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 };
+enum hipStreamCaptureMode {
+    hipStreamCaptureModeGlobal = 0,
+    hipStreamCaptureModeThreadLocal = 1,
+    hipStreamCaptureModeRelaxed = 2
+};
 constexpr unsigned hipEventDisableTiming = 2;
 
 struct SimStream {
@@ -42,7 +47,8 @@ inline std::map<void *, size_t> blocks;
 inline std::vector<std::pair<void *, SimStream *>> freed_on;
 inline int mallocs = 0, frees = 0, bad_frees = 0, device_syncs = 0, event_waits = 0, events = 0, trims = 0;
 inline bool fail_free = false, fail_wait = false;
-inline int device = 0;
+inline int device = 0, unsafe_calls = 0;               // calls that would end a capture
+inline hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 inline hipError_t last = hipSuccess;
 inline hipError_t err(hipError_t e) {
     if (e != hipSuccess) last = e;
@@ -111,7 +117,12 @@ inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
     *e = SimEvent{sim::of(s), sim::of(s)->queued};
     return hipSuccess;
 }
+inline hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *m) {
+    std::swap(*m, sim::mode);
+    return hipSuccess;
+}
 inline hipError_t hipEventQuery(hipEvent_t e) {
+    if (sim::mode != hipStreamCaptureModeRelaxed) ++sim::unsafe_calls;
     return !e->s || e->s->done >= e->at ? hipSuccess : sim::err(hipErrorNotReady);
 }
 inline hipError_t hipEventSynchronize(hipEvent_t e) {

@@ -283,7 +283,7 @@ const struct {
 int main(int argc, char **argv) {
     for (const auto &t : kTests) {
         if (argc < 2) puts(t.name);
-        else if (!strcmp(argv[1], t.name)) return t.run() && sim::bad_frees == 0 ? 0 : 1;
+        else if (!strcmp(argv[1], t.name)) return t.run() && sim::bad_frees == 0 && sim::unsafe_calls == 0 && sim::mode == hipStreamCaptureModeGlobal ? 0 : 1;
     }
     return argc < 2 ? 0 : 2;
 }
