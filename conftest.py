@@ -1,0 +1,23 @@
+"""An ordering that one test leaves out.
+
+test_carry_variants_on_two_streams fills each output with NaN on the default
+stream and computes it on a side stream, with nothing that orders the two: where
+the side stream is not held up, the fill may run last. It showed as NaN, and as
+nothing else, in up to 1% of such products, and in none with the fill waited for.
+"""
+import pytest
+
+
+@pytest.fixture(autouse=True)
+def fills_end_before_other_streams_start(request, monkeypatch):
+    if getattr(request.node, "originalname", "") == "test_carry_variants_on_two_streams":
+        torch = pytest.importorskip("torch")
+        full = torch.full
+
+        def full_and_wait(*args, **kwargs):
+            out = full(*args, **kwargs)
+            torch.cuda.default_stream().synchronize()
+            return out
+
+        monkeypatch.setattr(torch, "full", full_and_wait)
+    yield
