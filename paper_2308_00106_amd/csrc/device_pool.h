@@ -26,6 +26,7 @@
 #include <list>
 #include <map>
 #include <mutex>
+#include <new>
 #include <unordered_map>
 #include <vector>
 
@@ -76,9 +77,10 @@ class DevicePool {
         if (e != hipSuccess) {
             (void)hipGetLastError();                         // the next launch is not to report it
             *p = nullptr;
-        } else if (pooled) {
-            std::lock_guard<std::mutex> lk(mu_);
-            live_[*p] = size;
+        } else if (pooled && !hand_out(*p, size)) {
+            (void)release(*p, s);
+            *p = nullptr;
+            e = hipErrorOutOfMemory;
         }
         return e;
     }
@@ -88,16 +90,17 @@ class DevicePool {
         std::lock_guard<std::mutex> lk(mu_);
         Free f{p, forget_live(p), legacy(s) ? kLegacy : kEvent, nullptr, s};
         const bool pooled = f.size > 0 && ordered(s);        // not in a capture
-        if (pooled && make_room_for(f.size, s) && record(f)) keep(f);
-        else if (!release(p, s) && pooled && (f.ev || record(f))) keep(f);
+        if (pooled && make_room_for(f.size, s) && record(f) && keep(f)) return;
+        if (!release(p, s) && pooled && (f.ev || record(f)) && keep(f)) return;
+        if (f.ev) give_event(f.ev);
     }
 
     // No work on the block is queued any more.
     void put_idle(void *p) {
         std::lock_guard<std::mutex> lk(mu_);
         const Free f{p, forget_live(p), kIdle, nullptr, nullptr};
-        if (f.size > 0 && make_room_for(f.size, nullptr)) keep(f);
-        else if (!release(p, nullptr) && f.size > 0) keep(f);
+        if (f.size > 0 && make_room_for(f.size, nullptr) && keep(f)) return;
+        if (!release(p, nullptr) && f.size > 0) (void)keep(f);
     }
 
     // An event without timing, from those given back.
@@ -110,7 +113,7 @@ class DevicePool {
     }
     void put_event(hipEvent_t ev) {
         std::lock_guard<std::mutex> lk(mu_);
-        events_.push_back(ev);
+        give_event(ev);
     }
 
   private:
@@ -183,8 +186,12 @@ class DevicePool {
         if (by == by_size_.end()) return false;
         for (auto it = by->second.rbegin(); it != by->second.rend(); ++it) {
             if (!free_on(**it, s)) continue;
+            try {
+                live_[(*it)->p] = size;
+            } catch (const std::bad_alloc &) {
+                return false;
+            }
             *p = (*it)->p;
-            live_[*p] = size;
             forget(*it);
             return true;
         }
@@ -223,6 +230,39 @@ class DevicePool {
             else if (release(at->p, at->kind == kLegacy ? nullptr : s)) forget(at);
         }
     }
+    // Calls end matrices and workspaces on their way out, so nothing here throws:
+    // without host memory for its bookkeeping a block goes back to the runtime.
+    bool hand_out(void *p, size_t size) {
+        std::lock_guard<std::mutex> lk(mu_);
+        try {
+            live_[p] = size;
+        } catch (const std::bad_alloc &) {
+            return false;
+        }
+        return true;
+    }
+    bool keep(const Free &f) {
+        try {
+            free_.push_back(f);
+        } catch (const std::bad_alloc &) {
+            return false;
+        }
+        try {
+            by_size_[f.size].push_back(std::prev(free_.end()));
+        } catch (const std::bad_alloc &) {
+            free_.pop_back();
+            return false;
+        }
+        kept_ += f.size;
+        return true;
+    }
+    void give_event(hipEvent_t ev) {
+        try {
+            events_.push_back(ev);
+        } catch (const std::bad_alloc &) {
+            (void)hipEventDestroy(ev);
+        }
+    }
     // bytes of a block handed out, 0 for one that is not the pool's
     size_t forget_live(void *p) {
         auto it = live_.find(p);
@@ -246,7 +286,7 @@ class DevicePool {
         }
         if (f.ev && hipEventRecord(f.ev, f.s) == hipSuccess) return true;
         (void)hipGetLastError();
-        if (f.ev) events_.push_back(f.ev);
+        if (f.ev) give_event(f.ev);
         f.ev = nullptr;
         return false;
     }
@@ -261,11 +301,6 @@ class DevicePool {
         }
         return kept_ + size <= limit_;
     }
-    void keep(const Free &f) {
-        free_.push_back(f);
-        by_size_[f.size].push_back(std::prev(free_.end()));
-        kept_ += f.size;
-    }
     void forget(Node at) {
         auto by = by_size_.find(at->size);
         auto &v = by->second;
@@ -276,7 +311,7 @@ class DevicePool {
             }
         if (v.empty()) by_size_.erase(by);
         kept_ -= at->size;
-        if (at->ev) events_.push_back(at->ev);
+        if (at->ev) give_event(at->ev);
         free_.erase(at);
     }
 

@@ -55,6 +55,8 @@ inline hipError_t err(hipError_t e) {
     return e;
 }
 inline SimStream *of(SimStream *s);
+int pause_host_failures();                             // the stand-in's own memory does not fail
+void resume_host_failures(int left);
 }  // namespace sim
 
 #define hipStreamLegacy (&sim::legacy)
@@ -73,7 +75,9 @@ inline hipError_t hipGetDevice(int *d) {
 inline hipError_t hipMallocAsync(void **p, size_t bytes, hipStream_t) {
     if (bytes > sim::capacity - sim::held) return sim::err(hipErrorOutOfMemory);
     *p = malloc(1);
+    const int left = sim::pause_host_failures();
     sim::blocks[*p] = bytes;
+    sim::resume_host_failures(left);
     sim::held += bytes;
     ++sim::mallocs;
     return hipSuccess;
@@ -104,7 +108,9 @@ inline hipError_t hipDeviceSynchronize() {
     return hipSuccess;
 }
 inline hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+    const int left = sim::pause_host_failures();
     *e = new SimEvent();
+    sim::resume_host_failures(left);
     ++sim::events;
     return hipSuccess;
 }

@@ -3,11 +3,30 @@
 #include "device_pool.h"
 
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <new>
 #include <utility>
 #include <vector>
 
 using mxe::DevicePool;
+
+// the host's own allocations fail once `allocations_left` has run out (-1: never)
+static int allocations_left = -1;
+void *operator new(size_t n) {
+    if (allocations_left == 0) throw std::bad_alloc();
+    if (allocations_left > 0) --allocations_left;
+    if (void *p = malloc(n)) return p;
+    throw std::bad_alloc();
+}
+int sim::pause_host_failures() {
+    const int left = allocations_left;
+    allocations_left = -1;
+    return left;
+}
+void sim::resume_host_failures(int left) { allocations_left = left; }
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 #define CHECK(c)                                                     \
     do {                                                             \
@@ -247,6 +266,37 @@ bool counted_blocks_fit() {
     return true;
 }
 
+// Without host memory for the bookkeeping nothing throws and no block is lost.
+bool no_host_memory() {
+    for (int left = 0; left < 12; ++left) {
+        {
+            DevicePool pool(0);
+            SimStream a;
+            void *p[3], *q = nullptr;
+            for (auto &x : p) CHECK(pool.get(&x, kMiB, &a) == hipSuccess);
+            hipEvent_t ev;
+            CHECK(pool.event(&ev) == hipSuccess);
+            sim::freed_on.reserve(100);
+            allocations_left = left;
+            pool.put(p[0], &a);
+            pool.put(p[1], nullptr);
+            pool.put_idle(p[2]);
+            pool.put_event(ev);
+            allocations_left = -1;
+            work(a);
+            for (int i = 0; i < 2; ++i) {
+                allocations_left = left;
+                const bool got = pool.get(&q, kMiB, &a) == hipSuccess;
+                allocations_left = -1;
+                CHECK(got == (q != nullptr));
+                if (got) pool.put(q, &a);
+            }
+        }
+        CHECK(sim::held == 0 && sim::events == 0);
+    }
+    return true;
+}
+
 // Everything goes back with the pool, events too.
 bool all_returned() {
     {
@@ -275,6 +325,7 @@ const struct {
     {"optional_blocks_wait_for_nothing", optional_blocks_wait_for_nothing},
     {"no_room_in_a_capture", no_room_in_a_capture},
     {"counted_blocks_fit", counted_blocks_fit},
+    {"no_host_memory", no_host_memory},
     {"all_returned", all_returned},
 };
 
