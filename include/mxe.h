@@ -196,7 +196,8 @@ mxe_status mxe_spmv(mxe_ctx *ctx, mxe_mat m, int32_t k, const void *X, int64_t l
 /* Semirings for mxe_spmv_semiring (Section 2 defines the product on (+, *)
  * and notes it extends to others). */
 #define MXE_SR_PLUS_TIMES 0   /* y_i = sum of v * x: the same as mxe_spmv */
-#define MXE_SR_MIN_PLUS   1   /* y_i = min over row i's stored entries of v + x; +inf if none */
+#define MXE_SR_MIN_PLUS   1   /* y_i = min over row i's stored entries of v + x; +inf if none
+                               * (a v + x that is NaN counts as none) */
 #define MXE_SR_OR_AND     2   /* y_i = 1 if a stored v != 0 meets x != 0 in row i, else 0 */
 
 /* Y = M X over `semiring`, otherwise as mxe_spmv (k >= 1, index spaces,

@@ -194,8 +194,9 @@ __device__ inline float bf16_to_f32(uint16_t b) {
 
 // Semirings of the product (MXE_SR_* in mxe.h: 0 (+, *), 1 (min, +), 2 (or,
 // and)), Section 2: identity of the sum, the product of a value and an x, the
-// sum. min and or are exact; a min accumulator only ever takes a smaller
-// term, so it never turns NaN.
+// sum. min and or are exact. A term of (min, +) that is NaN is no path: it
+// becomes the identity here, where it arises, since a partial minimum that was
+// NaN would keep every term joined to it out of the sum.
 template <int SR, typename T> struct Semiring;
 template <typename T> struct Semiring<0, T> {
     __device__ static T identity() { return T(0); }
@@ -204,7 +205,10 @@ template <typename T> struct Semiring<0, T> {
 };
 template <typename T> struct Semiring<1, T> {
     __device__ static T identity() { return T(__builtin_inf()); }
-    __device__ static T mul(T a, T x) { return a + x; }
+    __device__ static T mul(T a, T x) {
+        const T m = a + x;
+        return m == m ? m : identity();
+    }
     __device__ static T add(T p, T q) { return q < p ? q : p; }
 };
 template <typename T> struct Semiring<2, T> {

@@ -205,12 +205,9 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_fill(
 // Entries per lane and load: 16 bytes of value where that is at most 4 entries.
 template <typename V> struct PanelVec { static constexpr int N = sizeof(V) == 8 ? 2 : 4; };  // divides the runs' 4
 
-// One entry's product; a NaN is no path in (min, +).
 template <int SR, typename V, typename T>
 __device__ inline T panel_product(V v, T x) {
-    const T m = Semiring<SR, T>::mul(PanelVal<V, T>::get(v), x);
-    if constexpr (SR == 1) return m == m ? m : Semiring<SR, T>::identity();
-    else return m;
+    return Semiring<SR, T>::mul(PanelVal<V, T>::get(v), x);
 }
 
 // First pass. Bound by memory bandwidth: value and offset read and product
