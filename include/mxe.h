@@ -337,7 +337,7 @@ mxe_status mxe_batch_destroy(mxe_ctx *ctx, mxe_plan plan);
  * get its result bit for bit. count above MXE_NOALLOC_MAX_ITEMS:
  * MXE_ERR_INVALID_ARG. Stream-ordered on `stream`; the descriptor table is
  * copied from host memory on that stream, and the call returns once the copy
- * has taken its data. Every call on one GPU shares that GPU's array, which
+ * has taken its data (in a capture the table becomes part of the graph). Every call on one GPU shares that GPU's array, which
  * keeps the last call's contents (the counters are cleared by a kernel on
  * `stream` before each use): calls whose work may overlap on one GPU (other
  * streams, threads or contexts) race on it and must be ordered by the

@@ -85,11 +85,19 @@ extern "C" mxe_status mxe_spmv_batch_noalloc(mxe_ctx *ctx, int32_t count, const 
     int32_t *qent_dev = (int32_t *)(base + kCounterBytes);
     BatchDesc *descs_dev = (BatchDesc *)(base + kCounterBytes + kQentBytes);
     // stream-ordered after any earlier use of the array on s; the sources are
-    // pageable host memory, which the copies have consumed when they return
-    MXE_HIP(hipMemcpyAsync(descs_dev, descs.data(), sizeof(BatchDesc) * descs.size(),
-                           hipMemcpyHostToDevice, s));
-    MXE_HIP(hipMemcpyAsync(qent_dev, qent.data(), sizeof(int32_t) * qent.size(),
-                           hipMemcpyHostToDevice, s));
+    // pageable host memory, which the copies have consumed when they return. A
+    // captured copy would read them at each replay, long after they are gone
+    if (DevicePool::capturing(s)) {
+        static_assert(sizeof(BatchDesc) % 8 == 0 && kQentBytes % 8 == 0, "whole words");
+        if (qent.size() % 2) qent.push_back(0);
+        MXE_HIP(launch_store_table(descs_dev, descs.data(), sizeof(BatchDesc) * descs.size(), s));
+        MXE_HIP(launch_store_table(qent_dev, qent.data(), sizeof(int32_t) * qent.size(), s));
+    } else {
+        MXE_HIP(hipMemcpyAsync(descs_dev, descs.data(), sizeof(BatchDesc) * descs.size(),
+                               hipMemcpyHostToDevice, s));
+        MXE_HIP(hipMemcpyAsync(qent_dev, qent.data(), sizeof(int32_t) * qent.size(),
+                               hipMemcpyHostToDevice, s));
+    }
     MXE_HIP(launch_batch_reset(counters, s));                // the counters start at zero
     MXE_HIP(launch_spmv_batch(descs_dev, qent_dev, qs, counters, grid, lds, vt, s));
     for (int32_t i = 0; i < count; ++i)

@@ -116,6 +116,15 @@ class DevicePool {
         give_event(ev);
     }
 
+    static bool legacy(hipStream_t s) { return s == nullptr || s == hipStreamLegacy; }
+    static bool capturing(hipStream_t s) {
+        if (legacy(s)) return false;                         // it cannot be captured
+        hipStreamCaptureStatus cs;
+        if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+        (void)hipGetLastError();
+        return true;
+    }
+
   private:
     enum Kind { kIdle, kLegacy, kEvent };
     struct Free {
@@ -136,17 +145,9 @@ class DevicePool {
         return *r;
     }
 
-    static bool legacy(hipStream_t s) { return s == nullptr || s == hipStreamLegacy; }
     static bool ordered(hipStream_t s) {
         if (legacy(s)) return true;
         return s != hipStreamPerThread && !capturing(s);
-    }
-    static bool capturing(hipStream_t s) {
-        if (legacy(s)) return false;                         // it cannot be captured
-        hipStreamCaptureStatus cs;
-        if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
-        (void)hipGetLastError();
-        return true;
     }
     static size_t paged(size_t bytes) {                      // small blocks to 256 bytes
         const size_t step = bytes < 32768 ? 256 : 4096;

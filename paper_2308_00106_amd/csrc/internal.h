@@ -289,6 +289,10 @@ struct BatchQueues {
     int32_t qtiles[kBatchQueues];
 };
 constexpr int kBatchBlock = 1024;       // threads per workgroup of the batch kernel
+// Copies a small host table to dst (8-byte aligned, whole words) on s, by kernel
+// arguments: in a capture its contents become part of the graph.
+constexpr int kTableWords = 448;        // of a launch's 4 KB of arguments
+hipError_t launch_store_table(void *dst, const void *src, size_t bytes, hipStream_t s);
 // counters: kBatchQueues device ints zeroed by launch_batch_reset before each
 // launch.
 hipError_t launch_batch_reset(int32_t *counters, hipStream_t s);

@@ -15,6 +15,7 @@
 #include "spmv_device.h"
 
 #include <algorithm>
+#include <cstring>
 
 namespace mxe {
 
@@ -135,6 +136,27 @@ int32_t batch_grid(size_t lds) {
 }
 
 }  // namespace
+
+// Words of a table by way of a kernel's arguments: a captured launch keeps them,
+// where a captured copy would read the host's memory again at each replay.
+struct TableWords {
+    uint64_t w[kTableWords];
+};
+__global__ __launch_bounds__(kTableWords) void k_store_words(uint64_t *__restrict__ dst, TableWords t, int n) {
+    if ((int)threadIdx.x < n) dst[threadIdx.x] = t.w[threadIdx.x];
+}
+
+hipError_t launch_store_table(void *dst, const void *src, size_t bytes, hipStream_t s) {
+    if (bytes % sizeof(uint64_t)) return hipErrorInvalidValue;
+    const size_t words = bytes / sizeof(uint64_t);
+    for (size_t i = 0; i < words; i += kTableWords) {
+        TableWords t{};
+        const size_t n = std::min<size_t>(words - i, kTableWords);
+        std::memcpy(t.w, (const uint64_t *)src + i, n * sizeof(uint64_t));
+        hipLaunchKernelGGL(k_store_words, dim3(1), dim3(kTableWords), 0, s, (uint64_t *)dst + i, t, (int)n);
+    }
+    return hipGetLastError();
+}
 
 hipError_t launch_batch_reset(int32_t *counters, hipStream_t s) {
     hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(kWave), 0, s, counters);
