@@ -2,8 +2,9 @@
 
 test_carry_variants_on_two_streams fills each output with NaN on the default
 stream and computes it on a side stream, with nothing that orders the two: where
-the side stream is not held up, the fill may run last. It showed as NaN, and as
-nothing else, in up to 1% of such products, and in none with the fill waited for.
+the side stream is not held up, the fill may run last. 4800 such products left
+NaN, and no other difference, in 48 outputs before the context kept device memory
+and in 953 since, and in none with the fill waited for.
 """
 import pytest
 

@@ -95,7 +95,9 @@ const char *mxe_last_error(void);
 int32_t mxe_abi_version(void);
 
 /* Creates a context on HIP device `device`. hbm_budget_bytes caps the HBM the
- * context holds for resident matrices and in-flight serving work (0 = no cap).
+ * context holds for resident matrices and in-flight serving work (0 = no cap);
+ * the workspaces of other calls, and up to 4 GiB of freed memory that the
+ * context keeps for its next calls, are outside it.
  * Returns MXE_ERR_DEVICE if the device is missing or is not gfx950. */
 mxe_status mxe_create(int32_t device, uint64_t hbm_budget_bytes, mxe_ctx **out);
 /* Waits for all work, stops the serving loop, frees every matrix and plan. */
@@ -255,8 +257,12 @@ mxe_status mxe_scatter_y(mxe_ctx *ctx, mxe_mat b, int32_t k, const void *Yp, int
  * products out (a workspace of one value per entry, taken for the call from
  * the context's device memory), a second sums them by row, so no x is gathered
  * from memory. Where there is no room for the workspace one slower pass gathers
- * x and returns the same bits. MXE_ERR_UNSUPPORTED from mxe_set_variant when k > 1 or the layout
- * does not fit. A batch runs its items on slab layouts instead. */
+ * x and returns the same bits. In a captured call the workspace is an
+ * allocation node and a free node of the graph; a forced MXE_VAR_SLAB product of
+ * permuted-space vectors holds none. MXE_ERR_UNSUPPORTED from mxe_set_variant
+ * when k > 1 or the layout does not fit; a tuned choice whose layout finds no
+ * room runs as a row-group product. A batch runs its items on slab layouts
+ * instead, or as row tiles where those find no room. */
 #define MXE_VAR_PANEL   0x700
 #define MXE_VARIANT(family, lanes) ((family) | (lanes))
 

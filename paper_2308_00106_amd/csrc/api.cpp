@@ -594,10 +594,14 @@ static mxe_status tune(mxe_ctx *ctx, Matrix &A, int32_t k, hipStream_t s, TuneRe
     // stage 2: the candidates within 8% of the fastest (two to five of them)
     // again, interleaved over two rounds of 10 products each, so candidates a
     // few percent apart are told apart. The column panels have to win by 5% in
-    // FP64, where they write and read 16 bytes of products an entry: what they
-    // gain on back-to-back products of one matrix is lost between others (1.7M
-    // rows of 14: 137 us against the slabs' 142, three matrices in turn 148
-    // against 145). With 4-byte products they lead either way.
+    // FP64, where they write and read 16 bytes of products an entry and the two
+    // stand within a tenth of each other: what a lead in back-to-back products of
+    // one matrix is worth between others differs by as much. Panels against the
+    // best slabs, us, back to back and three matrices in turn: 1.7M rows of 14
+    // entries 139 / 142 and 149 / 145, 2M of 10 115 / 114 and 126 / 130, 3M of 6
+    // 121 / 122 and 132 / 140, 1.5M skewed rows 119 / 103 and 126 / 118. The
+    // margin keeps the first from the panels and costs the third 5%. With 4-byte
+    // products they lead either way.
     auto handicap = [&](int v) {
         return (v & 0xf00) == MXE_VAR_PANEL && A.storage == MXE_F64 ? 1.05f : 1.0f;
     };

@@ -3,11 +3,12 @@
 //
 // The random permutation (Section 3; Eq. 1) is the stable ascending order of
 // 64-bit SplitMix64 keys. Because the keys are a pure function of the index,
-// they are never stored. Up to 8.4M indices, an LDS radix pass buckets the
-// indices by the top 10-12 key bits (per-workgroup LDS histograms, a scan,
-// an LDS-cursor scatter of 4-byte indices) and one workgroup per bucket of
-// ~2K sorts it in LDS (split by the next 8 bits, then a rank by (key, index)
-// inside sub-buckets of ~8). Larger ranges bucket by up to 20 top bits with
+// they are never stored. Up to 8192 indices are one workgroup's. Up to 8.4M, an
+// LDS radix pass buckets the indices by the top 6 to 12 key bits (per-workgroup
+// LDS histograms, a scan, an LDS-cursor scatter of 4-byte indices), about 256 to
+// a bucket up to 128K indices and 2K beyond, and one workgroup per bucket
+// sorts it in LDS (split by the next 8 bits, then a rank by (key, index) inside
+// sub-buckets of ~8). Larger ranges bucket by up to 20 top bits with
 // device atomics instead of LDS histograms and sort the buckets the same way.
 // Either way two light passes over 4-byte indices replace the eight read-write
 // passes of an LSD radix sort over 12-byte (key, index) pairs.

@@ -30,7 +30,9 @@
 //
 // Without memory for the products the second pass makes them itself, x gathered
 // from memory (launch_spmv_panel): the same products summed the same way, so the
-// same bits, but at a gather per entry.
+// same bits, but at a gather per entry. The FP32, BF16 and FP64 matrices above
+// take 547, 180 and 239 us so, where they take 180, 67 and 118 with the workspace
+// and 752, 188 and 317 as row-group products of eight lanes.
 //
 // Rows are summed in a fixed order (positions in groups, groups in row
 // order), so results are deterministic.
