@@ -170,15 +170,26 @@ class DevicePool {
         }
         return passed(f.ev);
     }
-    // Asked in the relaxed mode: in the others the question itself ends a capture
-    // that is under way on any stream.
+    // The thread's relaxed capture mode: in the others asking for an event or
+    // waiting ends a capture that is under way on any stream.
+    class Relaxed {
+      public:
+        Relaxed() : set_(hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess) {}
+        ~Relaxed() {
+            if (set_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+        }
+        Relaxed(const Relaxed &) = delete;
+        Relaxed &operator=(const Relaxed &) = delete;
+
+      private:
+        hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+        const bool set_;
+    };
     static bool passed(hipEvent_t ev) {
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-        const bool yes = hipEventQuery(ev) == hipSuccess;
-        if (!yes) (void)hipGetLastError();                   // hipErrorNotReady
-        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
-        return yes;
+        const Relaxed r;
+        if (hipEventQuery(ev) == hipSuccess) return true;
+        (void)hipGetLastError();                             // hipErrorNotReady
+        return false;
     }
     // A block of this size that s may use without waiting, the newest.
     bool take(void **p, size_t size, hipStream_t s) {
@@ -202,6 +213,7 @@ class DevicePool {
     // and then what the runtime itself holds unused. Waits for the blocks' last
     // uses, not for the device.
     void make_room(hipStream_t s) {
+        const Relaxed relaxed;
         Registry &r = registry();
         {
             std::lock_guard<std::mutex> lk(r.mu);

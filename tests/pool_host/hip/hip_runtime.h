@@ -100,6 +100,7 @@ inline hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *cs
     return hipSuccess;
 }
 inline hipError_t hipStreamSynchronize(hipStream_t s) {
+    if (sim::mode != hipStreamCaptureModeRelaxed) ++sim::unsafe_calls;
     sim::of(s)->done = sim::of(s)->queued;
     return hipSuccess;
 }
@@ -132,6 +133,7 @@ inline hipError_t hipEventQuery(hipEvent_t e) {
     return !e->s || e->s->done >= e->at ? hipSuccess : sim::err(hipErrorNotReady);
 }
 inline hipError_t hipEventSynchronize(hipEvent_t e) {
+    if (sim::mode != hipStreamCaptureModeRelaxed) ++sim::unsafe_calls;
     ++sim::event_waits;
     if (e->s && e->s->done < e->at) const_cast<SimStream *>(e->s)->done = e->at;
     return hipSuccess;
@@ -143,6 +145,7 @@ inline hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
 }
 inline hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t *, int) { return hipSuccess; }
 inline hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) {
+    if (sim::mode != hipStreamCaptureModeRelaxed) ++sim::unsafe_calls;
     ++sim::trims;
     return hipSuccess;
 }
