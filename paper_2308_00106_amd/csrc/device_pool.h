@@ -8,8 +8,9 @@
 // reused on the stream of its last use, or anywhere once the event recorded
 // there has passed; without such a block the call takes a new one. (Taking the
 // newest block behind a wait, two streams that issued the same product in turn
-// ran one after the other for good.) Blocks last used on the legacy stream
-// carry no event and stay with it. What lies unused is bounded (kPoolKeep) and goes
+// ran one after the other for good: 400K skewed FP64 rows in their original order
+// took 69 us a product on two streams and 55 on one, now 44 and 55.) Blocks last
+// used on the legacy stream carry no event and stay with it. What lies unused is bounded (kPoolKeep) and goes
 // back to the runtime past that, when an allocation fails, and with the
 // context: the oldest blocks that are free by now go first, and where they are
 // not enough the block being given back, again without a stream waiting for
