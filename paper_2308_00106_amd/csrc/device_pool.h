@@ -4,20 +4,22 @@
 // (9 us where only one size is ever asked for), more than most kernels here.
 //
 // Blocks are rounded up to an eighth of a power of two, where a budget counts
-// them or memory is short to whole pages only, and reused by size, but never so that one stream waits for another's work: a block given back is
-// reused on the stream of its last use, or anywhere once the event recorded
-// there has passed; without such a block the call takes a new one. (Taking the
-// newest block behind a wait, two streams that issued the same product in turn
-// ran one after the other for good: 400K skewed FP64 rows in their original order
-// took 69 us a product on two streams and 55 on one, now 44 and 55.) Blocks last
-// used on the legacy stream carry no event and stay with it. What lies unused is bounded (kPoolKeep) and goes
-// back to the runtime past that, when an allocation fails, and with the
-// context: the oldest blocks that are free by now go first, and where they are
-// not enough the block being given back, again without a stream waiting for
-// another. An allocation that fails takes back what lies unused in every
-// context of the device. While a stream is captured its blocks come from the runtime, as
-// nodes of the graph, and so do those of the per-thread stream, whose handle
-// does not say which stream it is.
+// them or memory is short to whole pages only, and reused by size, but never
+// so that one stream waits for another's work: a block given back is reused on
+// the stream of its last use, or anywhere once the event recorded there has
+// passed; without such a block the call takes a new one. (Taking the newest
+// block behind a wait, two streams that issued the same product in turn ran
+// one after the other for good: 400K skewed FP64 rows in their original order
+// took 69 us a product on two streams and 55 on one, now 44 and 55.) Blocks
+// last used on the legacy stream carry no event and stay with it. What lies
+// unused is bounded (kPoolKeep) and goes back to the runtime past that, when
+// an allocation fails, and with the context: the oldest blocks that are free
+// by now go first, and where they are not enough the block being given back,
+// again without a stream waiting for another. An allocation that fails takes
+// back what lies unused in every context of the device. While a stream is
+// captured its blocks come from the runtime, as nodes of the graph, and so do
+// those of the per-thread stream, whose handle does not say which stream it
+// is.
 #pragma once
 
 #include <hip/hip_runtime.h>
